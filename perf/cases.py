@@ -35,29 +35,29 @@ def _line(name, rics, r_eq, cells, ppc, steps, **kw):
 def listed():
     return [
         # one step of a small line, its diagnostics after each: launches and latency
-        _line("small line, single steps", "table", 4.0, 512, 64, 1, gamma_max=1.0e3, n_max=12.0,
+        _line("small line single steps", "table", 4.0, 512, 64, 1, gamma_max=1.0e3, n_max=12.0,
               conversion="curvature", atmosphere=True, sort=10, warm=40),
         # the same size as a batch job: many steps a call, replayed from graphs
-        _line("small line, graph", "table", 4.0, 512, 64, 100, gamma_max=1.0e3, n_max=12.0, conversion="curvature",
+        _line("small line graph", "table", 4.0, 512, 64, 100, gamma_max=1.0e3, n_max=12.0, conversion="curvature",
               atmosphere=True, sort=10, graph=100, warm=40),
         # an ordinary line of odd size by the closed forms, with angle-resolved emission
-        _line("odd line, closed forms", "exact", 4.0, 9973, 61, 20, emission="dipole", atmosphere=True,
+        _line("odd line closed forms", "exact", 4.0, 9973, 61, 20, emission="dipole", atmosphere=True,
               sort=10),
         # the field line of the headline run after it has heated (most of its 20,000 steps)
-        _line("long line, heated", "table", 30.0, 65536, 200, 50, init="cold", n_max=0.0, conversion="curvature",
+        _line("long line heated", "table", 30.0, 65536, 200, 50, init="cold", n_max=0.0, conversion="curvature",
               atmosphere=True, sort=50, warm=3000),
         # the hot cascade held at the density limit: events, pairs and annihilation in every cell
         _line("hot line at the limit", "table", 4.0, 65536, 200, 10, warm=60),
         # many uneven lines in one state
-        dict(name="many lines, graph", kind="step", lines=40, rics="table", steps=50, graph=50, sort=50, warm=50),
+        dict(name="many lines graph", kind="step", lines=40, rics="table", steps=50, graph=50, sort=50, warm=50),
         # the cascade on several long lines with atmospheres and ions, towards the density limit
         dict(name="cascade lines", kind="cascade", lines=8, rics="table", cells=32768, ppc=84, steps=20, graph=0,
              sort=50, warm=150),
         # the surrogate network in the pusher
         _line("surrogate line", "mlp", 4.0, 16384, 100, 5, warm=10),
         # the network on its own: a query, a large ragged batch, a training batch, a training run
-        dict(name="forward, small", kind="forward", n=1000),
-        dict(name="forward, large", kind="forward", n=1000003),
+        dict(name="forward small", kind="forward", n=1000),
+        dict(name="forward large", kind="forward", n=1000003),
         dict(name="gradient", kind="gradient", n=8192),
         dict(name="train", kind="train", pool=1 << 18, batch=8192, steps=100),
     ]
