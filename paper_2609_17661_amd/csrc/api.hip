@@ -83,6 +83,7 @@ struct pic1d_state {
     double* rc_nodes = nullptr;
     float4* table = nullptr;
     int32_t *ann_k = nullptr, *ann_off = nullptr, *ann_fill = nullptr, *ann_ctl = nullptr;
+    uint32_t* ann_thr = nullptr;
     int32_t *layer_cell = nullptr, *layer_line = nullptr, *layer_target = nullptr;
     unsigned long long* counters = nullptr;
     DevScalars* sc = nullptr;
@@ -231,6 +232,7 @@ void carve(Carver& cv, const Layout& L, pic1d_state* st) {
     s->table = cv.take<float4>(std::max<int64_t>(L.table_floats / 4, 1));
     s->ann_k = cv.take<int32_t>(L.n_cells);
     s->ann_off = cv.take<int32_t>(L.n_cells);
+    s->ann_thr = cv.take<uint32_t>(L.n_cells);
     s->ann_fill = cv.take<int32_t>(2 * (size_t)L.n_cells);
     s->ann_ctl = cv.take<int32_t>(4);
     s->layer_cell = cv.take<int32_t>(std::max(L.n_layer, 1));
@@ -699,7 +701,7 @@ int enqueue_step(pic1d_state* st) {
             an.hist[0] = st->hist[0]; an.hist[1] = st->hist[1];
             an.cell_line = st->cell_line; an.lines = st->dlines;
             an.n_total = nt; an.n_lines = st->lay.n_lines;
-            an.ann_k = st->ann_k; an.ann_off = st->ann_off; an.ann_fill = st->ann_fill; an.ann_ctl = st->ann_ctl;
+            an.ann_k = st->ann_k; an.ann_off = st->ann_off; an.ann_thr = st->ann_thr; an.ann_fill = st->ann_fill; an.ann_ctl = st->ann_ctl;
             // candidate records in the other particle buffer set (written only by the sort)
             an.cand_key = st->id[1 - b];
             an.cand_slot = st->cell[1 - b];
@@ -716,8 +718,10 @@ int enqueue_step(pic1d_state* st) {
         }
         // Ampere; its last block plans the next push and advances the step counter
         const int pk = prof_begin(st, 2);
-        // 64 cells per wavefront, 4 with annihilation (k_field's cells per wavefront)
-        const int field_cells = f.annihilation ? 16 : 256;
+        // 64 cells per wavefront; with annihilation 4, or 1 up to 64 cells per CU in all:
+        // there four selections one after another leave the chip idle (9,973 cells: k_field
+        // 48 us at 4, 24 us at 1), beyond it the extra blocks of the quiet steps cost more
+        const int field_cells = !f.annihilation ? 256 : nt <= 64 * st->n_cu ? 4 : 16;
         // (and one more block for the bookkeeping)
         hipLaunchKernelGGL(k_field, dim3(std::min(16 * st->aux_blocks, (nt + field_cells - 1) / field_cells) + 1),
                            dim3(256), 0, st->stream, f, book_args(st));

@@ -129,8 +129,8 @@ struct BookArgs {
 
 // Pair annihilation at the density limit (Sec. 3).  Per step, after the appends:
 // k_annih_plan sizes every cell's annihilation from its end-of-step counts,
-// k_annih_gather records the candidates (every e-/e+ of a cell over the limit),
-// and k_field selects and removes them before Ampere.  The candidate records
+// k_annih_gather records the candidates (the e-/e+ of a cell over the limit with the
+// smaller keys), and k_field selects and removes them before Ampere.  The candidate records
 // live in the particle buffer set the sort scatters into, idle between sorts.
 struct AnnihArgs {
     int32_t* cell;              // the live particle buffer set
@@ -147,6 +147,7 @@ struct AnnihArgs {
     int32_t n_lines;
     int32_t* ann_k;             // per global cell: pairs to annihilate this step, 0 if none
     int32_t* ann_off;           // per global cell: first candidate record (e- then e+)
+    uint32_t* ann_thr;          // per global cell: largest high key word recorded, 0 if none
     int32_t* ann_fill;          // per global cell and species 0/1: candidates recorded
     int32_t* ann_ctl;           // [0] records allocated, [1] cells over the limit (this step),
                                 //   [2] its copy for the field kernel

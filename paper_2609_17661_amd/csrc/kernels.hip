@@ -1268,14 +1268,23 @@ __global__ __launch_bounds__(256) void k_plan(BookArgs b, int advance_step) {
 // positions the push deposits from), and the neutral pair leaves no charge.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ uint64_t annih_key(uint64_t step, uint64_t id, uint32_t k0, uint32_t k1) {
-    const uint4 w = philox4x32_10(make_uint4((uint32_t)step, (uint32_t)id, (uint32_t)(id >> 32), STREAM_ANNIH),
-                                  k0, k1);
+    const uint4 w = philox4x32_10_wide(make_uint4((uint32_t)step, (uint32_t)id, (uint32_t)(id >> 32), STREAM_ANNIH),
+                                       k0, k1);
     return ((uint64_t)w.y << 32) | (uint64_t)w.x;
 }
 
+// The gather records only the candidates whose key's high word is at most the
+// cell's threshold, which admits lambda = k + 8 k^1/2 + 20 of the m keys of the
+// smaller species on average (the keys are uniform): fewer than k of them pass with
+// a probability below 1e-12 a cell, and k_field then records the whole cell.
+__device__ __forceinline__ uint32_t annih_threshold(int k, int m) {
+    const float lam = (float)k + 8.0f * sqrtf((float)k) + 20.0f;
+    return lam < (float)m ? (uint32_t)(lam / (float)m * 4294967040.0f) : 0xffffffffu;
+}
 
 // Every cell's k from its end-of-step counts, and for the cells over the limit a
-// run of candidate records (their e- then their e+), one allocation per block.
+// run of candidate records (room for all their e- then their e+), one allocation
+// per block.
 __global__ __launch_bounds__(256) void k_annih_plan(AnnihArgs a) {
     if (a.sc->err != 0) return;
     const uint64_t step = a.sc->step;
@@ -1283,10 +1292,11 @@ __global__ __launch_bounds__(256) void k_annih_plan(AnnihArgs a) {
     __shared__ int s_base;
     for (int g0 = blockIdx.x * 256; g0 < a.n_total; g0 += gridDim.x * 256) {
         const int g = g0 + (int)threadIdx.x;
-        int k = 0, need = 0;
+        int k = 0, need = 0, h0 = 0, h1 = 0;
         if (g < a.n_total) {
             const int* h = hist_out + 4 * (size_t)g;
-            const int h0 = h[0], h1 = h[1];
+            h0 = h[0];
+            h1 = h[1];
             const int N = h0 + h1 + h[2] + h[3];
             const double nmax = (double)a.lines[a.cell_line[g]].nmax;
             if ((double)N > nmax) k = (int)fmin(fmin((double)h0, (double)h1), ceil(((double)N - nmax) * 0.5));
@@ -1310,7 +1320,10 @@ __global__ __launch_bounds__(256) void k_annih_plan(AnnihArgs a) {
                 a.ann_fill[2 * (size_t)g + 1] = 0;
             }
         }
-        if (g < a.n_total) a.ann_k[g] = k;
+        if (g < a.n_total) {
+            a.ann_k[g] = k;
+            a.ann_thr[g] = k > 0 ? annih_threshold(k, min(h0, h1)) : 0u;
+        }
         __syncthreads();
     }
 }
@@ -1442,39 +1455,137 @@ __device__ uint32_t annih_select_regs(const AnnihArgs& a, int64_t rec0, int64_t 
     return taken;
 }
 
-// One wavefront removes cell g's k annihilating pairs (every lane calls it with
-// the same g and k): per species a most-significant-bit-first radix select finds
-// the k-th smallest key, keys below it are taken and keys equal to it (in
-// practice only itself) by rank of id.  Returns (to every lane) the annihilation
-// current in the deposit's units (2^-28 cell); the caller adds it to J[g] and
-// takes k off the cell's e-/e+ counts.
-__device__ long long annihilate_cell(const AnnihArgs& a, const int32_t* hist_out, int g, int k, int* hist) {
+// Removes the particle in a slot; returns its quantised offset (2^-28 cell).
+__device__ __forceinline__ long long annih_remove(const AnnihArgs& a, int64_t kidx) {
+    const long long q = (long long)(int)(a.off[kidx] * POS_SCALE);
+    a.cell[kidx] = DEAD_CELL;
+    a.off[kidx] = 0.5f;
+    a.u[kidx] = 0.0f;
+    return q;
+}
+
+// Records every e- (s = 0) or e+ (s = 1) of local cell c of a segment, where the
+// gather's threshold let fewer than k through; returns how many.
+__device__ __forceinline__ int annih_record_all(const AnnihArgs& a, uint64_t step, int seg, int c, int64_t rec0, int room) {
     const int lane = threadIdx.x & 63;
-    const int line = a.cell_line[g];
-    const int* h = hist_out + 4 * (size_t)g;
-    const int h0 = h[0], h1 = h[1];
-    // every e- and e+ of the cell must have been recorded (records beyond those
-    // written hold stale data of the other buffer set and are never read)
-    if (a.ann_fill[2 * (size_t)g] != h0 || a.ann_fill[2 * (size_t)g + 1] != h1) {
+    const int n = min(a.alloc[seg], a.seg_cap[seg]);
+    const int64_t base = a.seg_base[seg];
+    int found = 0;
+    for (int64_t i0 = 0; i0 < n; i0 += 64) {
+        const int64_t i = i0 + lane;
+        const bool mine = i < n && a.cell[base + i] == c;
+        const unsigned long long m = __ballot(mine);
+        const int r = found + __popcll(m & ((1ull << lane) - 1ull));
+        if (mine && r < room) {
+            a.cand_key[rec0 + r] = annih_key(step, a.id[base + i], a.key0, a.key1);
+            a.cand_slot[rec0 + r] = (int)i;
+        }
+        found += __popcll(m);
+    }
+    __threadfence();                     // the records are read back by other lanes of the wavefront
+    return found;
+}
+
+__device__ __forceinline__ uint32_t lane_word(uint32_t v, int l) {
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, l);
+}
+
+// Whether this lane's key (lane < m) is among the k smallest (key, id) of m <= 64
+// records: its rank by one comparison of the high words with every other key's,
+// broadcast from its lane through a scalar register -- no reduction over the
+// wavefront, and one load per lane in all.  If exactly k lanes rank below k these are
+// the k smallest; otherwise equal high words lie around the k-th, and the whole keys
+// and the ids decide.
+__device__ __forceinline__ bool annih_rank64(const AnnihArgs& a, uint64_t key, int slot, int64_t base, int m, int k) {
+    const int lane = threadIdx.x & 63;
+    const uint32_t lo = (uint32_t)key, hi = (uint32_t)(key >> 32);
+    int rank = 0;
+#pragma unroll 4
+    for (int i = 0; i < m; ++i) rank += lane_word(hi, i) < hi ? 1 : 0;
+    bool take = lane < m && rank < k;
+    if (__popcll(__ballot(take)) != k) {
+        const uint64_t id = lane < m ? a.id[base + slot] : ~0ull;
+        const uint32_t il = (uint32_t)id, ih = (uint32_t)(id >> 32);
+        rank = 0;
+        for (int i = 0; i < m; ++i) {
+            const uint64_t ki = (uint64_t)lane_word(hi, i) << 32 | lane_word(lo, i);
+            const uint64_t di = (uint64_t)lane_word(ih, i) << 32 | lane_word(il, i);
+            rank += (ki < key || (ki == key && di < id)) ? 1 : 0;
+        }
+        take = lane < m && rank < k;
+    }
+    return take;
+}
+
+// What k_field knows of a cell over the limit.
+struct AnnihCell {
+    int g, k, line;
+    int h0, h1;          // its e- and e+
+    int r0, r1;          // ... of which the gather recorded
+    int off;             // first record
+};
+
+// One wavefront removes a cell's k annihilating pairs (every lane calls it with the
+// same cell): the k of each species with the smallest (key, id).  Up to 64 records of
+// a species -- the thresholds leave about k + 8 k^1/2 + 20 of them -- one per lane
+// and ranked; up to 512 in registers (annih_select_regs); beyond, a
+// most-significant-bit-first radix select over the records in memory.  Returns (to
+// every lane) the annihilation current in the deposit's units (2^-28 cell); the
+// caller adds it to J[g] and takes k off the cell's e-/e+ counts.  Latency-bound: two
+// dependent round trips per cell, and the removed particles' scattered lines.  With
+// every candidate recorded and k wave-wide minima per species k_field took 57 us on
+// a 512-cell line, 51 us on 9,973 cells and 92 us on 65,536 (600 per cell); 21, 24
+// and 71 us now.
+__device__ long long annihilate_cell(const AnnihArgs& a, const AnnihCell& c, uint64_t step, int* hist) {
+    const int lane = threadIdx.x & 63;
+    const int k = c.k;
+    int m[2] = {c.r0, c.r1};
+    if (m[0] > c.h0 || m[1] > c.h1) {
         if (lane == 0) set_error(&a.sc->err, -4);
         return 0;
     }
+    if (m[0] < k || m[1] < k) {
+        const int cl = c.g - a.lines[c.line].cell_base;
+        for (int s = 0; s < 2; ++s) {
+            if (m[s] >= k) continue;
+            const int h = s ? c.h1 : c.h0;
+            m[s] = annih_record_all(a, step, 4 * c.line + s, cl, (int64_t)c.off + (s ? c.h0 : 0), h);
+            if (m[s] != h) {
+                if (lane == 0) set_error(&a.sc->err, -4);
+                return 0;
+            }
+        }
+    }
+    const int64_t rec[2] = {(int64_t)c.off, (int64_t)c.off + c.h0};
+    const int64_t base[2] = {a.seg_base[4 * c.line], a.seg_base[4 * c.line + 1]};
     long long dq = 0;
+    if (m[0] <= 64 && m[1] <= 64) {
+        uint64_t key[2];
+        int slot[2];
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            key[s] = lane < m[s] ? a.cand_key[rec[s] + lane] : ~0ull;
+            slot[s] = lane < m[s] ? a.cand_slot[rec[s] + lane] : 0;
+        }
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            if (annih_rank64(a, key[s], slot[s], base[s], m[s], k)) {
+                const long long q = annih_remove(a, base[s] + slot[s]);
+                dq += s == 0 ? q : -q;
+            }
+        }
+        return wave_sum_ll(dq);
+    }
     for (int s = 0; s < 2; ++s) {
-        const int m = s ? h1 : h0;
-        const int64_t rec0 = (int64_t)a.ann_off[g] + (s ? h0 : 0);
-        const int64_t base = a.seg_base[4 * line + s];
-        if (m <= 64 * ANNIH_KPL) {
-            const uint32_t taken = annih_select_regs(a, rec0, base, m, k, hist);
+        const int ms = m[s];
+        const int64_t rec0 = rec[s];
+        if (ms <= 64 * ANNIH_KPL) {
+            const uint32_t taken = annih_select_regs(a, rec0, base[s], ms, k, hist);
 #pragma unroll
             for (int j = 0; j < ANNIH_KPL; ++j) {
                 if ((taken >> j) & 1u) {
-                    const int64_t kidx = base + a.cand_slot[rec0 + lane + 64 * j];
-                    const long long q = (long long)(int)(a.off[kidx] * POS_SCALE);
+                    const long long q = annih_remove(a, base[s] + a.cand_slot[rec0 + lane + 64 * j]);
                     dq += s == 0 ? q : -q;
-                    a.cell[kidx] = DEAD_CELL;
-                    a.off[kidx] = 0.5f;
-                    a.u[kidx] = 0.0f;
                 }
             }
             continue;
@@ -1483,42 +1594,35 @@ __device__ long long annihilate_cell(const AnnihArgs& a, const int32_t* hist_out
         int want = k;                 // rank sought among the keys that match kth so far
         for (int b = 63; b >= 0; --b) {
             const uint64_t above = b == 63 ? 0ull : (~0ull << (b + 1));
-            int c = 0;
-            for (int r = lane; r < m; r += 64) {
+            int n0 = 0;
+            for (int r = lane; r < ms; r += 64) {
                 const uint64_t key = a.cand_key[rec0 + r];
-                c += ((key & above) == kth && ((key >> b) & 1ull) == 0ull) ? 1 : 0;
+                n0 += ((key & above) == kth && ((key >> b) & 1ull) == 0ull) ? 1 : 0;
             }
-            c = wave_sum_i(c);
-            if (want > c) {
-                want -= c;
+            n0 = wave_sum_i(n0);
+            if (want > n0) {
+                want -= n0;
                 kth |= 1ull << b;
             }
         }
         // kth is the k-th smallest key; `want` of the keys equal to it are taken
-        for (int r = lane; r < m; r += 64) {
+        for (int r = lane; r < ms; r += 64) {
             const uint64_t key = a.cand_key[rec0 + r];
             const int slot = a.cand_slot[rec0 + r];
             bool take = key < kth;
             if (key == kth) {
-                const uint64_t id = a.id[base + slot];
+                const uint64_t id = a.id[base[s] + slot];
                 int below = 0;
-                for (int r2 = 0; r2 < m; ++r2)
-                    below += (a.cand_key[rec0 + r2] == kth && a.id[base + a.cand_slot[rec0 + r2]] < id) ? 1 : 0;
+                for (int r2 = 0; r2 < ms; ++r2)
+                    below += (a.cand_key[rec0 + r2] == kth && a.id[base[s] + a.cand_slot[rec0 + r2]] < id) ? 1 : 0;
                 take = below < want;
             }
             if (take) {
-                const int64_t kidx = base + slot;
-                const long long q = (long long)(int)(a.off[kidx] * POS_SCALE);
+                const long long q = annih_remove(a, base[s] + slot);
                 dq += s == 0 ? q : -q;
-                a.cell[kidx] = DEAD_CELL;
-                a.off[kidx] = 0.5f;
-                a.u[kidx] = 0.0f;
             }
         }
     }
-    if (lane == 0)
-        atomicAdd(&a.counters[((size_t)line * CNT_REPL + (blockIdx.x & (CNT_REPL - 1))) * NCOUNT + 11],
-                  (unsigned long long)k);
     return wave_sum_ll(dq);
 }
 
@@ -1550,36 +1654,50 @@ __global__ __launch_bounds__(256) void k_field(FieldArgs f, BookArgs b) {
         }
         return;
     }
-    // Each wavefront takes cpw consecutive cells per iteration: all 64 lanes, or 4
-    // in a step where some cell is over the limit, so that the selections, which a
-    // wavefront runs one after another, spread over many wavefronts (the grid is
-    // sized for 4; with 64 most of its blocks find no cells).
+    // Each wavefront takes cpw consecutive cells per iteration: all 64 lanes, or, in a
+    // step where some cell is over the limit, as few as spread the cells over the
+    // grid's wavefronts, at most 4: a wavefront runs its selections one after another
+    // (with 64 cells a wavefront most of the grid's blocks find no cells).
     __shared__ int sHist[4][256];            // per wavefront: the radix histogram of the selection
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    const int cpw = (f.annihilation && f.an.ann_ctl[2] != 0) ? 4 : 64;
     const int wpb = blockDim.x >> 6;
-    for (int gw = (blockIdx.x * wpb + wid) * cpw; gw < n; gw += nb * wpb * cpw) {
+    const int nw = nb * wpb;
+    const int cpw = (f.annihilation && f.an.ann_ctl[2] != 0) ? max(1, min(4, (n + nw - 1) / nw)) : 64;
+    for (int gw = (blockIdx.x * wpb + wid) * cpw; gw < n; gw += nw * cpw) {
         const int g = gw + lane;
         const bool own = lane < cpw && g < n;
         long long dJ = 0;        // this lane's cell: annihilation current and pairs removed
         int k_own = 0;
         if (f.annihilation) {
-            // this wavefront's cells over the limit, one at a time, before their Ampere
+            // this wavefront's cells over the limit, one at a time, before their Ampere;
+            // what their selections need is read for all of them at once
             const int k = own ? f.an.ann_k[g] : 0;
             unsigned long long m = __ballot(k > 0);
-            while (m != 0ull) {
-                const int lead = __ffsll((long long)m) - 1;
-                m &= m - 1ull;
-                const long long d = annihilate_cell(f.an, hist_out, __shfl(g, lead, 64), __shfl(k, lead, 64),
-                                                    sHist[wid]);
-                if (lane == lead) {
-                    dJ = d;
-                    k_own = k;
+            if (m != 0ull) {
+                const bool over = k > 0;
+                const int line = over ? f.cell_line[g] : 0;
+                const int h0 = over ? hist_out[4 * (size_t)g] : 0;
+                const int h1 = over ? hist_out[4 * (size_t)g + 1] : 0;
+                const int r0 = over ? f.an.ann_fill[2 * (size_t)g] : 0;
+                const int r1 = over ? f.an.ann_fill[2 * (size_t)g + 1] : 0;
+                const int off = over ? f.an.ann_off[g] : 0;
+                while (m != 0ull) {
+                    const int lead = __ffsll((long long)m) - 1;
+                    m &= m - 1ull;
+                    auto of = [&](int v) { return __builtin_amdgcn_readlane(v, lead); };
+                    const AnnihCell c{gw + lead, of(k), of(line), of(h0), of(h1), of(r0), of(r1), of(off)};
+                    const long long d = annihilate_cell(f.an, c, step, sHist[wid]);
+                    if (lane == lead) {
+                        dJ = d;
+                        k_own = k;
+                    }
                 }
-            }
-            if (k_own > 0) {
-                hist_out[4 * (size_t)g] -= k_own;
-                hist_out[4 * (size_t)g + 1] -= k_own;
+                if (k_own > 0) {
+                    hist_out[4 * (size_t)g] -= k_own;
+                    hist_out[4 * (size_t)g + 1] -= k_own;
+                    atomicAdd(&f.an.counters[((size_t)line * CNT_REPL + (blockIdx.x & (CNT_REPL - 1))) * NCOUNT + 11],
+                              (unsigned long long)k_own);
+                }
             }
         }
         if (!own) continue;
@@ -1650,9 +1768,12 @@ __device__ __forceinline__ unsigned long long match_key(int key, bool active, in
     return mine;
 }
 
-// The candidates: every live e- and e+ (appends included) in a cell over the
-// limit records its key and slot.  Exits at once when no cell is over it.  Lanes
-// of a wavefront in the same cell reserve their records with one atomic.
+// The candidates: every live e- and e+ (appends included) of a cell over the limit
+// whose key is at most the cell's threshold records its key and slot.  Exits at once
+// when no cell is over the limit.  Bound by HBM: 4 bytes of cell, and in a cell over
+// the limit 8 of id, per particle (with every candidate recorded it was bound by the
+// records' scattered writes and the lanes' matching: 118 -> 88 us on a 65,536-cell line
+// of 600 per cell, 185 -> 138 us on eight lines of 32,768, 20 -> 14 us on one of 9,973).
 __global__ __launch_bounds__(256) void k_annih_gather(AnnihArgs a) {
     if (a.sc->err != 0) return;
     // a copy of the over-limit flag for k_field, which clears [1] for the next step
@@ -1661,49 +1782,48 @@ __global__ __launch_bounds__(256) void k_annih_gather(AnnihArgs a) {
     if (a.ann_ctl[1] == 0) return;
     const uint64_t step = a.sc->step;
     const int32_t* hist_out = a.hist[(step & 1) ^ 1];
-    const int lane = threadIdx.x & 63;
-    const unsigned long long below = (1ull << lane) - 1ull;
-    // a thread takes GATHER_U particles per pass and issues their cell and per-cell
-    // loads together, so that several loads are in flight per lane
+    // a thread takes GATHER_U particles per pass and issues their loads together, so
+    // that several loads are in flight per lane
     constexpr int U = GATHER_U;
-    const int64_t stride = (int64_t)gridDim.x * 256 * U;     // (a segment may hold nearly 2^31 slots)
+    constexpr int CHUNK = 256 * U;
+    // the chunks of all segments are dealt to the blocks in turn
+    int64_t first = blockIdx.x;                                  // this block's next chunk, from the segment's start
     for (int l = 0; l < a.n_lines; ++l) {
         const int cb = a.lines[l].cell_base;
         for (int s = 0; s < 2; ++s) {
             const int seg = 4 * l + s;
             const int n = min(a.alloc[seg], a.seg_cap[seg]);
             const int64_t base = a.seg_base[seg];
-            for (int64_t i0 = (int64_t)blockIdx.x * 256 * U; i0 < n; i0 += stride) {   // block-uniform trip count
-                int cu[U], ku[U];
+            const int64_t nchunk = (n + (int64_t)CHUNK - 1) / CHUNK;     // (a segment may hold nearly 2^31 slots)
+            for (; first < nchunk; first += gridDim.x) {
+                const int64_t i0 = first * CHUNK + (int)threadIdx.x;
+                int cu[U];
+                uint32_t tu[U];
+                uint64_t du[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) cu[u] = i0 + u * 256 < n ? a.cell[base + i0 + u * 256] : DEAD_CELL;
+#pragma unroll
+                for (int u = 0; u < U; ++u) tu[u] = cu[u] != DEAD_CELL ? a.ann_thr[cb + cu[u]] : 0u;
+#pragma unroll
+                for (int u = 0; u < U; ++u) du[u] = tu[u] != 0u ? a.id[base + i0 + u * 256] : 0ull;
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
-                    const int64_t i = i0 + u * 256 + (int)threadIdx.x;
-                    cu[u] = i < n ? a.cell[base + i] : DEAD_CELL;
-                }
-#pragma unroll
-                for (int u = 0; u < U; ++u) ku[u] = cu[u] != DEAD_CELL ? a.ann_k[cb + cu[u]] : 0;
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int i = (int)(i0 + u * 256 + (int)threadIdx.x);    // < n where used
-                    const int g = cu[u] != DEAD_CELL ? cb + cu[u] : 0;
-                    const bool cand = cu[u] != DEAD_CELL && ku[u] != 0;
-                    if (__ballot(cand) == 0ull) continue;                     // wave-uniform
-                    int leader;
-                    const unsigned long long mm = match_key(g, cand, leader);
-                    int r0 = 0;
-                    if (cand && lane == leader) r0 = atomicAdd(&a.ann_fill[2 * (size_t)g + s], __popcll(mm));
-                    const int r = __shfl(r0, leader, 64) + __popcll(mm & below);
-                    if (!cand) continue;
+                    if (tu[u] == 0u) continue;
+                    const uint64_t key = annih_key(step, du[u], a.key0, a.key1);
+                    if ((uint32_t)(key >> 32) > tu[u]) continue;
+                    const int g = cb + cu[u];
+                    const int r = atomicAdd(&a.ann_fill[2 * (size_t)g + s], 1);
                     const int* h = hist_out + 4 * (size_t)g;
                     if (r >= h[s]) {              // counts and particles disagree: cannot happen
                         set_error(&a.sc->err, -4);
                         continue;
                     }
                     const int64_t rec = (int64_t)a.ann_off[g] + (s ? h[0] : 0) + r;
-                    a.cand_key[rec] = annih_key(step, a.id[base + i], a.key0, a.key1);
-                    a.cand_slot[rec] = i;
+                    a.cand_key[rec] = key;
+                    a.cand_slot[rec] = (int)(i0 + u * 256);
                 }
             }
+            first -= nchunk;
         }
     }
 }

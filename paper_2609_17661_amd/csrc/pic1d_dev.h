@@ -94,6 +94,19 @@ __device__ __forceinline__ uint4 philox4x32_10(uint4 c, uint32_t k0, uint32_t k1
     return c;
 }
 
+// The same function with each product as one 64-bit multiply-add: half the quarter-rate
+// multiplies, in register pairs (for kernels with registers to spare).
+__device__ __forceinline__ uint4 philox4x32_10_wide(uint4 c, uint32_t k0, uint32_t k1) {
+#pragma unroll
+    for (int r = 0; r < 10; ++r) {
+        const uint64_t p0 = (uint64_t)0xD2511F53u * c.x, p1 = (uint64_t)0xCD9E8D57u * c.z;
+        c = make_uint4((uint32_t)(p1 >> 32) ^ c.y ^ k0, (uint32_t)p1, (uint32_t)(p0 >> 32) ^ c.w ^ k1, (uint32_t)p0);
+        k0 += 0x9E3779B9u;
+        k1 += 0xBB67AE85u;
+    }
+    return c;
+}
+
 __device__ __forceinline__ float uniform24(uint32_t w) { return (float)(w >> 8) * 0x1.0p-24f; }
 __device__ __forceinline__ float uniform24_open0(uint32_t w) { return (float)((w >> 8) + 1u) * 0x1.0p-24f; }
 __device__ __forceinline__ uint64_t id_from_words(uint32_t lo, uint32_t hi) {
