@@ -43,6 +43,7 @@ struct Layout {
     int32_t n_layer = 0;
     int32_t photon_region = 0;   // photon records per append region
     int32_t n_chunks = 0;        // chunks of SCAN_CELLS cells over all lines (the sort's scan)
+    int32_t max_chunks = 0;      // ... and of the longest line
     bool mlp = false;            // surrogate-network RICS backend
     bool mlp_fallback = false;   // ... with the table of every line as its fallback
     int32_t table_ns = 0;
@@ -70,6 +71,7 @@ struct pic1d_state {
     int cur = 0;  // which particle buffer set is live
     int64_t* seg_base = nullptr;
     int32_t *seg_cap = nullptr, *n_cur = nullptr, *alloc = nullptr, *tile_prefix = nullptr, *new_count = nullptr;
+    int32_t* sort_prefix = nullptr;
     LineDev* dlines = nullptr;
     double *E = nullptr, *j_last = nullptr, *E_sum = nullptr, *j_sum = nullptr;
     float* E32 = nullptr;
@@ -173,7 +175,9 @@ Layout plan_layout(const pic1d_config* c, std::vector<LineHost>* lines_out) {
         LineHost lh;
         build_line(c, l, cb, (int32_t)(toff / 4), lh);
         cb += c->lines[l].n_cells;
-        L.n_chunks += (c->lines[l].n_cells + SCAN_CELLS - 1) / SCAN_CELLS;
+        const int32_t chunks = (c->lines[l].n_cells + SCAN_CELLS - 1) / SCAN_CELLS;
+        L.n_chunks += chunks;
+        L.max_chunks = std::max(L.max_chunks, chunks);
         L.max_nodes = std::max(L.max_nodes, c->lines[l].n_cells + 1);
         for (int s = 0; s < 4; ++s) L.total_slots += lh.cap[s];
         toff += (int64_t)lh.table.size();
@@ -208,6 +212,7 @@ void carve(Carver& cv, const Layout& L, pic1d_state* st) {
     s->alloc = cv.take<int32_t>(L.nseg);
     s->new_count = cv.take<int32_t>(L.nseg);
     s->tile_prefix = cv.take<int32_t>(L.nseg + 1);
+    s->sort_prefix = cv.take<int32_t>(L.nseg + 1);
     s->dlines = cv.take<LineDev>(L.n_lines);
     s->E = cv.take<double>(L.n_cells);
     s->E32 = cv.take<float>(L.n_cells);
@@ -366,9 +371,11 @@ int launch_push(pic1d_state* st) {
     return PIC1D_OK;
 }
 
-int launch_plan(pic1d_state* st, int advance) {
+int launch_plan(pic1d_state* st, int advance, const int32_t* new_count = nullptr) {
     const int pk = prof_begin(st, 3);
-    hipLaunchKernelGGL(k_plan, dim3(1), dim3(256), 0, st->stream, book_args(st), advance);
+    BookArgs b = book_args(st);
+    b.new_count = new_count;
+    hipLaunchKernelGGL(k_plan, dim3(1), dim3(256), 0, st->stream, b, advance);
     prof_end(st, pk);
     return PIC1D_OK;
 }
@@ -388,23 +395,26 @@ int launch_sort(pic1d_state* st) {
     const int b = st->cur, o = 1 - st->cur;
     s.cell = st->cell[b]; s.off = st->off[b]; s.u = st->u[b]; s.id = st->id[b];
     s.cell2 = st->cell[o]; s.off2 = st->off[o]; s.u2 = st->u[o]; s.id2 = st->id[o];
-    s.seg_base = st->seg_base; s.seg_cap = st->seg_cap; s.n_cur = st->n_cur; s.alloc = st->alloc;
-    s.tile_prefix = st->tile_prefix;
-    s.nseg = st->lay.nseg; s.tile = 64 * st->ppt; s.lines = st->dlines; s.hist[0] = st->hist[0]; s.hist[1] = st->hist[1];
+    s.seg_base = st->seg_base; s.n_cur = st->n_cur; s.sort_prefix = st->sort_prefix;
+    s.nseg = st->lay.nseg; s.lines = st->dlines;
     s.bins = st->bins; s.chunk_sum = st->chunk_sum; s.chunk_line = st->chunk_line; s.line_chunk0 = st->line_chunk0;
     s.n_chunks = st->lay.n_chunks; s.n_bins = st->sort_sub * st->lay.n_cells; s.sub = st->sort_sub;
     s.new_count = st->new_count; s.sc = st->sc;
     const int pk = prof_begin(st, 4);
-    hipLaunchKernelGGL(k_sort_zero, dim3(st->aux_blocks), dim3(256), 0, st->stream, s);
-    hipLaunchKernelGGL(k_sort_count, dim3(4 * st->aux_blocks), dim3(PUSH_TPB), 0, st->stream, s);
-    hipLaunchKernelGGL(k_sort_chunks, dim3(st->lay.n_chunks), dim3(SCAN_CELLS), 0, st->stream, s);
-    hipLaunchKernelGGL(k_sort_lines, dim3(st->lay.n_lines), dim3(256), 0, st->stream, s);
-    hipLaunchKernelGGL(k_sort_cursors, dim3(st->lay.n_chunks), dim3(SCAN_CELLS), 0, st->stream, s);
-    hipLaunchKernelGGL(k_sort_scatter, dim3(4 * st->aux_blocks), dim3(PUSH_TPB), 0, st->stream, s);
-    hipLaunchKernelGGL(k_sort_finish, dim3((st->lay.nseg + 255) / 256), dim3(256), 0, st->stream, s);
+    // two blocks of the scatter's LDS fit a CU, four of the count's threads
+    hipLaunchKernelGGL(k_sort_zero, dim3(st->aux_blocks + 1), dim3(256), 0, st->stream, s);
+    hipLaunchKernelGGL(k_sort_count, dim3(4 * st->n_cu), dim3(SORT_TPB), 0, st->stream, s);
+    if (st->lay.max_chunks <= SCAN_MAX_CHUNKS) {
+        hipLaunchKernelGGL(k_sort_scan, dim3(st->lay.n_lines), dim3(SCAN_CELLS), 0, st->stream, s);
+    } else {
+        hipLaunchKernelGGL(k_sort_chunks, dim3(st->lay.n_chunks), dim3(SCAN_CELLS), 0, st->stream, s);
+        hipLaunchKernelGGL(k_sort_lines, dim3(st->lay.n_lines), dim3(256), 0, st->stream, s);
+        hipLaunchKernelGGL(k_sort_cursors, dim3(st->lay.n_chunks), dim3(SCAN_CELLS), 0, st->stream, s);
+    }
+    hipLaunchKernelGGL(k_sort_scatter, dim3(2 * st->n_cu), dim3(SORT_TPB), 0, st->stream, s);
     prof_end(st, pk);
     st->cur = o;
-    return launch_plan(st, 0);
+    return launch_plan(st, 0, st->new_count);
 }
 
 int check_error(pic1d_state* st) {

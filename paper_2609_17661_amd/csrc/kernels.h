@@ -18,6 +18,12 @@ constexpr int CNT_REPL = 64;                    // replicas of every counter (sp
 constexpr int SORT_SUB_DEFAULT = 8;             // sort key: cell and offset in eighths of a cell ...
 constexpr int SORT_SUB_MAX = 32;                // ... or in up to 32 parts (a power of two)
 constexpr int SCAN_CELLS = 256;                 // cells per chunk of the sort's scan (one block)
+constexpr int SCAN_MAX_CHUNKS = 4;              // chunks of the longest line up to which one block scans a line
+constexpr int SORT_TPB = 512;                   // threads per block of the sort's count and scatter
+constexpr int SORT_U = 8;                       // particles per thread
+constexpr int SORT_TILE = SORT_TPB * SORT_U;    // consecutive slots of a segment per block and pass
+constexpr int SORT_W = 2048;                    // bins of a tile ranked at a time in LDS
+constexpr int SORT_PASSES = 8;                  // windows of SORT_W bins at most; wider tiles go to the global bins
 
 constexpr int GATHER_U = 4;                     // particles per thread and pass of the annihilation gather
 constexpr int GATHER_BLOCKS_PER_CU = 16;        // its blocks per CU
@@ -122,6 +128,7 @@ struct BookArgs {
     int32_t* alloc;
     const int32_t* seg_cap;
     int32_t* tile_prefix;
+    const int32_t* new_count;  // after a sort: its live counts (null otherwise)
     int32_t nseg;
     int32_t tile;              // particles per tile (64 ppt)
     DevScalars* sc;
@@ -194,14 +201,10 @@ struct SortArgs {
     float* u2;
     uint64_t* id2;
     const int64_t* seg_base;
-    const int32_t* seg_cap;
-    int32_t* n_cur;
-    int32_t* alloc;
-    const int32_t* tile_prefix;
+    const int32_t* n_cur;
+    int32_t* sort_prefix;      // [nseg + 1]: first tile of SORT_TILE slots of each segment
     int32_t nseg;
-    int32_t tile;              // particles per tile (64 ppt)
     const LineDev* lines;
-    int32_t* hist[2];          // counts per cell and species; current = hist[step & 1]
     int4* bins;                // [cells * sub]: counts, then cursors, per species
     int4* chunk_sum;           // [n_chunks]: counts per chunk, then its first slot per species
     const int32_t* chunk_line; // [n_chunks]: line of each chunk of SCAN_CELLS cells
@@ -294,8 +297,8 @@ __global__ void k_sort_count(SortArgs s);
 __global__ void k_sort_chunks(SortArgs s);
 __global__ void k_sort_lines(SortArgs s);
 __global__ void k_sort_cursors(SortArgs s);
+__global__ void k_sort_scan(SortArgs s);
 __global__ void k_sort_scatter(SortArgs s);
-__global__ void k_sort_finish(SortArgs s);
 __global__ void k_init_pairs(InitArgs a);
 __global__ void k_hist(HistArgs h);
 __global__ void k_moments_particles(MomArgs m);
