@@ -93,6 +93,7 @@ struct pic1d_state {
     double* mom_out = nullptr;          // [0] Gauss residual maximum; then MOM_GRID_BLOCKS pairs of partials
     unsigned long long* mom_kin = nullptr;   // kinetic energy in fixed-point chunks
     PhotonRec* photons = nullptr;
+    int32_t* queue = nullptr;
     int32_t* n_photons = nullptr;
     float* mlp_params = nullptr;
     bf16x8* mlp_ft = nullptr;
@@ -250,6 +251,7 @@ void carve(Carver& cv, const Layout& L, pic1d_state* st) {
     s->mom_kin = cv.take<unsigned long long>(4);
     s->photons = cv.take<PhotonRec>(c_pairs(L) ? (size_t)PHOTON_REPL * L.photon_region : 1);
     s->n_photons = cv.take<int32_t>(PHOTON_REPL);
+    s->queue = cv.take<int32_t>(1);
     s->mlp_params = cv.take<float>(L.mlp ? MLP_NPARAM : 1);
     s->mlp_ft = cv.take<bf16x8>(L.mlp ? FT_TOTAL * 64 : 1);
     s->mlp_bt = cv.take<bf16x8>(L.mlp ? BT_TOTAL * 64 : 1);
@@ -275,7 +277,8 @@ const void* push_kernel(int backend, int ppt, int ww) {
                                 : ppt == 16 ? (const void*)k_push<RICS_TABLE, 16, 128, 0> : nullptr;
             return (ww == 64 && ppt == 8) ? (const void*)k_push<RICS_TABLE, 8, 64, 0> : nullptr;
         case RICS_MLP:
-            return (ww == 32 && ppt == 8) ? (const void*)k_push<RICS_MLP, 8, 32, 0> : nullptr;
+            // (works on half tiles)
+            return (ww == 32 && ppt == 8) ? (const void*)k_push<RICS_MLP, 4, 32, 0> : nullptr;
         default:
             return nullptr;
     }
@@ -297,6 +300,7 @@ PushArgs push_args(pic1d_state* st) {
     a.pair_step = st->pair_step; a.counters = st->counters; a.sc = st->sc;
     a.key0 = (uint32_t)(st->cfg.seed & 0xFFFFFFFFu); a.key1 = (uint32_t)(st->cfg.seed >> 32);
     a.xcd_walk = st->xcd_walk;
+    a.queue = st->queue;
     a.mlp_ft = st->mlp_ft; a.mlp_bias = st->mlp_bias;
     for (int k = 0; k < 3; ++k) { a.mlp_mean[k] = st->mlp_norm[k]; a.mlp_std[k] = st->mlp_norm[3 + k]; }
     a.mlp_kTn = (float)((st->cfg.kT_keV - 0.3) * (2.0 / 0.7) - 1.0);
@@ -311,6 +315,7 @@ PushArgs push_args(pic1d_state* st) {
 BookArgs book_args(pic1d_state* st) {
     BookArgs b{};
     b.n_photons = st->n_photons;
+    b.queue = st->queue;
     b.n_cur = st->n_cur; b.alloc = st->alloc; b.seg_cap = st->seg_cap; b.tile_prefix = st->tile_prefix;
     b.nseg = st->lay.nseg; b.tile = 64 * st->ppt; b.sc = st->sc;
     return b;
@@ -352,14 +357,14 @@ int launch_push(pic1d_state* st) {
     const int pk = prof_begin(st, 0);
     if (st->backend == RICS_MLP && st->n_table_lines > 0) {
         // the surrogate with table fallback: the lines on their tables through the table
-        // kernel (its own occupancy; the MLP kernel holds one wavefront per SIMD), the
+        // kernel (its own occupancy; the MLP kernel holds two wavefronts per SIMD), the
         // lines on the network through the MLP kernel
         const int n_net = st->lay.n_lines - st->n_table_lines;
         if (st->ppt != 8 || st->ww != 32) return fail(st, PIC1D_EINVAL, "push shape not built");
         const void* kt = n_net > 0 ? (const void*)k_push<RICS_TABLE, 8, 128, 1> : (const void*)k_push<RICS_TABLE, 8, 128, 0>;
         HIP_TRY(st, hipLaunchKernel(kt, dim3(st->push_blocks_table), dim3(PUSH_TPB), args, 0, st->stream));
         if (n_net > 0)
-            HIP_TRY(st, hipLaunchKernel((const void*)k_push<RICS_MLP, 8, 32, 2>, dim3(st->push_blocks), dim3(PUSH_TPB_MLP),
+            HIP_TRY(st, hipLaunchKernel((const void*)k_push<RICS_MLP, 4, 32, 2>, dim3(st->push_blocks), dim3(PUSH_TPB_MLP),
                                         args, 0, st->stream));
     } else {
         const void* kp = push_kernel(st->backend, st->ppt, st->ww);

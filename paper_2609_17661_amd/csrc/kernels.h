@@ -9,8 +9,8 @@ namespace pic1d {
 enum { RICS_OFF = 0, RICS_EXACT = 1, RICS_TABLE = 2, RICS_MLP = 3 };
 
 constexpr int PUSH_TPB = 256;                   // threads per block of the particle kernels
-constexpr int PUSH_TPB_MLP = 256;               // ... with the surrogate network: one block per CU (its
-                                                // weights fill the LDS), one wavefront per SIMD
+constexpr int PUSH_TPB_MLP = 512;               // ... with the surrogate network: one block per CU (its
+                                                // weights fill the LDS), two wavefronts per SIMD
 constexpr int PUSH_PPT_DEFAULT = 8;             // consecutive particles per thread per tile: 4, 8 or 16
                                                 // (a tile, 64 ppt particles, is one wavefront's work item;
                                                 // the other particle kernels take a tile per block)
@@ -78,6 +78,7 @@ struct PushArgs {
     const float* mlp_bias;
     float mlp_mean[3], mlp_std[3];
     float mlp_kTn;             // kT input, normalised to [-1, 1]
+    int32_t* queue;            // work items taken this step (the network's pusher)
     int32_t xcd_walk;          // 1: each XCD walks a contiguous range of tiles (its own L2)
 };
 
@@ -124,6 +125,7 @@ struct AtmArgs {
 
 struct BookArgs {
     int32_t* n_photons;        // reset to 0 for the next step (may be null)
+    int32_t* queue;            // reset to 0
     int32_t* n_cur;
     int32_t* alloc;
     const int32_t* seg_cap;

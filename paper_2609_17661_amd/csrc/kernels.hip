@@ -556,7 +556,7 @@ __device__ __forceinline__ void counts_flush(unsigned long long* counters, int l
 // lane) and the window (cells) are template parameters picked by the autotuner;
 // tiles whose cells span more than the window deposit through global atomics.
 constexpr int push_waves(int backend) {
-    return backend == RICS_MLP ? 1 : backend == RICS_TABLE ? 5 : 6;
+    return backend == RICS_MLP ? 2 : backend == RICS_TABLE ? 5 : 6;
 }
 
 // Sorting network on PPT keys (ascending): the 19-comparator network for 8, five
@@ -609,6 +609,13 @@ __global__ __launch_bounds__(BACKEND == RICS_MLP ? PUSH_TPB_MLP : PUSH_TPB)
 __attribute__((amdgpu_waves_per_eu(push_waves(BACKEND)))) void k_push(PushArgs a) {
     static_assert(PPT == 4 || PPT == 8 || PPT == 16, "4, 8 or 16 particles per lane");
     constexpr int TILE = 64 * PPT;
+    // With the surrogate network a particle costs between one evaluation and six,
+    // depending on where it is: the wavefronts take their work from a queue, and half
+    // a planned tile at a time, as a few of these fill a launch (3.3e6 particles:
+    // 2.40 ms where each XCD walked its own range of whole tiles, the wavefronts of the
+    // cheap ranges idle 45% of the launch; 1.35 ms so).
+    constexpr bool QUEUE = BACKEND == RICS_MLP;
+    constexpr int SUB = QUEUE ? PUSH_PPT_DEFAULT / PPT : 1;
     constexpr int TPB = BACKEND == RICS_MLP ? PUSH_TPB_MLP : PUSH_TPB;
     __shared__ unsigned long long sJ[TPB / 64][WW];
     __shared__ int sH[TPB / 64][WW];
@@ -617,11 +624,9 @@ __attribute__((amdgpu_waves_per_eu(push_waves(BACKEND)))) void k_push(PushArgs a
     __shared__ float sPu[TPB / 64][PPT][64];
     // surrogate weights, staged once per block (the network runs on them for every particle)
     __shared__ bf16x8 sW[BACKEND == RICS_MLP ? FT_TOTAL * 64 : 1];
-    __shared__ float sWb[BACKEND == RICS_MLP ? MLP_BIAS : 1];
     if constexpr (BACKEND == RICS_MLP) {
         // before the error check: every wave of the block reaches the barrier
         for (int e = threadIdx.x; e < FT_TOTAL * 64; e += TPB) sW[e] = a.mlp_ft[e];
-        for (int e = threadIdx.x; e < MLP_BIAS; e += TPB) sWb[e] = a.mlp_bias[e];
         __syncthreads();
     }
     if (a.sc->err != 0) return;
@@ -629,7 +634,7 @@ __attribute__((amdgpu_waves_per_eu(push_waves(BACKEND)))) void k_push(PushArgs a
     if (blockIdx.x == 0 && threadIdx.x == 0) a.sc->step_field = step;
     const int32_t* hist_in = (step & 1) ? a.hist[1] : a.hist[0];
     int32_t* hist_out = (step & 1) ? a.hist[0] : a.hist[1];
-    const int total = a.tile_prefix[a.nseg];
+    const int total = SUB * a.tile_prefix[a.nseg];
     const int lane = threadIdx.x & 63;
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     Counts cnt;
@@ -639,14 +644,24 @@ __attribute__((amdgpu_waves_per_eu(push_waves(BACKEND)))) void k_push(PushArgs a
     // current tile's results are stored and its deposit window flushed, so that the
     // loads are in flight while the stores and atomics drain.
     WaveWalk ww(total, a.xcd_walk);
+    auto pop = [&] {
+        int t = 0;
+        if (lane == 0) t = atomicAdd(a.queue, 1);
+        return __builtin_amdgcn_readfirstlane(t);
+    };
+    if constexpr (QUEUE) {
+        ww.t = pop();
+        ww.end = total;
+    }
     int f_seg = 0, f_ib = 0, f_nv = 0;
     bool f_full = false;
     int64_t f_base = 0;
     int4 fc[PPT / 4];
     float4 fo[PPT / 4], fu[PPT / 4];
     // (every call assigns all fetched values, so that none stays live across the loop)
-    auto fetch = [&](int t) {
-        const bool have = t < ww.end;
+    auto fetch = [&](int item) {
+        const bool have = item < ww.end;
+        const int t = SUB == 1 ? item : item / SUB;
         if (have && (t < seg_t0 || t >= seg_t1)) {
             seg = find_segment(kconst(a.tile_prefix), a.nseg, t);
             seg_t0 = kconst(a.tile_prefix)[seg];
@@ -656,7 +671,7 @@ __attribute__((amdgpu_waves_per_eu(push_waves(BACKEND)))) void k_push(PushArgs a
         f_base = kconst(a.seg_base)[seg];
         // this lane's PPT consecutive particles (vector loads; slots up to the
         // capacity, a multiple of 256, always exist)
-        const int t0 = (t - seg_t0) * TILE;
+        const int t0 = SUB == 1 ? (t - seg_t0) * TILE : (item - SUB * seg_t0) * TILE;
         const int ncur = kconst(a.n_cur)[seg];
         f_full = have && ncur - t0 >= TILE;        // wave-uniform
         f_ib = t0 + lane * PPT;
@@ -673,7 +688,9 @@ __attribute__((amdgpu_waves_per_eu(push_waves(BACKEND)))) void k_push(PushArgs a
         }
     };
     fetch(ww.t);
-    for (; ww.t < ww.end; ww.t += ww.stride) {
+    int next = 0;
+    for (; ww.t < ww.end; ww.t = QUEUE ? next : ww.t + ww.stride) {
+        if constexpr (QUEUE) next = pop();
         const int tseg = f_seg, ib = f_ib, nv = f_nv;
         const int64_t base = f_base;
         const int line = tseg >> 2, sp = tseg & 3;
@@ -687,7 +704,7 @@ __attribute__((amdgpu_waves_per_eu(push_waves(BACKEND)))) void k_push(PushArgs a
         // left to the other launch
         if constexpr (KIND != 0) {
             if ((L.use_table != 0) != (KIND == 1)) {
-                fetch(ww.t + ww.stride);
+                fetch(QUEUE ? next : ww.t + ww.stride);
                 continue;
             }
         }
@@ -841,7 +858,7 @@ __attribute__((amdgpu_waves_per_eu(push_waves(BACKEND)))) void k_push(PushArgs a
             float o1;
             bool gone;
             advance_particle<BACKEND>(a, L, T, cc, alive, line, sp, base + ib + slot, cc.cell, oq, uq, cnt, c1, o1,
-                                      jm, j0, jp, d, gone, sW, sWb);
+                                      jm, j0, jp, d, gone, sW, a.mlp_bias);
             nonfinite = nonfinite || !isfinite(uq);
             cnt.pushed += alive ? 1 : 0;
             cnt.pushed_ion += (alive && sp == 3) ? 1 : 0;
@@ -880,7 +897,7 @@ __attribute__((amdgpu_waves_per_eu(push_waves(BACKEND)))) void k_push(PushArgs a
                 }
             }
         }
-        fetch(ww.t + ww.stride);
+        fetch(QUEUE ? next : ww.t + ww.stride);
         // flush the window
         wave_sync();
         for (int cc2 = lane; cc2 < span; cc2 += 64) {
@@ -908,11 +925,11 @@ template __global__ void k_push<RICS_TABLE, 4, 128, 0>(PushArgs);
 template __global__ void k_push<RICS_TABLE, 8, 128, 0>(PushArgs);
 template __global__ void k_push<RICS_TABLE, 16, 128, 0>(PushArgs);
 template __global__ void k_push<RICS_TABLE, 8, 64, 0>(PushArgs);
-template __global__ void k_push<RICS_MLP, 8, 32, 0>(PushArgs);
+template __global__ void k_push<RICS_MLP, 4, 32, 0>(PushArgs);
 // the surrogate's states with lines on both sources: the table lines alone, the
 // network lines alone
 template __global__ void k_push<RICS_TABLE, 8, 128, 1>(PushArgs);
-template __global__ void k_push<RICS_MLP, 8, 32, 2>(PushArgs);
+template __global__ void k_push<RICS_MLP, 4, 32, 2>(PushArgs);
 
 // ---------------------------------------------------------------------------
 // Photon conversion (Sec. 3): every recorded photon with E >= 2 m_e c^2 turns into
@@ -1228,6 +1245,7 @@ __device__ __forceinline__ int block_excl_scan(int v, int& total) {
 __device__ void bookkeeping(const BookArgs& b) {
     if (b.sc->err != 0) return;
     if (b.n_photons && threadIdx.x < PHOTON_REPL) b.n_photons[threadIdx.x] = 0;
+    if (threadIdx.x == 0) b.queue[0] = 0;
     const int nseg = b.nseg;
     const int per = (nseg + 255) / 256;
     const int s0 = threadIdx.x * per, s1 = min(s0 + per, nseg);

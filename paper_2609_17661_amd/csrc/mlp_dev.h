@@ -56,16 +56,30 @@ struct Split3 {
     bf16x8 hi, mid, lo;
 };
 
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+typedef __attribute__((ext_vector_type(2))) float f32x2;
+
+// Two values at a time: one packed conversion per term, and its halves widened back
+// by a shift and a mask (converting value by value, the compiler makes a conversion
+// and a permute of each).
 __device__ __forceinline__ void split3(const float (&v)[8], Split3& s) {
+    uint32_t* hi = reinterpret_cast<uint32_t*>(&s.hi);
+    uint32_t* mid = reinterpret_cast<uint32_t*>(&s.mid);
+    uint32_t* lo = reinterpret_cast<uint32_t*>(&s.lo);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const __bf16 h = (__bf16)v[i];
-        const float r1 = v[i] - (float)h;
-        const __bf16 m = (__bf16)r1;
-        const float r2 = r1 - (float)m;
-        s.hi[i] = h;
-        s.mid[i] = m;
-        s.lo[i] = (__bf16)r2;
+    for (int i = 0; i < 4; ++i) {
+        auto pack = [](float a, float b) {
+            return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
+        };
+        auto low = [](uint32_t w) { return __builtin_bit_cast(float, w << 16); };
+        auto high = [](uint32_t w) { return __builtin_bit_cast(float, w & 0xffff0000u); };
+        const float a = v[2 * i], b = v[2 * i + 1];
+        const uint32_t h = pack(a, b);
+        const float a1 = a - low(h), b1 = b - high(h);
+        const uint32_t m = pack(a1, b1);
+        hi[i] = h;
+        mid[i] = m;
+        lo[i] = pack(a1 - low(m), b1 - high(m));
     }
 }
 
@@ -101,38 +115,59 @@ __device__ __forceinline__ bf16x8 mlp_input_operand(const float (&x)[4], int g) 
     return b;
 }
 
-// Activations of m-tiles 2K, 2K+1 as the B operand of k-step K.
-__device__ __forceinline__ void operand_from_tiles(const f32x4& t0, const f32x4& t1, Split3& s) {
-    const float v[8] = {t0[0], t0[1], t0[2], t0[3], t1[0], t1[1], t1[2], t1[3]};
-    split3(v, s);
-}
+// SiLU of m-tiles 2K, 2K+1 as the B operand of k-step K.
+struct SiluOperand {
+    __device__ __forceinline__ void operator()(const f32x4& t0, const f32x4& t1, Split3& s) const {
+        float v[8];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            v[j] = silu_f(t0[j]);
+            v[4 + j] = silu_f(t1[j]);
+        }
+        split3(v, s);
+    }
+};
 
-// One 128 -> 128 layer on a 16-sample group: acc[T] = bias + sum_K W(T,K) B(K) over
+// The m-tiles 2K, 2K+1 themselves as the B operand of k-step K.
+struct PlainOperand {
+    __device__ __forceinline__ void operator()(const f32x4& t0, const f32x4& t1, Split3& s) const {
+        const float v[8] = {t0[0], t0[1], t0[2], t0[3], t1[0], t1[1], t1[2], t1[3]};
+        split3(v, s);
+    }
+};
+
+// One 128 -> 128 layer on a 16-sample group: out[T] = bias + sum_K W(T,K) B(K) over
 // the three terms of B.  The loops run K, term, tile, so that consecutive MFMAs
-// write eight different accumulators (independent chains); each tile still sums
-// in the order K0 hi, K0 mid, K0 lo, K1 hi, ...  bias == nullptr starts from zero.
-template <class WPtr>
-__device__ __forceinline__ void hidden_layer(WPtr w, int base, const float* __restrict__ bias, const Split3 (&op)[4],
-                                             f32x4 (&acc)[8]) {
+// write eight different accumulators (independent chains); each tile sums in the
+// order K0 hi, K0 mid, K0 lo, K1 hi, ...  An operand is formed right before its MFMAs, so
+// that only one is live (12 registers instead of 48), and the scheduler is kept from
+// hoisting the next one's: two wavefronts then fit a SIMD without spills.  They
+// overlap one's vector with the other's matrix instructions (which leave the vector
+// unit half of their 16 cycles; mixing the two within a wavefront, one MFMA to four
+// vector instructions, was 6% slower).  bias == nullptr starts from zero.
+template <class WPtr, class Operand>
+__device__ __forceinline__ void hidden_layer(WPtr w, int base, const float* __restrict__ bias, const f32x4 (&in)[8],
+                                             f32x4 (&out)[8], Operand operand) {
     const int lane = threadIdx.x & 63, g = lane >> 4;
-    f32x4 c[8];
 #pragma unroll
     for (int T = 0; T < 8; ++T)
-        c[T] = bias ? *reinterpret_cast<const f32x4*>(bias + 16 * T + 4 * g) : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        out[T] = bias ? *reinterpret_cast<const f32x4*>(bias + 16 * T + 4 * g) : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
     for (int K = 0; K < 4; ++K) {
         bf16x8 wt[8];
 #pragma unroll
         for (int T = 0; T < 8; ++T) wt[T] = w[(base + T * 4 + K) * 64 + lane];
+        __builtin_amdgcn_sched_barrier(0);       // the weights' latency passes under the operand
+        Split3 op;
+        operand(in[2 * K], in[2 * K + 1], op);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int T = 0; T < 8; ++T) c[T] = mfma(wt[T], op[K].hi, c[T]);
+        for (int T = 0; T < 8; ++T) out[T] = mfma(wt[T], op.hi, out[T]);
 #pragma unroll
-        for (int T = 0; T < 8; ++T) c[T] = mfma(wt[T], op[K].mid, c[T]);
+        for (int T = 0; T < 8; ++T) out[T] = mfma(wt[T], op.mid, out[T]);
 #pragma unroll
-        for (int T = 0; T < 8; ++T) c[T] = mfma(wt[T], op[K].lo, c[T]);
+        for (int T = 0; T < 8; ++T) out[T] = mfma(wt[T], op.lo, out[T]);
     }
-#pragma unroll
-    for (int T = 0; T < 8; ++T) acc[T] = c[T];
 }
 
 // Forward pass of one 16-sample group.  `bin` is the input operand of this
@@ -156,36 +191,15 @@ __device__ __forceinline__ f32x4 mlp_group_forward(WPtr wf, const float* __restr
             for (int T = 0; T < 8; ++T)
                 *reinterpret_cast<f32x4*>(zs + h * zlayer + row * MLP_W + 16 * T + 4 * g) = acc[T];
         }
-        Split3 op[4];
+        f32x4 next[8];
+        hidden_layer(wf, FT_H0 + 32 * h, bias + MLP_W * (h + 1), acc, next, SiluOperand());
 #pragma unroll
-        for (int K = 0; K < 4; ++K) {
-            f32x4 a0, a1;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                a0[j] = silu_f(acc[2 * K][j]);
-                a1[j] = silu_f(acc[2 * K + 1][j]);
-            }
-            operand_from_tiles(a0, a1, op[K]);
-        }
-        const float* bl = bias + MLP_W * (h + 1);
-        const int base = FT_H0 + 32 * h;
-        hidden_layer(wf, base, bl, op, acc);
+        for (int T = 0; T < 8; ++T) acc[T] = next[T];
     }
     if (STORE) {
 #pragma unroll
         for (int T = 0; T < 8; ++T)
             *reinterpret_cast<f32x4*>(zs + 3 * zlayer + row * MLP_W + 16 * T + 4 * g) = acc[T];
-    }
-    Split3 op[4];
-#pragma unroll
-    for (int K = 0; K < 4; ++K) {
-        f32x4 a0, a1;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            a0[j] = silu_f(acc[2 * K][j]);
-            a1[j] = silu_f(acc[2 * K + 1][j]);
-        }
-        operand_from_tiles(a0, a1, op[K]);
     }
     // one output tile: three partial sums (one per term) keep three MFMA chains in flight
     f32x4 o_hi, o_mid = {0.0f, 0.0f, 0.0f, 0.0f}, o_lo = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -193,10 +207,12 @@ __device__ __forceinline__ f32x4 mlp_group_forward(WPtr wf, const float* __restr
     for (int j = 0; j < 4; ++j) o_hi[j] = (g == 0 && j < 3) ? bias[4 * MLP_W + j] : 0.0f;
 #pragma unroll
     for (int K = 0; K < 4; ++K) {
+        Split3 op;
+        SiluOperand()(acc[2 * K], acc[2 * K + 1], op);
         const bf16x8 w = wf[(FT_OUT + K) * 64 + lane];
-        o_hi = mfma(w, op[K].hi, o_hi);
-        o_mid = mfma(w, op[K].mid, o_mid);
-        o_lo = mfma(w, op[K].lo, o_lo);
+        o_hi = mfma(w, op.hi, o_hi);
+        o_mid = mfma(w, op.mid, o_mid);
+        o_lo = mfma(w, op.lo, o_lo);
     }
     f32x4 out;
 #pragma unroll
@@ -250,11 +266,10 @@ __device__ __forceinline__ void mlp_group_backward(WPtr wb, const f32x4& dout, c
             *reinterpret_cast<f32x4*>(ds + h * zlayer + row * MLP_W + 16 * T + 4 * g) = acc[T];
         }
         if (h == 0) break;
-        Split3 op[4];
+        f32x4 next[8];
+        hidden_layer(wb, BT_H0 + 32 * (h - 1), nullptr, acc, next, PlainOperand());  // W_{h+1}^T maps dL/dz_h to dL/da_{h-1}
 #pragma unroll
-        for (int K = 0; K < 4; ++K) operand_from_tiles(acc[2 * K], acc[2 * K + 1], op[K]);
-        const int base = BT_H0 + 32 * (h - 1);          // W_{h+1}^T maps dL/dz_h to dL/da_{h-1}
-        hidden_layer(wb, base, nullptr, op, acc);
+        for (int T = 0; T < 8; ++T) acc[T] = next[T];
     }
 }
 
