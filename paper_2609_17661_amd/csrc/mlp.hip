@@ -29,7 +29,7 @@ inline int fail(void*, int code, const std::string& msg) { return set_global_err
 constexpr uint32_t STREAM_MLP_SAMPLE = 7, STREAM_MLP_INIT = 8, STREAM_MLP_BATCH = 9;
 constexpr int MLP_MAX_ATTEMPTS = 64;
 constexpr int MLP_CHUNK = 256;          // samples per weight-gradient block
-constexpr int WGRAD_ZSPLIT = 4;         // blocks sharing one chunk of a 128 x 128 layer's tiles
+constexpr int WGRAD_ROLES = 8;          // blocks per chunk: two per 128 x 128 layer, the input and the output layer
 constexpr int MLP_TPB = 256;
 constexpr int ADAM_BLOCKS = (MLP_NPARAM + MLP_TPB - 1) / MLP_TPB;   // one parameter per thread
 
@@ -334,114 +334,175 @@ __global__ __launch_bounds__(MLP_TPB) void k_mlp_train_bwd(const bf16x8* __restr
     }
 }
 
+// The activation rounded to float32 before it is split (mlp_dev.h's operands take the
+// product into the first subtraction unrounded).
+__device__ __forceinline__ float silu_rounded(float z) {
+#pragma clang fp contract(off)
+    const float s = __builtin_amdgcn_rcpf(1.0f + __expf(-z));
+    return z * s;
+}
+
+// c += A B over the six products of the operands' terms above 2^-24 relative.
+__device__ __forceinline__ f32x4 mfma6(const Split3& A, const Split3& B, f32x4 c) {
+    c = mfma(A.hi, B.hi, c);
+    c = mfma(A.hi, B.mid, c);
+    c = mfma(A.mid, B.hi, c);
+    c = mfma(A.hi, B.lo, c);
+    c = mfma(A.lo, B.hi, c);
+    return mfma(A.mid, B.mid, c);
+}
+
 // Weight and bias gradients of one layer over one chunk of MLP_CHUNK rows:
 // dW[o][i] = sum_s delta[s][o] a[s][i], db[o] = sum_s delta[s][o]; both operands
-// enter as three bfloat16 terms (the six products above 2^-24 relative).
-// grid = (chunks, 5 layers); partial[chunk][param] in the flat packing.
-__global__ __launch_bounds__(MLP_TPB) void k_mlp_wgrad(const float4* __restrict__ XN, const float* __restrict__ Z,
-                                                       const float* __restrict__ DS, const float4* __restrict__ DOUT,
-                                                       int64_t zlayer, float* __restrict__ partial) {
-    constexpr int LD = 36;
-    __shared__ float sD[MLP_W][LD];
-    __shared__ float sA[MLP_W][LD];
-    const int layer = blockIdx.y + 1;
-    const int M = layer == 5 ? 3 : MLP_W;
-    const int N = layer == 1 ? 4 : MLP_W;
-    const int offW = layer == 1 ? MLP_OFF_W1 : layer == 2 ? MLP_OFF_W2 : layer == 3 ? MLP_OFF_W3
-                   : layer == 4 ? MLP_OFF_W4 : MLP_OFF_W5;
-    const int offB = offW + M * N;
-    const int nTo = (M + 15) / 16, nTi = (N + 15) / 16, ntile = nTo * nTi;
-    // the 128 x 128 layers split their 64 tiles over the blocks of gridDim.z (more
-    // blocks than CUs at training batches); the small layers take z = 0 alone
-    const int zsplit = (M == MLP_W && N == MLP_W) ? (int)gridDim.z : 1;
-    if ((int)blockIdx.z >= zsplit) return;
-    const int t_first = (int)blockIdx.z * (ntile / zsplit), t_end = t_first + ntile / zsplit;
-    const int lane = threadIdx.x & 63, g = lane >> 4, r = lane & 15;
-    const int w = threadIdx.x >> 6;
+// enter as three bfloat16 terms.  A lane's operand is eight samples of one neuron: it
+// reads them straight from the row-major arrays (16 lanes share a 64-byte piece of a
+// row), so nothing is transposed.  In the 128 x 128 layers a block of four wavefronts
+// takes half the output neurons, 16 per wavefront; each wavefront forms a quarter of
+// the activations' operands, once per block, and shares them through LDS.
+// grid = (chunks, WGRAD_ROLES);
+// partial[chunk][param] in the flat packing.  Bound by latency and the operands'
+// formation: 15.5 us at 8,192 rows, where staging float32 through LDS and splitting it
+// again for every tile took 84 us.
+__global__ __launch_bounds__(MLP_TPB) __attribute__((amdgpu_waves_per_eu(1, 2))) void k_mlp_wgrad(
+    const float4* __restrict__ XN, const float* __restrict__ Z, const float* __restrict__ DS,
+    const float4* __restrict__ DOUT, int64_t zlayer, float* __restrict__ partial) {
+    constexpr int KSTEPS = MLP_CHUNK / 32;
+    __shared__ bf16x8 sA[2][8][3][64];           // activation operands of a k-step, double-buffered
+    const int lane = threadIdx.x & 63, g = lane >> 4, r = lane & 15, w = threadIdx.x >> 6;
     const int64_t row0 = (int64_t)blockIdx.x * MLP_CHUNK;
-    f32x4 acc[16];
-#pragma unroll
-    for (int k = 0; k < 16; ++k) acc[k] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    float db = 0.0f;
-    for (int ks = 0; ks < MLP_CHUNK / 32; ++ks) {
-        const int64_t s0 = row0 + 32 * ks;
-        // stage delta^T and a^T for 32 rows (zero beyond M / N)
-        for (int e = threadIdx.x; e < 32 * MLP_W; e += blockDim.x) {
-            const int s = e / MLP_W, c = e % MLP_W;
-            const int64_t row = s0 + s;
-            float dv = 0.0f, av = 0.0f;
-            // the deltas of the block's output rows (all rows in block z = 0, which also
-            // sums the bias gradient)
-            const bool dneed = blockIdx.z == 0 || (c >= 32 * (int)blockIdx.z && c < 32 * (int)blockIdx.z + 32);
-            if (c < M && dneed) {
-                if (layer == 5) {
-                    const float4 v = DOUT[row];
-                    dv = c == 0 ? v.x : c == 1 ? v.y : v.z;
-                } else {
-                    dv = DS[(layer - 1) * zlayer + row * MLP_W + c];
-                }
-            }
-            if (c < N) {
-                if (layer == 1) {
-                    const float4 v = XN[row];
-                    av = c == 0 ? v.x : c == 1 ? v.y : c == 2 ? v.z : v.w;
-                } else {
-                    av = silu_f(Z[(layer - 2) * zlayer + row * MLP_W + c]);
-                }
-            }
-            sD[c][s] = dv;
-            sA[c][s] = av;
-        }
-        __syncthreads();
-        if (blockIdx.z == 0 && (int)threadIdx.x < M) {
-            float s = 0.0f;
-            for (int k = 0; k < 32; ++k) s += sD[threadIdx.x][k];
-            db += s;
-        }
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            const int t = t_first + w + 4 * k;
-            if (t < t_end) {
-                const int To = t / nTi, Ti = t % nTi;
-                float dv[8], av[8];
-                const float4 d0 = *reinterpret_cast<const float4*>(&sD[16 * To + r][8 * g]);
-                const float4 d1 = *reinterpret_cast<const float4*>(&sD[16 * To + r][8 * g + 4]);
-                const float4 a0 = *reinterpret_cast<const float4*>(&sA[16 * Ti + r][8 * g]);
-                const float4 a1 = *reinterpret_cast<const float4*>(&sA[16 * Ti + r][8 * g + 4]);
-                dv[0] = d0.x; dv[1] = d0.y; dv[2] = d0.z; dv[3] = d0.w;
-                dv[4] = d1.x; dv[5] = d1.y; dv[6] = d1.z; dv[7] = d1.w;
-                av[0] = a0.x; av[1] = a0.y; av[2] = a0.z; av[3] = a0.w;
-                av[4] = a1.x; av[5] = a1.y; av[6] = a1.z; av[7] = a1.w;
-                Split3 A, B;
-                split3(dv, A);
-                split3(av, B);
-                f32x4 c = acc[k];
-                c = mfma(A.hi, B.hi, c);
-                c = mfma(A.hi, B.mid, c);
-                c = mfma(A.mid, B.hi, c);
-                c = mfma(A.hi, B.lo, c);
-                c = mfma(A.lo, B.hi, c);
-                c = mfma(A.mid, B.mid, c);
-                acc[k] = c;
-            }
-        }
-        __syncthreads();
-    }
     float* out = partial + (int64_t)blockIdx.x * MLP_NPARAM;
+    const int role = blockIdx.y;
+    const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+    // eight samples (rows 8g .. 8g+7 of a k-step) of neuron column c
+    auto column = [&](const float* base, int ks, int c, float (&v)[8]) {
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        const int t = t_first + w + 4 * k;
-        if (t < t_end) {
-            const int To = t / nTi, Ti = t % nTi;
-            const int i = 16 * Ti + r;
+        for (int i = 0; i < 8; ++i) v[i] = base[(row0 + 32 * ks + 8 * g + i) * MLP_W + c];
+    };
+    auto silu8 = [](const float (&z)[8], Split3& s) {
+        float v[8];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int o = 16 * To + 4 * g + j;
-                if (o < M && i < N) out[offW + o * N + i] = acc[k][j];
+        for (int i = 0; i < 8; ++i) v[i] = silu_rounded(z[i]);
+        split3(v, s);
+    };
+    // the sum over a k-step's 32 samples in their order, from the four lanes that hold a
+    // neuron's samples to its lane g = 3
+    auto ordered_sum = [&](const float (&d)[8]) {
+        float s = 0.0f;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if (q > 0) s = __shfl(s, 16 * (q - 1) + r, 64);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) s += d[i];
+        }
+        return s;
+    };
+    if (role < WGRAD_ROLES - 2) {
+        const int layer = 2 + (role >> 1);       // 2, 3, 4
+        const int To = 4 * (role & 1) + w;
+        const float* D = DS + (layer - 1) * zlayer;
+        const float* Zp = Z + (layer - 2) * zlayer;
+        f32x4 acc[8];
+        float db = 0.0f;
+#pragma unroll
+        for (int t = 0; t < 8; ++t) acc[t] = zero;
+        float dv[8], z0[8], z1[8];
+        auto load = [&](int ks) {
+            column(D, ks, 16 * To + r, dv);
+            column(Zp, ks, 32 * w + r, z0);
+            column(Zp, ks, 32 * w + 16 + r, z1);
+        };
+        load(0);
+        for (int ks = 0; ks < KSTEPS; ++ks) {
+            const int buf = ks & 1;
+            Split3 A, B;
+            split3(dv, A);
+            db += ordered_sum(dv);
+            silu8(z0, B);
+            sA[buf][2 * w][0][lane] = B.hi;
+            sA[buf][2 * w][1][lane] = B.mid;
+            sA[buf][2 * w][2][lane] = B.lo;
+            silu8(z1, B);
+            sA[buf][2 * w + 1][0][lane] = B.hi;
+            sA[buf][2 * w + 1][1][lane] = B.mid;
+            sA[buf][2 * w + 1][2][lane] = B.lo;
+            __syncthreads();                     // (the buffer's readers of two k-steps ago passed the last one)
+            if (ks + 1 < KSTEPS) load(ks + 1);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                Split3 Bt[4];
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    Bt[t].hi = sA[buf][4 * h + t][0][lane];
+                    Bt[t].mid = sA[buf][4 * h + t][1][lane];
+                    Bt[t].lo = sA[buf][4 * h + t][2][lane];
+                }
+#pragma unroll
+                for (int t = 0; t < 4; ++t) acc[4 * h + t] = mfma6(A, Bt[t], acc[4 * h + t]);
             }
         }
+        const int offW = layer == 2 ? MLP_OFF_W2 : layer == 3 ? MLP_OFF_W3 : MLP_OFF_W4;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int o = 16 * To + 4 * g + j;
+#pragma unroll
+            for (int t = 0; t < 8; ++t) out[offW + o * MLP_W + 16 * t + r] = acc[t][j];
+        }
+        if (g == 3) out[offW + MLP_W * MLP_W + 16 * To + r] = db;
+    } else if (role == WGRAD_ROLES - 2) {
+        // the input layer
+        f32x4 acc[2] = {zero, zero};
+        float db[2] = {0.0f, 0.0f};
+        for (int ks = 0; ks < KSTEPS; ++ks) {
+            float x[8], d[8];
+            Split3 A, B;
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                x[i] = r < 4 ? reinterpret_cast<const float*>(XN + row0 + 32 * ks + 8 * g + i)[r] : 0.0f;
+            split3(x, B);
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                column(DS, ks, 32 * w + 16 * t + r, d);
+                split3(d, A);
+                db[t] += ordered_sum(d);
+                acc[t] = mfma6(A, B, acc[t]);
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            if (r < 4)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) out[MLP_OFF_W1 + (32 * w + 16 * t + 4 * g + j) * 4 + r] = acc[t][j];
+            if (g == 3) out[MLP_OFF_B1 + 32 * w + 16 * t + r] = db[t];
+        }
+    } else {
+        // the output layer: three rows
+        f32x4 acc[2] = {zero, zero};
+        float db = 0.0f;
+        const float* Zp = Z + 3 * zlayer;
+        for (int ks = 0; ks < KSTEPS; ++ks) {
+            float d[8], z[8];
+            Split3 A, B;
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                d[i] = r < 3 ? reinterpret_cast<const float*>(DOUT + row0 + 32 * ks + 8 * g + i)[r] : 0.0f;
+            split3(d, A);
+            db += ordered_sum(d);
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                column(Zp, ks, 32 * w + 16 * t + r, z);
+                silu8(z, B);
+                acc[t] = mfma6(A, B, acc[t]);
+            }
+        }
+        if (g == 0) {
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+#pragma unroll
+                for (int t = 0; t < 2; ++t) out[MLP_OFF_W5 + j * MLP_W + 32 * w + 16 * t + r] = acc[t][j];
+            }
+        }
+        if (g == 3 && w == 0 && r < 3) out[MLP_OFF_B5 + r] = db;
     }
-    if (blockIdx.z == 0 && (int)threadIdx.x < M) out[offB + threadIdx.x] = db;
 }
 
 // Sum of the chunk partials (fixed order) and, if apply, one Adam step
@@ -581,7 +642,7 @@ int run_grad(const MlpWork& w, TrainFwdArgs fa, hipStream_t s) {
                        s, fa);
     hipLaunchKernelGGL(k_mlp_train_bwd, dim3(std::min<int64_t>(FWD_BLOCKS, (w.rows / 16 + 3) / 4)), dim3(MLP_TPB), 0,
                        s, w.bt, w.DOUT, w.Z, w.DS, (int64_t)(w.rows * MLP_W));
-    hipLaunchKernelGGL(k_mlp_wgrad, dim3(w.nchunk, 5, WGRAD_ZSPLIT), dim3(MLP_TPB), 0, s, w.XN, w.Z, w.DS, w.DOUT,
+    hipLaunchKernelGGL(k_mlp_wgrad, dim3(w.nchunk, WGRAD_ROLES), dim3(MLP_TPB), 0, s, w.XN, w.Z, w.DS, w.DOUT,
                        (int64_t)(w.rows * MLP_W), w.partial);
     MLP_TRY(hipGetLastError());
     return PIC1D_OK;
