@@ -326,7 +326,7 @@ __device__ __forceinline__ MlpRics mlp_rics(const PushArgs& a, const bf16x8* W, 
 #pragma unroll
         for (int k = 0; k < 4; ++k) xg[k] = __shfl(xn[k], 16 * G + r, 64);
         const bf16x8 bin = mlp_input_operand(xg, g4);
-        const f32x4 out = mlp_group_forward<false>(W, Wb, bin, nullptr, 0, 0);
+        const f32x4 out = mlp_group_forward(W, Wb, bin);
         const float v0 = __shfl(out[0], r, 64), v1 = __shfl(out[1], r, 64);
         if (g4 == G) {
             o0 = v0;

@@ -234,7 +234,7 @@ __global__ __launch_bounds__(MLP_TPB) void k_mlp_forward(const bf16x8* __restric
         float xn[4] = {0.0f, 0.0f, 0.0f, 0.0f};
         if (row < n && g < 2) mlp_normalise(X[row], xn);
         const bf16x8 bin = mlp_input_operand(xn, g);
-        const f32x4 o = mlp_group_forward<false>(ft, bias, bin, nullptr, 0, 0);
+        const f32x4 o = mlp_group_forward(ft, bias, bin);
         if (g == 0 && row < n) {
             out[row * 3 + 0] = o[0];
             out[row * 3 + 1] = o[1];
@@ -243,8 +243,9 @@ __global__ __launch_bounds__(MLP_TPB) void k_mlp_forward(const bf16x8* __restric
     }
 }
 
-struct TrainFwdArgs {
+struct TrainArgs {
     const bf16x8* ft;
+    const bf16x8* bt;
     const float* bias;
     const float4* X;          // inputs (raw)
     const float* T;           // explicit normalised targets (n x 3), or null
@@ -255,29 +256,42 @@ struct TrainFwdArgs {
     uint32_t step, k0, k1;
     float4* XN;               // normalised inputs of the batch rows
     float* Z;                 // pre-activations, 4 x rows x 128
+    float* DS;                // dL/dz, 4 x rows x 128
     float4* DOUT;             // dL/d(out), rows x 4
     int64_t zlayer;
     double* loss_part;        // one partial sum of squared errors per block
 };
 
-__global__ __launch_bounds__(MLP_TPB) void k_mlp_train_fwd(TrainFwdArgs a) {
-    __shared__ double sl[MLP_TPB / 64];
-    const int lane = threadIdx.x & 63, g = lane >> 4, r = lane & 15;
-    const int64_t wave = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
-    const int64_t nwave = ((int64_t)gridDim.x * blockDim.x) >> 6;
+// A product rounded to float32, whatever it is subtracted from next.
+__device__ __forceinline__ float mul_rounded(float a, float b) {
+#pragma clang fp contract(off)
+    return a * b;
+}
+
+// Forward and backward over a batch: pre-activations Z, dL/d(out), dL/dz of the hidden
+// layers DS and the loss.  A block of four wavefronts takes a group of 16 samples at a
+// time (GroupOperands); the pre-activations stay in registers for the way back.
+// Latency-bound at training batches, where a group is all a block gets: 17 us at
+// 8,192 samples for both directions, 16 and 19 us with a group per wavefront and a
+// kernel for each direction.
+__global__ __launch_bounds__(MLP_TPB) __attribute__((amdgpu_waves_per_eu(2))) void k_mlp_train(TrainArgs a) {
+    __shared__ GroupOperands sh;
+    const int lane = threadIdx.x & 63, g = lane >> 4, r = lane & 15, w = threadIdx.x >> 6;
     const int64_t rows = a.zlayer / MLP_W;
     double lsum = 0.0;
-    for (int64_t q = wave; q * 16 < rows; q += nwave) {
+    int buf = 0;
+    for (int64_t q = blockIdx.x; q * 16 < rows; q += gridDim.x) {
         const int64_t row = q * 16 + r;
         const bool valid = row < a.n_batch;
+        const int64_t at = row * MLP_W + 32 * w + 4 * g;      // this lane's neurons: at .. at+3 and at+16 .. at+19
         float xn[4] = {0.0f, 0.0f, 0.0f, 0.0f};
         float t[3] = {0.0f, 0.0f, 0.0f};
         if (valid && g < 2) {
             int64_t src = row;
             if (a.n_pool > 0) {
-                const uint4 w = philox4x32_10(make_uint4(a.step, (uint32_t)row, (uint32_t)(row >> 32), STREAM_MLP_BATCH),
+                const uint4 p = philox4x32_10(make_uint4(a.step, (uint32_t)row, (uint32_t)(row >> 32), STREAM_MLP_BATCH),
                                               a.k0, a.k1);
-                const uint64_t h = ((uint64_t)w.x << 32) | w.y;
+                const uint64_t h = ((uint64_t)p.x << 32) | p.y;
                 src = (int64_t)__umul64hi(h, (uint64_t)a.n_pool);
             }
             mlp_normalise(a.X[src], xn);
@@ -293,53 +307,80 @@ __global__ __launch_bounds__(MLP_TPB) void k_mlp_train_fwd(TrainFwdArgs a) {
             }
         }
         const bf16x8 bin = mlp_input_operand(xn, g);
-        const f32x4 o = mlp_group_forward<true>(a.ft, a.bias, bin, a.Z, a.zlayer, row);
+        f32x4 z[4][2];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const int T = 2 * w + k;
+            z[0][k] = *reinterpret_cast<const f32x4*>(a.bias + 16 * T + 4 * g);
+            z[0][k] = mfma(a.ft[(FT_L1 + T) * 64 + lane], bin, z[0][k]);
+        }
+        bf16x8 wt[2][4];
+#pragma unroll
+        for (int h = 0; h < 3; ++h) {
+            load_pair(a.ft, FT_H0 + 32 * h, w, wt);
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                *reinterpret_cast<f32x4*>(a.Z + h * a.zlayer + at + 16 * k) = z[h][k];
+                z[h + 1][k] = *reinterpret_cast<const f32x4*>(a.bias + MLP_W * (h + 1) + 16 * (2 * w + k) + 4 * g);
+            }
+            share_operand(sh, buf, w, z[h], SiluOperand());
+            hidden_pair(sh, buf, wt, z[h + 1]);
+            buf ^= 1;
+        }
+#pragma unroll
+        for (int k = 0; k < 2; ++k) *reinterpret_cast<f32x4*>(a.Z + 3 * a.zlayer + at + 16 * k) = z[3][k];
+        share_operand(sh, buf, w, z[3], SiluOperand());
+        const f32x4 o = output_layer(sh, buf, a.ft, a.bias);
+        buf ^= 1;
+        float d[3] = {0.0f, 0.0f, 0.0f};
         if (g == 0) {
             const float c = 2.0f / (3.0f * (float)a.n_batch);
-            float4 d = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
             if (valid) {
                 const float e0 = o[0] - t[0], e1 = o[1] - t[1], e2 = o[2] - t[2];
-                d = make_float4(c * e0, c * e1, c * e2, 0.0f);
-                lsum += (double)e0 * e0 + (double)e1 * e1 + (double)e2 * e2;
+                d[0] = c * e0;
+                d[1] = c * e1;
+                d[2] = c * e2;
+                if (w == 0) lsum += (double)e0 * e0 + (double)e1 * e1 + (double)e2 * e2;
             }
-            a.DOUT[row] = d;
-            a.XN[row] = make_float4(xn[0], xn[1], xn[2], xn[3]);
+            if (w == 0) {
+                a.DOUT[row] = make_float4(d[0], d[1], d[2], 0.0f);
+                a.XN[row] = make_float4(xn[0], xn[1], xn[2], xn[3]);
+            }
+        }
+        // back: dL/da of the last hidden layer, then through SiLU' and W^T layer by layer
+#pragma unroll
+        for (int j = 0; j < 3; ++j) d[j] = __shfl(d[j], r, 64);
+        const bf16x8 bdo = mlp_output_operand(d, g);
+        f32x4 acc[2];
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+            acc[k] = mfma(a.bt[(BT_OUT + 2 * w + k) * 64 + lane], bdo, f32x4{0.0f, 0.0f, 0.0f, 0.0f});
+#pragma unroll
+        for (int h = 3; h >= 0; --h) {
+            if (h > 0) load_pair(a.bt, BT_H0 + 32 * (h - 1), w, wt);      // W_{h+1}^T maps dL/dz_h to dL/da_{h-1}
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) acc[k][j] = mul_rounded(acc[k][j], silu_grad_f(z[h][k][j]));
+                *reinterpret_cast<f32x4*>(a.DS + h * a.zlayer + at + 16 * k) = acc[k];
+            }
+            if (h == 0) break;
+            share_operand(sh, buf, w, acc, PlainOperand());
+            acc[0] = acc[1] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+            hidden_pair(sh, buf, wt, acc);
+            buf ^= 1;
         }
     }
-    for (int o = 32; o > 0; o >>= 1) lsum += __shfl_xor(lsum, o, 64);
-    if (lane == 0) sl[threadIdx.x >> 6] = lsum;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double s = 0.0;
-        for (int w = 0; w < MLP_TPB / 64; ++w) s += sl[w];
-        a.loss_part[blockIdx.x] = s;
-    }
-}
-
-__global__ __launch_bounds__(MLP_TPB) void k_mlp_train_bwd(const bf16x8* __restrict__ bt, const float4* __restrict__ DOUT,
-                                                           const float* __restrict__ Z, float* __restrict__ DS,
-                                                           int64_t zlayer) {
-    const int lane = threadIdx.x & 63, g = lane >> 4, r = lane & 15;
-    const int64_t wave = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
-    const int64_t nwave = ((int64_t)gridDim.x * blockDim.x) >> 6;
-    const int64_t rows = zlayer / MLP_W;
-    for (int64_t q = wave; q * 16 < rows; q += nwave) {
-        const int64_t row = q * 16 + r;
-        f32x4 d = {0.0f, 0.0f, 0.0f, 0.0f};
-        if (g == 0) {
-            const float4 v = DOUT[row];
-            d = f32x4{v.x, v.y, v.z, 0.0f};
-        }
-        mlp_group_backward(bt, d, Z, DS, zlayer, row);
+    if (w == 0) {
+        for (int o = 32; o > 0; o >>= 1) lsum += __shfl_xor(lsum, o, 64);
+        if (lane == 0) a.loss_part[blockIdx.x] = lsum;
     }
 }
 
 // The activation rounded to float32 before it is split (mlp_dev.h's operands take the
 // product into the first subtraction unrounded).
 __device__ __forceinline__ float silu_rounded(float z) {
-#pragma clang fp contract(off)
-    const float s = __builtin_amdgcn_rcpf(1.0f + __expf(-z));
-    return z * s;
+    return mul_rounded(z, __builtin_amdgcn_rcpf(1.0f + __expf(-z)));
 }
 
 // c += A B over the six products of the operands' terms above 2^-24 relative.
@@ -511,10 +552,60 @@ struct AdamArgs {
     float lr, beta1, omb1, beta2, omb2, eps, bc1, bc2;   // omb = 1 - beta, bc = 1 - beta^t (formed in float64)
 };
 
+// Writes parameter e's bfloat16 value to its places in the MFMA tiles (the inverse of
+// k_mlp_pack's reading; the tiles' zeros stay as k_mlp_pack left them).
+struct PackedNet {
+    __bf16* ft;
+    __bf16* bt;
+    float* bias;
+};
+
+__device__ __forceinline__ void mlp_repack(const PackedNet& n, int e, float v) {
+    const __bf16 b = (__bf16)v;
+    auto put = [](__bf16* tiles, int tile, int g, int r, int i, __bf16 x) { tiles[(tile * 64 + 16 * g + r) * 8 + i] = x; };
+    // position (K, g, i) of an input neuron in mlp_perm's order
+    auto place = [](int neuron, int& K, int& g, int& i) {
+        const int m = neuron & 31;
+        K = neuron >> 5;
+        g = (m & 15) >> 2;
+        i = (m & 3) + (m < 16 ? 0 : 4);
+    };
+    int K, g, i;
+    if (e < MLP_OFF_B1) {
+        const int o = e >> 2, k = e & 3;
+        put(n.ft, FT_L1 + (o >> 4), 0, o & 15, k, b);
+        put(n.ft, FT_L1 + (o >> 4), 0, o & 15, 4 + k, b);
+        put(n.ft, FT_L1 + (o >> 4), 1, o & 15, k, b);
+    } else if (e < MLP_OFF_W2) {
+        n.bias[e - MLP_OFF_B1] = v;
+    } else if (e < MLP_OFF_W5) {
+        constexpr int LAYER = MLP_W * MLP_W + MLP_W;
+        const int h = (e - MLP_OFF_W2) / LAYER, k = (e - MLP_OFF_W2) - h * LAYER;
+        if (k < MLP_W * MLP_W) {
+            const int o = k >> 7, in = k & 127;
+            place(in, K, g, i);
+            put(n.ft, FT_H0 + 32 * h + (o >> 4) * 4 + K, g, o & 15, i, b);
+            place(o, K, g, i);
+            put(n.bt, BT_H0 + 32 * h + (in >> 4) * 4 + K, g, in & 15, i, b);
+        } else {
+            n.bias[MLP_W * (h + 1) + k - MLP_W * MLP_W] = v;
+        }
+    } else if (e < MLP_OFF_B5) {
+        const int o = (e - MLP_OFF_W5) >> 7, in = (e - MLP_OFF_W5) & 127;
+        place(in, K, g, i);
+        put(n.ft, FT_OUT + K, g, o, i, b);
+        for (int pp = o; pp < 9; pp += 3) put(n.bt, BT_OUT + (in >> 4), pp >> 3, in & 15, pp & 7, b);
+    } else {
+        n.bias[4 * MLP_W + e - MLP_OFF_B5] = v;
+    }
+}
+
+// With n.ft set, the updated parameters also replace theirs in the packed tiles: the
+// next training step needs no launch of k_mlp_pack.
 __global__ __launch_bounds__(MLP_TPB) void k_mlp_adam(const float* __restrict__ partial, int nchunk,
                                                       float* __restrict__ p, float* __restrict__ m,
                                                       float* __restrict__ v, float* __restrict__ grad_out, int apply,
-                                                      AdamArgs h) {
+                                                      AdamArgs h, PackedNet n) {
     for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < MLP_NPARAM; e += gridDim.x * blockDim.x) {
         float gsum = 0.0f;
 #pragma unroll 8
@@ -525,7 +616,9 @@ __global__ __launch_bounds__(MLP_TPB) void k_mlp_adam(const float* __restrict__ 
             const float vv = h.beta2 * v[e] + h.omb2 * gsum * gsum;
             m[e] = mm;
             v[e] = vv;
-            p[e] -= h.lr * (mm / h.bc1) / (sqrtf(vv / h.bc2) + h.eps);
+            const float pn = p[e] - h.lr * (mm / h.bc1) / (sqrtf(vv / h.bc2) + h.eps);
+            p[e] = pn;
+            if (n.ft) mlp_repack(n, e, pn);
         }
     }
 }
@@ -580,6 +673,9 @@ struct MlpWork {
 };
 
 constexpr int FWD_BLOCKS = 1024;
+
+// blocks of k_mlp_train: a 16-sample group each, at most two rounds of the chip
+int train_blocks(int64_t rows) { return (int)std::min<int64_t>(FWD_BLOCKS, rows / 16); }
 constexpr int STAT_BLOCKS = 512;
 
 // Carve the training workspace: tiles, parameters and Adam moments, the sample
@@ -637,11 +733,8 @@ void split_seed(uint64_t seed, uint32_t& k0, uint32_t& k1) {
 
 // one forward + backward + weight-gradient pass over the batch rows already
 // addressed by `fa`; leaves the chunk partials in w.partial
-int run_grad(const MlpWork& w, TrainFwdArgs fa, hipStream_t s) {
-    hipLaunchKernelGGL(k_mlp_train_fwd, dim3(std::min<int64_t>(FWD_BLOCKS, (w.rows / 16 + 3) / 4)), dim3(MLP_TPB), 0,
-                       s, fa);
-    hipLaunchKernelGGL(k_mlp_train_bwd, dim3(std::min<int64_t>(FWD_BLOCKS, (w.rows / 16 + 3) / 4)), dim3(MLP_TPB), 0,
-                       s, w.bt, w.DOUT, w.Z, w.DS, (int64_t)(w.rows * MLP_W));
+int run_grad(const MlpWork& w, TrainArgs fa, hipStream_t s) {
+    hipLaunchKernelGGL(k_mlp_train, dim3(train_blocks(w.rows)), dim3(MLP_TPB), 0, s, fa);
     hipLaunchKernelGGL(k_mlp_wgrad, dim3(w.nchunk, WGRAD_ROLES), dim3(MLP_TPB), 0, s, w.XN, w.Z, w.DS, w.DOUT,
                        (int64_t)(w.rows * MLP_W), w.partial);
     MLP_TRY(hipGetLastError());
@@ -664,15 +757,15 @@ double sum_loss(const MlpWork& w, int nblocks, hipStream_t s) {
 int loss_grad_on(const MlpWork& w, const float* params, int64_t n, const float* x, const float* t, float* grad,
                  double* loss, hipStream_t s) {
     hipLaunchKernelGGL(k_mlp_pack, dim3(64), dim3(MLP_TPB), 0, s, params, w.ft, w.bt, w.bias);
-    TrainFwdArgs fa{};
+    TrainArgs fa{};
     fa.ft = w.ft; fa.bias = w.bias; fa.X = reinterpret_cast<const float4*>(x); fa.T = t;
-    fa.n_batch = n; fa.n_pool = 0; fa.XN = w.XN; fa.Z = w.Z; fa.DOUT = w.DOUT;
+    fa.n_batch = n; fa.n_pool = 0; fa.XN = w.XN; fa.Z = w.Z; fa.DS = w.DS; fa.DOUT = w.DOUT; fa.bt = w.bt;
     fa.zlayer = w.rows * MLP_W; fa.loss_part = w.loss_part;
     if (int rc = run_grad(w, fa, s)) return rc;
     hipLaunchKernelGGL(k_mlp_adam, dim3(ADAM_BLOCKS), dim3(MLP_TPB), 0, s, w.partial, w.nchunk, nullptr, nullptr, nullptr, grad,
-                       0, adam_args(0.0, 0.0, 0.0, 1.0, 1));
+                       0, adam_args(0.0, 0.0, 0.0, 1.0, 1), PackedNet{});
     MLP_TRY(hipGetLastError());
-    const double l = sum_loss(w, (int)std::min<int64_t>(FWD_BLOCKS, (w.rows / 16 + 3) / 4), s);
+    const double l = sum_loss(w, train_blocks(w.rows), s);
     if (loss) *loss = l / (3.0 * (double)n);
     return PIC1D_OK;
 }
@@ -800,7 +893,7 @@ int pic1d_mlp_adam(float* params, float* m, float* v, const float* grad, int64_t
         return fail(nullptr, PIC1D_EINVAL, "bad arguments");
     hipStream_t s = static_cast<hipStream_t>(stream);
     hipLaunchKernelGGL(k_mlp_adam, dim3(ADAM_BLOCKS), dim3(MLP_TPB), 0, s, grad, 1, params, m, v, nullptr, 1,
-                       adam_args(lr, beta1, beta2, eps, t));
+                       adam_args(lr, beta1, beta2, eps, t), PackedNet{});
     MLP_TRY(hipGetLastError());
     MLP_TRY(hipStreamSynchronize(s));
     return PIC1D_OK;
@@ -858,30 +951,30 @@ int pic1d_mlp_train(const pic1d_mlp_train_config* c, pic1d_mlp_train_result* res
     MLP_TRY(hipMemsetAsync(w.v, 0, sizeof(float) * MLP_NPARAM, s));
     MLP_TRY(hipMemsetAsync(w.XN, 0, sizeof(float4) * w.rows, s));
 
-    const int fwd_blocks = (int)std::min<int64_t>(FWD_BLOCKS, (w.rows / 16 + 3) / 4);
-    TrainFwdArgs fa{};
+    TrainArgs fa{};
     fa.ft = w.ft; fa.bias = w.bias; fa.X = w.X; fa.T = nullptr; fa.O = w.O; fa.norm = w.norm;
     fa.n_batch = c->batch; fa.n_pool = c->n_samples; fa.k0 = k0; fa.k1 = k1;
-    fa.XN = w.XN; fa.Z = w.Z; fa.DOUT = w.DOUT; fa.zlayer = w.rows * MLP_W; fa.loss_part = w.loss_part;
+    fa.XN = w.XN; fa.Z = w.Z; fa.DS = w.DS; fa.DOUT = w.DOUT; fa.bt = w.bt; fa.zlayer = w.rows * MLP_W; fa.loss_part = w.loss_part;
     const double b1 = c->beta1 > 0.0 ? c->beta1 : 0.9, b2 = c->beta2 > 0.0 ? c->beta2 : 0.999;
     const double eps = c->eps > 0.0 ? c->eps : 1e-8;
     const int nlog = std::max(0, std::min(res->n_loss, c->steps));
     int logged = 0;
     res->loss_first = NAN;
+    hipLaunchKernelGGL(k_mlp_pack, dim3(64), dim3(MLP_TPB), 0, s, w.master, w.ft, w.bt, w.bias);
+    const PackedNet net{reinterpret_cast<__bf16*>(w.ft), reinterpret_cast<__bf16*>(w.bt), w.bias};
     for (int t = 1; t <= c->steps; ++t) {
-        hipLaunchKernelGGL(k_mlp_pack, dim3(64), dim3(MLP_TPB), 0, s, w.master, w.ft, w.bt, w.bias);
         fa.step = (uint32_t)t;
         if (int rc = run_grad(w, fa, s)) return rc;
         const double lr = c->lr_final + 0.5 * (c->lr - c->lr_final) *
                                             (1.0 + std::cos(3.141592653589793 * (double)(t - 1) / (double)c->steps));
         hipLaunchKernelGGL(k_mlp_adam, dim3(ADAM_BLOCKS), dim3(MLP_TPB), 0, s, w.partial, w.nchunk, w.master, w.m, w.v,
-                           nullptr, 1, adam_args(lr, b1, b2, eps, t));
+                           nullptr, 1, adam_args(lr, b1, b2, eps, t), net);
         MLP_TRY(hipGetLastError());
         const bool first = t == 1;
         const bool log_now = nlog > 0 && res->loss && logged < nlog &&
                              (int64_t)(t - 1) * nlog / c->steps >= logged;
         if (first || log_now || t == c->steps) {
-            const double l = sum_loss(w, fwd_blocks, s) / (3.0 * (double)c->batch);
+            const double l = sum_loss(w, train_blocks(w.rows), s) / (3.0 * (double)c->batch);
             if (first) res->loss_first = l;
             if (log_now) res->loss[logged++] = l;
             if (t == c->steps) res->loss_last = l;

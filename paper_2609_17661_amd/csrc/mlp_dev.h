@@ -172,11 +172,8 @@ __device__ __forceinline__ void hidden_layer(WPtr w, int base, const float* __re
 
 // Forward pass of one 16-sample group.  `bin` is the input operand of this
 // lane; returns D of the output layer (lanes g == 0: outputs 0..2 of sample r).
-// With STORE, the pre-activations of the four hidden layers are written to
-// zs + l*zlayer + row*128 (row = first sample of the group + r).
-template <bool STORE, class WPtr>
-__device__ __forceinline__ f32x4 mlp_group_forward(WPtr wf, const float* __restrict__ bias, const bf16x8& bin,
-                                                   float* __restrict__ zs, int64_t zlayer, int64_t row) {
+template <class WPtr>
+__device__ __forceinline__ f32x4 mlp_group_forward(WPtr wf, const float* __restrict__ bias, const bf16x8& bin) {
     const int lane = threadIdx.x & 63, g = lane >> 4;
     f32x4 acc[8];
 #pragma unroll
@@ -186,20 +183,10 @@ __device__ __forceinline__ f32x4 mlp_group_forward(WPtr wf, const float* __restr
     }
 #pragma unroll 1
     for (int h = 0; h < 3; ++h) {
-        if (STORE) {
-#pragma unroll
-            for (int T = 0; T < 8; ++T)
-                *reinterpret_cast<f32x4*>(zs + h * zlayer + row * MLP_W + 16 * T + 4 * g) = acc[T];
-        }
         f32x4 next[8];
         hidden_layer(wf, FT_H0 + 32 * h, bias + MLP_W * (h + 1), acc, next, SiluOperand());
 #pragma unroll
         for (int T = 0; T < 8; ++T) acc[T] = next[T];
-    }
-    if (STORE) {
-#pragma unroll
-        for (int T = 0; T < 8; ++T)
-            *reinterpret_cast<f32x4*>(zs + 3 * zlayer + row * MLP_W + 16 * T + 4 * g) = acc[T];
     }
     // one output tile: three partial sums (one per term) keep three MFMA chains in flight
     f32x4 o_hi, o_mid = {0.0f, 0.0f, 0.0f, 0.0f}, o_lo = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -220,17 +207,9 @@ __device__ __forceinline__ f32x4 mlp_group_forward(WPtr wf, const float* __restr
     return out;
 }
 
-// Backward pass of one 16-sample group: from dL/d(out) (lanes g == 0, sample r,
-// components 0..2) to dL/dz of the four hidden layers, written to
-// ds + l*zlayer + row*128; the stored pre-activations zs are read back.
-template <class WPtr>
-__device__ __forceinline__ void mlp_group_backward(WPtr wb, const f32x4& dout, const float* __restrict__ zs,
-                                                   float* __restrict__ ds, int64_t zlayer, int64_t row) {
-    const int lane = threadIdx.x & 63, g = lane >> 4, r = lane & 15;
-    // small-K operand of W5^T: positions 0..2 hi, 3..5 mid, 6..8 lo
-    float d3[3];
-#pragma unroll
-    for (int j = 0; j < 3; ++j) d3[j] = __shfl(dout[j], r, 64);
+// B operand of W5^T in the backward pass for dL/d(out) d3[0..2] of sample r of the
+// group: positions 0..2 hi, 3..5 mid, 6..8 lo.
+__device__ __forceinline__ bf16x8 mlp_output_operand(const float (&d3)[3], int g) {
     __bf16 hi[3], mi[3], lo[3];
 #pragma unroll
     for (int j = 0; j < 3; ++j) {
@@ -239,38 +218,78 @@ __device__ __forceinline__ void mlp_group_backward(WPtr wb, const f32x4& dout, c
         mi[j] = (__bf16)r1;
         lo[j] = (__bf16)(r1 - (float)mi[j]);
     }
-    bf16x8 bdo;
+    bf16x8 b;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) bdo[i] = (__bf16)0.0f;
+    for (int i = 0; i < 8; ++i) b[i] = (__bf16)0.0f;
     if (g == 0) {
-        bdo[0] = hi[0]; bdo[1] = hi[1]; bdo[2] = hi[2];
-        bdo[3] = mi[0]; bdo[4] = mi[1]; bdo[5] = mi[2];
-        bdo[6] = lo[0]; bdo[7] = lo[1];
+        b[0] = hi[0]; b[1] = hi[1]; b[2] = hi[2];
+        b[3] = mi[0]; b[4] = mi[1]; b[5] = mi[2];
+        b[6] = lo[0]; b[7] = lo[1];
     } else if (g == 1) {
-        bdo[0] = lo[2];
+        b[0] = lo[2];
     }
-    f32x4 acc[8];
+    return b;
+}
+
+// The 16-sample group of a block of four wavefronts: wavefront w holds the m-tiles 2w
+// and 2w+1 of every layer (32 neurons), forms the operand of k-step w from them and
+// shares it through LDS, so that a layer costs a quarter of the time it takes one
+// wavefront.  Each tile sums in the order of hidden_layer.
+struct GroupOperands {
+    bf16x8 t[2][4][3][64];      // double-buffered: [buffer][k-step][term][lane]
+};
+
+template <class Operand>
+__device__ __forceinline__ void share_operand(GroupOperands& sh, int buf, int w, const f32x4 (&in)[2], Operand operand) {
+    const int lane = threadIdx.x & 63;
+    Split3 op;
+    operand(in[0], in[1], op);
+    sh.t[buf][w][0][lane] = op.hi;
+    sh.t[buf][w][1][lane] = op.mid;
+    sh.t[buf][w][2][lane] = op.lo;
+    __syncthreads();        // (the other buffer's readers passed the barrier before)
+}
+
+// The weight tiles of wavefront w's two m-tiles of a 128 -> 128 layer.
+template <class WPtr>
+__device__ __forceinline__ void load_pair(WPtr wt, int base, int w, bf16x8 (&o)[2][4]) {
+    const int lane = threadIdx.x & 63;
 #pragma unroll
-    for (int T = 0; T < 8; ++T) {
-        acc[T] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-        acc[T] = mfma(wb[(BT_OUT + T) * 64 + lane], bdo, acc[T]);
-    }
-#pragma unroll 1
-    for (int h = 3; h >= 0; --h) {
-        // acc holds dL/da of hidden layer h (0-based); times SiLU'(z) gives dL/dz
+    for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int T = 0; T < 8; ++T) {
-            const f32x4 z = *reinterpret_cast<const f32x4*>(zs + h * zlayer + row * MLP_W + 16 * T + 4 * g);
+        for (int K = 0; K < 4; ++K) o[t][K] = wt[(base + (2 * w + t) * 4 + K) * 64 + lane];
+}
+
+// out[t] += W(2w+t, .) B over the shared operands.
+__device__ __forceinline__ void hidden_pair(const GroupOperands& sh, int buf, const bf16x8 (&wt)[2][4], f32x4 (&out)[2]) {
+    const int lane = threadIdx.x & 63;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) acc[T][j] *= silu_grad_f(z[j]);
-            *reinterpret_cast<f32x4*>(ds + h * zlayer + row * MLP_W + 16 * T + 4 * g) = acc[T];
+    for (int K = 0; K < 4; ++K)
+#pragma unroll
+        for (int term = 0; term < 3; ++term) {
+            const bf16x8 b = sh.t[buf][K][term][lane];
+#pragma unroll
+            for (int t = 0; t < 2; ++t) out[t] = mfma(wt[t][K], b, out[t]);
         }
-        if (h == 0) break;
-        f32x4 next[8];
-        hidden_layer(wb, BT_H0 + 32 * (h - 1), nullptr, acc, next, PlainOperand());  // W_{h+1}^T maps dL/dz_h to dL/da_{h-1}
+}
+
+// The output layer over the shared operands (every wavefront the same).
+template <class WPtr>
+__device__ __forceinline__ f32x4 output_layer(const GroupOperands& sh, int buf, WPtr wf, const float* __restrict__ bias) {
+    const int lane = threadIdx.x & 63, g = lane >> 4;
+    f32x4 o[3] = {{0.0f, 0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f, 0.0f}};
 #pragma unroll
-        for (int T = 0; T < 8; ++T) acc[T] = next[T];
+    for (int j = 0; j < 3; ++j) o[0][j] = g == 0 ? bias[4 * MLP_W + j] : 0.0f;
+#pragma unroll
+    for (int K = 0; K < 4; ++K) {
+        const bf16x8 w = wf[(FT_OUT + K) * 64 + lane];
+#pragma unroll
+        for (int term = 0; term < 3; ++term) o[term] = mfma(w, sh.t[buf][K][term][lane], o[term]);
     }
+    f32x4 out;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) out[j] = o[0][j] + (o[1][j] + o[2][j]);
+    return out;
 }
 
 }  // namespace pic1d
