@@ -243,6 +243,80 @@ __global__ __launch_bounds__(MLP_TPB) void k_mlp_forward(const bf16x8* __restric
     }
 }
 
+// Inference on a small batch, a block of four wavefronts per group (GroupOperands), from
+// the parameters themselves: the rounding to bfloat16 and the order of k_mlp_pack's
+// tiles are two 16-byte loads and four packed conversions per tile and lane, so no
+// packing launch comes first.  Latency-bound; at 1,000 samples the call takes 28.6 us
+// (34.7 with the packing and a group per wavefront).  Beyond FWD_SMALL samples the
+// blocks' float32 weights (202 KB each from L2) cost more than the launch.
+__global__ __launch_bounds__(MLP_TPB) __attribute__((amdgpu_waves_per_eu(2))) void k_mlp_forward_small(
+    const float* __restrict__ p, const float4* __restrict__ X, int64_t n, float* __restrict__ out) {
+    __shared__ GroupOperands sh;
+    const int lane = threadIdx.x & 63, g = lane >> 4, r = lane & 15, w = threadIdx.x >> 6;
+    auto rounded = [](const float4& a, const float4& b) {
+        bf16x8 t;
+        t[0] = (__bf16)a.x; t[1] = (__bf16)a.y; t[2] = (__bf16)a.z; t[3] = (__bf16)a.w;
+        t[4] = (__bf16)b.x; t[5] = (__bf16)b.y; t[6] = (__bf16)b.z; t[7] = (__bf16)b.w;
+        return t;
+    };
+    const float4 none = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    // operand of k-step K from a row of 128 weights (mlp_perm's order)
+    auto row_tile = [&](const float* row, int K) {
+        const float4* q = reinterpret_cast<const float4*>(row + 32 * K + 4 * g);
+        return rounded(q[0], q[4]);
+    };
+    constexpr int OFF_W[3] = {MLP_OFF_W2, MLP_OFF_W3, MLP_OFF_W4};
+    int buf = 0;
+    for (int64_t q = blockIdx.x; q * 16 < n; q += gridDim.x) {
+        const int64_t row = q * 16 + r;
+        float xn[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        if (row < n && g < 2) mlp_normalise(X[row], xn);
+        const bf16x8 bin = mlp_input_operand(xn, g);
+        f32x4 z[2];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const int o = 16 * (2 * w + k);
+            const float4 w1 = *reinterpret_cast<const float4*>(p + MLP_OFF_W1 + 4 * (o + r));
+            z[k] = *reinterpret_cast<const f32x4*>(p + MLP_OFF_B1 + o + 4 * g);
+            z[k] = mfma(rounded(g < 2 ? w1 : none, g == 0 ? w1 : none), bin, z[k]);
+        }
+#pragma unroll
+        for (int h = 0; h < 3; ++h) {
+            bf16x8 wt[2][4];
+            f32x4 next[2];
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const int o = 16 * (2 * w + k);
+#pragma unroll
+                for (int K = 0; K < 4; ++K) wt[k][K] = row_tile(p + OFF_W[h] + MLP_W * (o + r), K);
+                next[k] = *reinterpret_cast<const f32x4*>(p + OFF_W[h] + MLP_W * MLP_W + o + 4 * g);
+            }
+            share_operand(sh, buf, w, z, SiluOperand());
+            hidden_pair(sh, buf, wt, next);
+            z[0] = next[0];
+            z[1] = next[1];
+            buf ^= 1;
+        }
+        bf16x8 wo[4];
+#pragma unroll
+        for (int K = 0; K < 4; ++K) {
+            const bf16x8 t = row_tile(p + MLP_OFF_W5 + MLP_W * min(r, 2), K);      // (rows 3 .. 15 are zero)
+            wo[K] = r < 3 ? t : rounded(none, none);
+        }
+        float b5[3];
+#pragma unroll
+        for (int j = 0; j < 3; ++j) b5[j] = p[MLP_OFF_B5 + j];
+        share_operand(sh, buf, w, z, SiluOperand());
+        const f32x4 o = output_layer(sh, buf, wo, b5);
+        buf ^= 1;
+        if (w == 0 && g == 0 && row < n) {
+            out[row * 3 + 0] = o[0];
+            out[row * 3 + 1] = o[1];
+            out[row * 3 + 2] = o[2];
+        }
+    }
+}
+
 struct TrainArgs {
     const bf16x8* ft;
     const bf16x8* bt;
@@ -330,7 +404,11 @@ __global__ __launch_bounds__(MLP_TPB) __attribute__((amdgpu_waves_per_eu(2))) vo
 #pragma unroll
         for (int k = 0; k < 2; ++k) *reinterpret_cast<f32x4*>(a.Z + 3 * a.zlayer + at + 16 * k) = z[3][k];
         share_operand(sh, buf, w, z[3], SiluOperand());
-        const f32x4 o = output_layer(sh, buf, a.ft, a.bias);
+        bf16x8 wo[4];
+#pragma unroll
+        for (int K = 0; K < 4; ++K) wo[K] = a.ft[(FT_OUT + K) * 64 + lane];
+        const float b5[3] = {a.bias[4 * MLP_W], a.bias[4 * MLP_W + 1], a.bias[4 * MLP_W + 2]};
+        const f32x4 o = output_layer(sh, buf, wo, b5);
         buf ^= 1;
         float d[3] = {0.0f, 0.0f, 0.0f};
         if (g == 0) {
@@ -673,6 +751,7 @@ struct MlpWork {
 };
 
 constexpr int FWD_BLOCKS = 1024;
+constexpr int64_t FWD_SMALL = 4096;
 
 // blocks of k_mlp_train: a 16-sample group each, at most two rounds of the chip
 int train_blocks(int64_t rows) { return (int)std::min<int64_t>(FWD_BLOCKS, rows / 16); }
@@ -850,8 +929,12 @@ int pic1d_mlp_forward(const float* params, int64_t n, const float* x, float* out
     if (int rc = check_workspace(workspace, workspace_bytes, need.bytes)) return rc;
     const MlpWork w = mlp_layout(static_cast<char*>(workspace), 1, 0);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    hipLaunchKernelGGL(k_mlp_pack, dim3(64), dim3(MLP_TPB), 0, s, params, w.ft, w.bt, w.bias);
-    if (n > 0) {
+    // (the small kernel reads the parameters 16 bytes at a time)
+    if (n > 0 && n <= FWD_SMALL && (reinterpret_cast<uintptr_t>(params) & 15) == 0) {
+        hipLaunchKernelGGL(k_mlp_forward_small, dim3((unsigned)((n + 15) / 16)), dim3(MLP_TPB), 0, s, params,
+                           reinterpret_cast<const float4*>(x), n, out);
+    } else if (n > 0) {
+        hipLaunchKernelGGL(k_mlp_pack, dim3(64), dim3(MLP_TPB), 0, s, params, w.ft, w.bt, w.bias);
         const int blocks = (int)std::min<int64_t>(FWD_BLOCKS, (n + 63) / 64);
         hipLaunchKernelGGL(k_mlp_forward, dim3(blocks), dim3(MLP_TPB), 0, s, w.ft, w.bias,
                            reinterpret_cast<const float4*>(x), n, out);

@@ -263,29 +263,37 @@ __device__ __forceinline__ void load_pair(WPtr wt, int base, int w, bf16x8 (&o)[
 // out[t] += W(2w+t, .) B over the shared operands.
 __device__ __forceinline__ void hidden_pair(const GroupOperands& sh, int buf, const bf16x8 (&wt)[2][4], f32x4 (&out)[2]) {
     const int lane = threadIdx.x & 63;
+    bf16x8 b[4][3];
 #pragma unroll
     for (int K = 0; K < 4; ++K)
 #pragma unroll
-        for (int term = 0; term < 3; ++term) {
-            const bf16x8 b = sh.t[buf][K][term][lane];
+        for (int term = 0; term < 3; ++term) b[K][term] = sh.t[buf][K][term][lane];
+    __builtin_amdgcn_sched_barrier(0);       // all reads in flight before the first product
 #pragma unroll
-            for (int t = 0; t < 2; ++t) out[t] = mfma(wt[t][K], b, out[t]);
-        }
+    for (int K = 0; K < 4; ++K)
+#pragma unroll
+        for (int term = 0; term < 3; ++term)
+#pragma unroll
+            for (int t = 0; t < 2; ++t) out[t] = mfma(wt[t][K], b[K][term], out[t]);
 }
 
-// The output layer over the shared operands (every wavefront the same).
-template <class WPtr>
-__device__ __forceinline__ f32x4 output_layer(const GroupOperands& sh, int buf, WPtr wf, const float* __restrict__ bias) {
+// The output layer over the shared operands (every wavefront the same): its tiles w and
+// bias b.
+__device__ __forceinline__ f32x4 output_layer(const GroupOperands& sh, int buf, const bf16x8 (&w)[4], const float (&b)[3]) {
     const int lane = threadIdx.x & 63, g = lane >> 4;
     f32x4 o[3] = {{0.0f, 0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f, 0.0f}};
 #pragma unroll
-    for (int j = 0; j < 3; ++j) o[0][j] = g == 0 ? bias[4 * MLP_W + j] : 0.0f;
+    for (int j = 0; j < 3; ++j) o[0][j] = g == 0 ? b[j] : 0.0f;
+    bf16x8 op[4][3];
 #pragma unroll
-    for (int K = 0; K < 4; ++K) {
-        const bf16x8 w = wf[(FT_OUT + K) * 64 + lane];
+    for (int K = 0; K < 4; ++K)
 #pragma unroll
-        for (int term = 0; term < 3; ++term) o[term] = mfma(w, sh.t[buf][K][term][lane], o[term]);
-    }
+        for (int term = 0; term < 3; ++term) op[K][term] = sh.t[buf][K][term][lane];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int K = 0; K < 4; ++K)
+#pragma unroll
+        for (int term = 0; term < 3; ++term) o[term] = mfma(w[K], op[K][term], o[term]);
     f32x4 out;
 #pragma unroll
     for (int j = 0; j < 4; ++j) out[j] = o[0][j] + (o[1][j] + o[2][j]);
