@@ -90,8 +90,9 @@ struct pic1d_state {
     unsigned long long* counters = nullptr;
     DevScalars* sc = nullptr;
     unsigned long long* rho = nullptr;
-    double* mom_out = nullptr;          // [0] Gauss residual maximum; then MOM_GRID_BLOCKS pairs of partials
-    unsigned long long* mom_kin = nullptr;   // kinetic energy in fixed-point chunks
+    // pinned host memory that results come back through: a MomHeader, then per-cell arrays
+    char* pinned = nullptr;
+    size_t pinned_bytes = 0;
     PhotonRec* photons = nullptr;
     int32_t* queue = nullptr;
     int32_t* n_photons = nullptr;
@@ -130,6 +131,7 @@ struct pic1d_state {
     ~pic1d_state() {
         drop_graphs();
         if (cap_stream) (void)hipStreamDestroy(cap_stream);
+        if (pinned) (void)hipHostFree(pinned);
         for (hipEvent_t e : ev_pool) (void)hipEventDestroy(e);
     }
 };
@@ -164,6 +166,8 @@ hipError_t copy_sync(hipStream_t s, void* dst, const void* src, size_t bytes, hi
     } while (0)
 
 bool c_pairs(const Layout& L) { return L.pairs; }
+
+size_t mom_header_bytes() { return (sizeof(MomHeader) + 255) & ~(size_t)255; }
 
 Layout plan_layout(const pic1d_config* c, std::vector<LineHost>* lines_out) {
     Layout L;
@@ -247,8 +251,6 @@ void carve(Carver& cv, const Layout& L, pic1d_state* st) {
     s->counters = cv.take<unsigned long long>((size_t)NCOUNT * CNT_REPL * L.n_lines);
     s->sc = cv.take<DevScalars>(1);
     s->rho = cv.take<unsigned long long>(L.max_nodes);
-    s->mom_out = cv.take<double>(8 + 2 * MOM_GRID_BLOCKS);
-    s->mom_kin = cv.take<unsigned long long>(4);
     s->photons = cv.take<PhotonRec>(c_pairs(L) ? (size_t)PHOTON_REPL * L.photon_region : 1);
     s->n_photons = cv.take<int32_t>(PHOTON_REPL);
     s->queue = cv.take<int32_t>(1);
@@ -423,9 +425,10 @@ int launch_sort(pic1d_state* st) {
 }
 
 int check_error(pic1d_state* st) {
-    DevScalars h{};
-    HIP_TRY(st, hipMemcpyAsync(&h, st->sc, sizeof(h), hipMemcpyDeviceToHost, st->stream));
+    HIP_TRY(st, hipMemcpyAsync(st->pinned, st->sc, sizeof(DevScalars), hipMemcpyDeviceToHost, st->stream));
     HIP_TRY(st, hipStreamSynchronize(st->stream));
+    DevScalars h{};
+    std::memcpy(&h, st->pinned, sizeof(h));
     if (h.err != 0) {
         st->frozen = h.err;
         return fail(st, h.err, h.err == PIC1D_ECAPACITY   ? "particle capacity exceeded (state frozen)"
@@ -498,6 +501,14 @@ int pic1d_init(const pic1d_config* cfg, pic1d_state** out) {
     occ = std::max(1, std::min(occ, 8));
     st->push_blocks = st->n_cu * occ;
     st->aux_blocks = st->n_cu * 4;
+
+    // 7 arrays of the longest line, at most 4 MiB (longer lines come back in parts)
+    st->pinned_bytes = std::min<size_t>((size_t)4 << 20, mom_header_bytes() + 7 * sizeof(double) * (size_t)st->lay.max_nodes);
+    if (hipHostMalloc((void**)&st->pinned, st->pinned_bytes, hipHostMallocDefault) != hipSuccess) {
+        st->pinned = nullptr;
+        delete st;
+        return fail(nullptr, PIC1D_EDEVICE, "no pinned host memory");
+    }
 
     const hipStream_t s = st->stream;
     auto bail = [&](int code, const std::string& m) {
@@ -1056,96 +1067,63 @@ int pic1d_profile_read(pic1d_state* st, pic1d_profile_out* out) {
 int pic1d_moments(pic1d_state* st, int32_t line, int32_t flags, pic1d_moments_out* out) {
     if (!st || !out || line < 0 || line >= st->lay.n_lines) return fail(st, PIC1D_EINVAL, "bad arguments");
     const LineHost& lh = st->lines[line];
-    const int n = lh.dev.n_cells, cb = lh.dev.cell_base;
+    const int n = lh.dev.n_cells;
     const hipStream_t s = st->stream;
-    HIP_TRY(st, hipMemsetAsync(st->rho, 0, sizeof(unsigned long long) * (n + 1), s));
-    HIP_TRY(st, hipMemsetAsync(st->mom_out, 0, 8 * sizeof(double), s));
-    HIP_TRY(st, hipMemsetAsync(st->mom_kin, 0, 4 * sizeof(unsigned long long), s));
+    const double Q = lh.dev.Q, C = lh.dev.C, ppc0 = st->cfg.ppc0;
+    MomHeader* hdr = reinterpret_cast<MomHeader*>(st->pinned);
     MomArgs m{};
     m.cell = st->cell[st->cur]; m.off = st->off[st->cur]; m.u = st->u[st->cur];
-    m.seg_base = st->seg_base; m.n_cur = st->n_cur; m.tile_prefix = st->tile_prefix; m.nseg = st->lay.nseg;
-    m.tile = 64 * st->ppt;
-    m.line = line; m.lines = st->dlines; m.E = st->E; m.rho = st->rho; m.out = st->mom_out;
-    m.kin = st->mom_kin; m.part = st->mom_out + 8;
+    m.seg_base = st->seg_base; m.n_cur = st->n_cur;
+    m.line = line; m.lines = st->dlines; m.E = st->E; m.rho = st->rho;
+    m.hdr = hdr; m.arr = reinterpret_cast<double*>(st->pinned + mom_header_bytes());
+    m.average = (flags & PIC1D_MOM_AVERAGE) != 0;
+    m.sc = st->sc; m.hist[0] = st->hist[0]; m.hist[1] = st->hist[1]; m.pair_last = st->pair_last; m.j_last = st->j_last;
+    m.E_sum = st->E_sum; m.j_sum = st->j_sum; m.pair_sum = st->pair_sum; m.n_sum = st->n_sum;
+    m.avg_count = st->avg_count; m.counters = st->counters;
+    m.ppc0 = ppc0;
+    m.jn = ppc0 * Q * C;              // n0 e c in code units
     const double sign[4] = {-1.0, 1.0, -1.0, 1.0};
     for (int k = 0; k < 4; ++k) m.sign[k] = sign[k];
     m.mass_ratio = st->cfg.mass_ratio;
+    int64_t chunks = 0;
+    for (int k = 0; k < 4; ++k) chunks += (st->seg_cap_h[4 * line + k] + 256 * MOM_U - 1) / (256 * MOM_U);
+    const int part_blocks = (int)std::max<int64_t>(1, std::min<int64_t>(MOM_PART_BLOCKS, chunks));
     const int grid_blocks = std::max(1, std::min(MOM_GRID_BLOCKS, (n + 256) / 256));
-    hipLaunchKernelGGL(k_moments_particles, dim3(st->aux_blocks), dim3(PUSH_TPB), 0, s, m);
-    hipLaunchKernelGGL(k_moments_grid, dim3(grid_blocks), dim3(256), 0, s, m);
-    double mo[8];
-    std::vector<double> part(2 * (size_t)grid_blocks);
-    unsigned long long kin[4];
-    DevScalars sc{};
-    long long avg = 0;
-    std::vector<int32_t> ncur(4);
-    std::vector<unsigned long long> cnt((size_t)NCOUNT * CNT_REPL);
-    HIP_TRY(st, hipMemcpyAsync(mo, st->mom_out, sizeof(mo), hipMemcpyDeviceToHost, s));
-    HIP_TRY(st, hipMemcpyAsync(part.data(), st->mom_out + 8, part.size() * sizeof(double), hipMemcpyDeviceToHost, s));
-    HIP_TRY(st, hipMemcpyAsync(kin, st->mom_kin, sizeof(kin), hipMemcpyDeviceToHost, s));
-    HIP_TRY(st, hipMemcpyAsync(&sc, st->sc, sizeof(sc), hipMemcpyDeviceToHost, s));
-    HIP_TRY(st, hipMemcpyAsync(&avg, st->avg_count, sizeof(avg), hipMemcpyDeviceToHost, s));
-    HIP_TRY(st, hipMemcpyAsync(ncur.data(), st->n_cur + 4 * line, 4 * sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    HIP_TRY(st, hipMemcpyAsync(cnt.data(), st->counters + (size_t)NCOUNT * CNT_REPL * line, cnt.size() * sizeof(unsigned long long), hipMemcpyDeviceToHost, s));
-    const bool average = (flags & PIC1D_MOM_AVERAGE) != 0;
-    std::vector<int32_t> hist(4 * (size_t)n);
-    std::vector<long long> nsum, psum;
-    std::vector<int32_t> plast;
-    std::vector<double> E(n), jv(n);
-    if (average) {
-        nsum.resize(4 * (size_t)n);
-        psum.resize(n);
-        HIP_TRY(st, hipMemcpyAsync(nsum.data(), st->n_sum + 4 * (size_t)cb, nsum.size() * 8, hipMemcpyDeviceToHost, s));
-        HIP_TRY(st, hipMemcpyAsync(psum.data(), st->pair_sum + cb, psum.size() * 8, hipMemcpyDeviceToHost, s));
-        HIP_TRY(st, hipMemcpyAsync(E.data(), st->E_sum + cb, n * 8, hipMemcpyDeviceToHost, s));
-        HIP_TRY(st, hipMemcpyAsync(jv.data(), st->j_sum + cb, n * 8, hipMemcpyDeviceToHost, s));
-    } else {
-        plast.resize(n);
+    hipLaunchKernelGGL(k_moments_particles, dim3(part_blocks), dim3(256), 0, s, m);
+    // per-cell arrays, as many cells at a time as the pinned buffer holds
+    const int room = (int)std::min<size_t>(n, (st->pinned_bytes - mom_header_bytes()) / (7 * sizeof(double)));
+    double* const to[7] = {out->n_cell[0], out->n_cell[1], out->n_cell[2], out->n_cell[3], out->j, out->E, out->pair_rate};
+    for (int c0 = 0; c0 < n; c0 += room) {
+        m.c0 = c0;
+        m.c1 = std::min(n, c0 + room);
+        m.first = c0 == 0;
+        hipLaunchKernelGGL(k_moments_grid, dim3(grid_blocks), dim3(256), 0, s, m);
+        HIP_TRY(st, hipGetLastError());
         HIP_TRY(st, hipStreamSynchronize(s));
-        HIP_TRY(st, hipMemcpyAsync(hist.data(), st->hist[sc.step & 1] + 4 * (size_t)cb, hist.size() * 4, hipMemcpyDeviceToHost, s));
-        HIP_TRY(st, hipMemcpyAsync(plast.data(), st->pair_last + cb, n * 4, hipMemcpyDeviceToHost, s));
-        HIP_TRY(st, hipMemcpyAsync(E.data(), st->E + cb, n * 8, hipMemcpyDeviceToHost, s));
-        HIP_TRY(st, hipMemcpyAsync(jv.data(), st->j_last + cb, n * 8, hipMemcpyDeviceToHost, s));
+        const size_t len = (size_t)(m.c1 - m.c0);
+        for (int k = 0; k < 7; ++k)
+            if (to[k]) std::memcpy(to[k] + c0, m.arr + k * len, len * sizeof(double));
     }
-    HIP_TRY(st, hipStreamSynchronize(s));
-    const double Q = lh.dev.Q, C = lh.dev.C, ppc0 = st->cfg.ppc0;
-    const double jn = ppc0 * Q * C;   // n0 e c in code units
-    const double na = average ? (double)std::max(avg, 1ll) : 1.0;
-    for (int sp = 0; sp < 4; ++sp)
-        if (out->n_cell[sp])
-            for (int c = 0; c < n; ++c)
-                out->n_cell[sp][c] = (average ? (double)nsum[4 * (size_t)c + sp] : (double)hist[4 * (size_t)c + sp]) / (na * ppc0);
-    if (out->j) for (int c = 0; c < n; ++c) out->j[c] = jv[c] / (na * jn);
-    if (out->E) for (int c = 0; c < n; ++c) out->E[c] = E[c] / na;
-    if (out->pair_rate)
-        for (int c = 0; c < n; ++c) out->pair_rate[c] = average ? (double)psum[c] / na : (double)plast[c];
     // partial sums in block order (the same bits on every call)
-    double esum = 0.0, e2 = 0.0;
+    double esum = 0.0, e2 = 0.0, rmax = 0.0;
+    for (int k = 0; k < 4; ++k) out->count[k] = 0;
     for (int b = 0; b < grid_blocks; ++b) {
-        esum += part[2 * (size_t)b];
-        e2 += part[2 * (size_t)b + 1];
+        esum += hdr->part[b][0];
+        e2 += hdr->part[b][1];
+        rmax = std::max(rmax, hdr->rmax[b]);
+        for (int k = 0; k < 4; ++k) out->count[k] += hdr->count[b][k];     // (absorbed particles excluded)
     }
     // kinetic energy: the three 32-bit chunk sums of sum m (gamma - 1) / m_e * 2^48
-    const unsigned __int128 ksum = (unsigned __int128)kin[0] + ((unsigned __int128)kin[1] << 32) +
-                                   ((unsigned __int128)kin[2] << 64);
-    out->gauss_residual = mo[0] / (4.0 * M_PI * Q * ppc0);
+    unsigned __int128 ksum = 0;
+    for (int b = 0; b < part_blocks; ++b)
+        for (int k = 0; k < 3; ++k) ksum += (unsigned __int128)hdr->kin[b][k] << (32 * k);
+    out->gauss_residual = rmax / (4.0 * M_PI * Q * ppc0);
     out->v_circuit = -esum / (C * C);
     out->energy_kinetic = (double)ksum * 0x1.0p-48 * Q * C * C;
     out->energy_field = e2 / (8.0 * M_PI);
-    for (int k = 0; k < 4; ++k) out->count[k] = 0;
-    out->step = (int64_t)sc.step;
-    out->avg_steps = avg;
-    for (int k = 0; k < NCOUNT; ++k) {
-        out->counters[k] = 0;
-        for (int r = 0; r < CNT_REPL; ++r) out->counters[k] += (int64_t)cnt[(size_t)r * NCOUNT + k];
-    }
-    // live counts: the histogram of the current particles (absorbed ones excluded)
-    {
-        std::vector<int32_t> hc(4 * (size_t)n);
-        HIP_TRY(st, copy_sync(st->stream, hc.data(), st->hist[sc.step & 1] + 4 * (size_t)cb, hc.size() * 4, hipMemcpyDeviceToHost));
-        for (int c = 0; c < n; ++c)
-            for (int k = 0; k < 4; ++k) out->count[k] += hc[4 * (size_t)c + k];
-    }
+    out->step = hdr->step;
+    out->avg_steps = hdr->avg;
+    for (int k = 0; k < NCOUNT; ++k) out->counters[k] = hdr->counters[k];
     if (flags & PIC1D_MOM_RESET) {
         HIP_TRY(st, hipMemsetAsync(st->n_sum, 0, 4 * 8 * (size_t)st->lay.n_cells, s));
         HIP_TRY(st, hipMemsetAsync(st->pair_sum, 0, 8 * (size_t)st->lay.n_cells, s));
@@ -1154,7 +1132,6 @@ int pic1d_moments(pic1d_state* st, int32_t line, int32_t flags, pic1d_moments_ou
         HIP_TRY(st, hipMemsetAsync(st->avg_count, 0, 8, s));
         HIP_TRY(st, hipStreamSynchronize(s));
     }
-    (void)ncur;
     return PIC1D_OK;
 }
 
@@ -1228,8 +1205,12 @@ int pic1d_set_particles(pic1d_state* st, int32_t line, int32_t species, int64_t 
 int pic1d_get_field(pic1d_state* st, int32_t line, double* E) {
     if (!st || !E || line < 0 || line >= st->lay.n_lines) return fail(st, PIC1D_EINVAL, "bad arguments");
     const LineDev& d = st->lines[line].dev;
-    HIP_TRY(st, hipStreamSynchronize(st->stream));
-    HIP_TRY(st, copy_sync(st->stream, E, st->E + d.cell_base, 8 * (size_t)d.n_cells, hipMemcpyDeviceToHost));
+    const int room = (int)std::min<size_t>(d.n_cells, st->pinned_bytes / sizeof(double));
+    for (int c0 = 0; c0 < d.n_cells; c0 += room) {
+        const size_t bytes = sizeof(double) * (size_t)std::min(room, d.n_cells - c0);
+        HIP_TRY(st, copy_sync(st->stream, st->pinned, st->E + d.cell_base + c0, bytes, hipMemcpyDeviceToHost));
+        std::memcpy(E + c0, st->pinned, bytes);
+    }
     return PIC1D_OK;
 }
 

@@ -242,27 +242,52 @@ struct HistArgs {
     int32_t* hist;
 };
 
+constexpr int MOM_GRID_BLOCKS = 256;          // blocks of k_moments_grid at most
+constexpr int MOM_PART_BLOCKS = 1024;         // blocks of k_moments_particles at most
+constexpr int MOM_U = 8;                      // particles per thread and pass of k_moments_particles
+constexpr int MOM_W = 1024;                   // nodes of a block's LDS charge window
+
+// What the moments kernels write into the state's pinned host buffer besides the
+// per-cell arrays: per-block partials, which the host adds in block order.
+struct MomHeader {
+    int64_t step, avg;
+    int64_t counters[NCOUNT];
+    double rmax[MOM_GRID_BLOCKS];             // largest Gauss residual
+    double part[MOM_GRID_BLOCKS][2];          // sum E, sum E^2
+    int64_t count[MOM_GRID_BLOCKS][NSPEC];    // live particles
+    uint64_t kin[MOM_PART_BLOCKS][3];         // sum of m (gamma - 1) / m_e at 2^-48, in 32-bit chunks (exact, any order)
+};
+
 struct MomArgs {
     const int32_t* cell;
     const float* off;
     const float* u;
     const int64_t* seg_base;
     const int32_t* n_cur;
-    const int32_t* tile_prefix;
-    int32_t nseg;
-    int32_t tile;              // particles per tile (64 ppt)
     int32_t line;
     const LineDev* lines;
     const double* E;
-    unsigned long long* rho;   // fixed point, nodes of the line
-    double* out;               // [0] maximum Gauss residual (bits, atomic max)
-    unsigned long long* kin;   // [3]: sum of m (gamma - 1) / m_e at 2^-48, in 32-bit chunks (exact, any order)
-    double* part;              // [MOM_GRID_BLOCKS][2]: per block sum E, sum E^2 (summed in block order on the host)
+    unsigned long long* rho;   // fixed point, nodes of the line; zero between calls
+    MomHeader* hdr;            // pinned host memory
+    double* arr;               // pinned host memory: [7][c1 - c0] densities, j, E, pair rate of the chunk's cells
+    int32_t c0, c1;            // cells of this launch's arrays
+    int32_t first;             // 1: the line's scalars too
+    int32_t average;
+    // per-cell sources over all lines, and their normalisation
+    const DevScalars* sc;
+    const int32_t* hist[2];
+    const int32_t* pair_last;
+    const double* j_last;
+    const double* E_sum;
+    const double* j_sum;
+    const long long* pair_sum;
+    const long long* n_sum;
+    const long long* avg_count;
+    const unsigned long long* counters;
+    double ppc0, jn;           // n0, n0 e c
     double sign[4];
     double mass_ratio;
 };
-
-constexpr int MOM_GRID_BLOCKS = 256;          // blocks of k_moments_grid at most
 
 // Finite-disk RICS table of one line (disk.hip): Gauss-Legendre product rule of
 // n_c x n_phi nodes over the stellar disk, float64, written as float32 records.
