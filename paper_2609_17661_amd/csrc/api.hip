@@ -111,10 +111,13 @@ struct pic1d_state {
     int push_bpc = 0;                              // push blocks per CU
     int ppt = PUSH_PPT_DEFAULT;                    // particles per lane per tile of the push
     int ww = 0;                                    // deposit window of the push (cells)
+    bool shape_set = false;                        // through pic1d_set_push_shape
+    int tiles = 0;                                 // tiles of the planned push when last read back
     int sort_sub = SORT_SUB_DEFAULT;               // sort bins per cell
     int n_table_lines = 0;                         // MLP with table fallback: lines on their table
     int push_blocks_table = 0;                     // ... and the table kernel's blocks for them
     int graph_steps = 0;                           // requested steps per graph; 0 = eager
+    int graph_parts = 0;                           // push_parts of the captured graphs
     int graph_len = 0;                             // steps per graph (a multiple of sort_interval)
     hipGraphExec_t gexec[2] = {nullptr, nullptr};  // by the live buffer set at the graph's start
     hipStream_t cap_stream = nullptr;
@@ -267,22 +270,31 @@ void carve(Carver& cv, const Layout& L, pic1d_state* st) {
 const void* push_kernel(int backend, int ppt, int ww) {
     switch (backend) {
         case RICS_OFF:
-            if (ww == 32) return ppt == 4 ? (const void*)k_push<RICS_OFF, 4, 32, 0> : ppt == 8 ? (const void*)k_push<RICS_OFF, 8, 32, 0>
-                               : ppt == 16 ? (const void*)k_push<RICS_OFF, 16, 32, 0> : nullptr;
-            return (ww == 64 && ppt == 8) ? (const void*)k_push<RICS_OFF, 8, 64, 0> : nullptr;
+            if (ww == 32) return ppt == 4 ? (const void*)k_push<RICS_OFF, 4, 32, 0, 1> : ppt == 8 ? (const void*)k_push<RICS_OFF, 8, 32, 0, 1>
+                               : ppt == 16 ? (const void*)k_push<RICS_OFF, 16, 32, 0, 1> : nullptr;
+            return (ww == 64 && ppt == 8) ? (const void*)k_push<RICS_OFF, 8, 64, 0, 1> : nullptr;
         case RICS_EXACT:
-            if (ww == 32) return ppt == 4 ? (const void*)k_push<RICS_EXACT, 4, 32, 0> : ppt == 8 ? (const void*)k_push<RICS_EXACT, 8, 32, 0>
-                               : ppt == 16 ? (const void*)k_push<RICS_EXACT, 16, 32, 0> : nullptr;
-            return (ww == 64 && ppt == 8) ? (const void*)k_push<RICS_EXACT, 8, 64, 0> : nullptr;
+            if (ww == 32) return ppt == 4 ? (const void*)k_push<RICS_EXACT, 4, 32, 0, 1> : ppt == 8 ? (const void*)k_push<RICS_EXACT, 8, 32, 0, 1>
+                               : ppt == 16 ? (const void*)k_push<RICS_EXACT, 16, 32, 0, 1> : nullptr;
+            return (ww == 64 && ppt == 8) ? (const void*)k_push<RICS_EXACT, 8, 64, 0, 1> : nullptr;
         case RICS_TABLE:
-            if (ww == 128) return ppt == 4 ? (const void*)k_push<RICS_TABLE, 4, 128, 0> : ppt == 8 ? (const void*)k_push<RICS_TABLE, 8, 128, 0>
-                                : ppt == 16 ? (const void*)k_push<RICS_TABLE, 16, 128, 0> : nullptr;
-            return (ww == 64 && ppt == 8) ? (const void*)k_push<RICS_TABLE, 8, 64, 0> : nullptr;
+            if (ww == 128) return ppt == 4 ? (const void*)k_push<RICS_TABLE, 4, 128, 0, 1> : ppt == 8 ? (const void*)k_push<RICS_TABLE, 8, 128, 0, 1>
+                                : ppt == 16 ? (const void*)k_push<RICS_TABLE, 16, 128, 0, 1> : nullptr;
+            return (ww == 64 && ppt == 8) ? (const void*)k_push<RICS_TABLE, 8, 64, 0, 1> : nullptr;
         case RICS_MLP:
             // (works on half tiles)
-            return (ww == 32 && ppt == 8) ? (const void*)k_push<RICS_MLP, 4, 32, 0> : nullptr;
+            return (ww == 32 && ppt == 8) ? (const void*)k_push<RICS_MLP, 4, 32, 0, 2> : nullptr;
         default:
             return nullptr;
+    }
+}
+
+// The default tile's kernel working on parts of tiles.
+const void* push_part_kernel(int backend, int parts) {
+    switch (backend) {
+        case RICS_OFF: return parts == 4 ? (const void*)k_push<RICS_OFF, 2, 32, 0, 4> : (const void*)k_push<RICS_OFF, 4, 32, 0, 2>;
+        case RICS_EXACT: return parts == 4 ? (const void*)k_push<RICS_EXACT, 2, 32, 0, 4> : (const void*)k_push<RICS_EXACT, 4, 32, 0, 2>;
+        default: return parts == 4 ? (const void*)k_push<RICS_TABLE, 2, 128, 0, 4> : (const void*)k_push<RICS_TABLE, 4, 128, 0, 2>;
     }
 }
 
@@ -353,6 +365,20 @@ void prof_collect(pic1d_state* st) {
     st->ev_kernel.clear();
 }
 
+// Parts of the default tile that the wavefronts take separately (0: whole tiles).  Few
+// tiles leave the chip idle while each wavefront works through its eight particles per
+// lane, so the parts follow the last read-back number of tiles against the wavefronts
+// the chip holds (20 per CU): four up to half of them, two up to twice as many.
+// TABLE, us a launch with whole, half and quarter tiles: 35 / 23 / 18 at 124 tiles,
+// 42 / 31 / 30 at 1,863, 50 / 42 / 43 at 3,829, 70 / 64 / 70 at 7,846, 114 / 114 / 128 at
+// 16,023.  A shape set through pic1d_set_push_shape stays as it was set.
+int push_parts(const pic1d_state* st) {
+    if (st->shape_set || st->backend == RICS_MLP || st->ppt != PUSH_PPT_DEFAULT || st->ww != default_window(st->backend))
+        return 0;
+    const int waves = 20 * st->n_cu;
+    return 2 * st->tiles <= waves ? 4 : st->tiles <= 2 * waves ? 2 : 0;
+}
+
 int launch_push(pic1d_state* st) {
     PushArgs a = push_args(st);
     void* args[] = {&a};
@@ -363,14 +389,15 @@ int launch_push(pic1d_state* st) {
         // lines on the network through the MLP kernel
         const int n_net = st->lay.n_lines - st->n_table_lines;
         if (st->ppt != 8 || st->ww != 32) return fail(st, PIC1D_EINVAL, "push shape not built");
-        const void* kt = n_net > 0 ? (const void*)k_push<RICS_TABLE, 8, 128, 1> : (const void*)k_push<RICS_TABLE, 8, 128, 0>;
+        const void* kt = n_net > 0 ? (const void*)k_push<RICS_TABLE, 8, 128, 1, 1> : (const void*)k_push<RICS_TABLE, 8, 128, 0, 1>;
         HIP_TRY(st, hipLaunchKernel(kt, dim3(st->push_blocks_table), dim3(PUSH_TPB), args, 0, st->stream));
         if (n_net > 0)
-            HIP_TRY(st, hipLaunchKernel((const void*)k_push<RICS_MLP, 4, 32, 2>, dim3(st->push_blocks), dim3(PUSH_TPB_MLP),
+            HIP_TRY(st, hipLaunchKernel((const void*)k_push<RICS_MLP, 4, 32, 2, 2>, dim3(st->push_blocks), dim3(PUSH_TPB_MLP),
                                         args, 0, st->stream));
     } else {
         const void* kp = push_kernel(st->backend, st->ppt, st->ww);
         if (!kp) return fail(st, PIC1D_EINVAL, "push shape not built");
+        if (const int parts = push_parts(st)) kp = push_part_kernel(st->backend, parts);
         HIP_TRY(st, hipLaunchKernel(kp, dim3(st->push_blocks), dim3(st->backend == RICS_MLP ? PUSH_TPB_MLP : PUSH_TPB),
                                     args, 0, st->stream));
     }
@@ -424,11 +451,18 @@ int launch_sort(pic1d_state* st) {
     return launch_plan(st, 0, st->new_count);
 }
 
-int check_error(pic1d_state* st) {
-    HIP_TRY(st, hipMemcpyAsync(st->pinned, st->sc, sizeof(DevScalars), hipMemcpyDeviceToHost, st->stream));
+// The device scalars, and with them the number of planned tiles; waits for the stream.
+int read_scalars(pic1d_state* st, DevScalars& h) {
+    HIP_TRY(st, hipMemcpyAsync(st->pinned, st->sc, sizeof(h), hipMemcpyDeviceToHost, st->stream));
     HIP_TRY(st, hipStreamSynchronize(st->stream));
-    DevScalars h{};
     std::memcpy(&h, st->pinned, sizeof(h));
+    st->tiles = h.tiles;
+    return PIC1D_OK;
+}
+
+int check_error(pic1d_state* st) {
+    DevScalars h{};
+    if (int rc = read_scalars(st, h)) return rc;
     if (h.err != 0) {
         st->frozen = h.err;
         return fail(st, h.err, h.err == PIC1D_ECAPACITY   ? "particle capacity exceeded (state frozen)"
@@ -658,7 +692,7 @@ int pic1d_init(const pic1d_config* cfg, pic1d_state** out) {
     if (launch_hist(st) != PIC1D_OK) return bail(PIC1D_EDEVICE, st->err);
     // the initial plasma in position order (its offsets are random within each cell)
     if (cfg->sort_interval > 0 && launch_sort(st) != PIC1D_OK) return bail(PIC1D_EDEVICE, st->err);
-    INIT_TRY(hipStreamSynchronize(s));
+    if (check_error(st) != PIC1D_OK) return bail(PIC1D_EDEVICE, st->err);       // (waits for the stream)
     INIT_TRY(hipGetLastError());
 #undef INIT_TRY
     *out = st;
@@ -815,6 +849,9 @@ int pic1d_step(pic1d_state* st, int32_t n_steps) {
     int32_t i = 0;
     const int G = st->graph_len;
     if (G > 0 && !st->prof_on) {
+        // captured graphs hold the particle kernel of their time
+        if (st->graph_parts != push_parts(st)) st->drop_graphs();
+        st->graph_parts = push_parts(st);
         // eager up to the next multiple of G, then whole graphs
         while (i < n_steps && st->host_step % (uint64_t)G != 0) {
             if (int rc = enqueue_step(st)) return rc;
@@ -867,6 +904,7 @@ int pic1d_set_push_shape(pic1d_state* st, int32_t blocks_per_cu, int32_t ppt, in
     if (!st || blocks_per_cu < 1 || blocks_per_cu > 32) return fail(st, PIC1D_EINVAL, "bad arguments");
     if (st->frozen) return fail(st, PIC1D_ESTATE, "state frozen by an earlier error");
     if (!push_kernel(st->backend, ppt, window)) return fail(st, PIC1D_EINVAL, "push shape not built");
+    st->shape_set = true;
     return set_push_shape(st, blocks_per_cu, ppt, window);
 }
 
@@ -1198,8 +1236,8 @@ int pic1d_set_particles(pic1d_state* st, int32_t line, int32_t species, int64_t 
     launch_plan(st, 0);
     int rc = launch_hist(st);
     if (rc) return rc;
-    HIP_TRY(st, hipStreamSynchronize(st->stream));
-    return PIC1D_OK;
+    DevScalars h{};
+    return read_scalars(st, h);
 }
 
 int pic1d_get_field(pic1d_state* st, int32_t line, double* E) {

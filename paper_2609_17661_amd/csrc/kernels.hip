@@ -568,7 +568,9 @@ __device__ __forceinline__ void sort_keys(uint32_t* k) {
         k[i] = min(x, y);
         k[j] = max(x, y);
     };
-    if constexpr (PPT == 4) {
+    if constexpr (PPT == 2) {
+        cx(0, 1);
+    } else if constexpr (PPT == 4) {
         cx(0, 1); cx(2, 3); cx(0, 2); cx(1, 3); cx(1, 2);
     } else if constexpr (PPT == 8) {
         constexpr int NET[19][2] = {{0, 2}, {1, 3}, {4, 6}, {5, 7}, {0, 4}, {1, 5}, {2, 6}, {3, 7}, {0, 1}, {2, 3},
@@ -604,18 +606,23 @@ __device__ __forceinline__ void wave_sync() {
 // merges its lanes in a private LDS window and flushes the window to the global
 // fixed-point current with one atomic per touched cell.  No block-level
 // synchronisation.
-template <int BACKEND, int PPT, int WW, int KIND>
+template <int BACKEND, int PPT, int WW, int KIND, int SUB>
 __global__ __launch_bounds__(BACKEND == RICS_MLP ? PUSH_TPB_MLP : PUSH_TPB)
 __attribute__((amdgpu_waves_per_eu(push_waves(BACKEND)))) void k_push(PushArgs a) {
-    static_assert(PPT == 4 || PPT == 8 || PPT == 16, "4, 8 or 16 particles per lane");
+    static_assert(PPT == 2 || PPT == 4 || PPT == 8 || PPT == 16, "2, 4, 8 or 16 particles per lane");
+    // A wavefront's item: TILE particles, one of the SUB parts of a planned tile.
     constexpr int TILE = 64 * PPT;
     // With the surrogate network a particle costs between one evaluation and six,
-    // depending on where it is: the wavefronts take their work from a queue, and half
-    // a planned tile at a time, as a few of these fill a launch (3.3e6 particles:
-    // 2.40 ms where each XCD walked its own range of whole tiles, the wavefronts of the
-    // cheap ranges idle 45% of the launch; 1.35 ms so).
+    // depending on where it is: the wavefronts take their items from a queue, and half
+    // a planned tile at a time, as a few of these fill a launch (4.9e6 particles on 16,384
+    // cells: 2.40 ms where each XCD walked its own range of whole tiles, the wavefronts
+    // of the cheap ranges idle 45% of the launch; 1.65 ms so, with two wavefronts per
+    // SIMD; three spill, 1.87 ms).  Bound by vector issue: 1,500 instructions and 308
+    // MFMAs per 16 evaluations.
     constexpr bool QUEUE = BACKEND == RICS_MLP;
-    constexpr int SUB = QUEUE ? PUSH_PPT_DEFAULT / PPT : 1;
+    using VecI = std::conditional_t<PPT == 2, int2, int4>;
+    using VecF = std::conditional_t<PPT == 2, float2, float4>;
+    constexpr int VN = PPT == 2 ? 2 : 4;          // particles per vector load
     constexpr int TPB = BACKEND == RICS_MLP ? PUSH_TPB_MLP : PUSH_TPB;
     __shared__ unsigned long long sJ[TPB / 64][WW];
     __shared__ int sH[TPB / 64][WW];
@@ -656,8 +663,8 @@ __attribute__((amdgpu_waves_per_eu(push_waves(BACKEND)))) void k_push(PushArgs a
     int f_seg = 0, f_ib = 0, f_nv = 0;
     bool f_full = false;
     int64_t f_base = 0;
-    int4 fc[PPT / 4];
-    float4 fo[PPT / 4], fu[PPT / 4];
+    VecI fc[PPT / VN];
+    VecF fo[PPT / VN], fu[PPT / VN];
     // (every call assigns all fetched values, so that none stays live across the loop)
     auto fetch = [&](int item) {
         const bool have = item < ww.end;
@@ -676,14 +683,20 @@ __attribute__((amdgpu_waves_per_eu(push_waves(BACKEND)))) void k_push(PushArgs a
         f_full = have && ncur - t0 >= TILE;        // wave-uniform
         f_ib = t0 + lane * PPT;
         f_nv = have ? max(0, min(PPT, ncur - f_ib)) : 0;
-        const int4* cp = reinterpret_cast<const int4*>(a.cell + f_base + f_ib);
-        const float4* op = reinterpret_cast<const float4*>(a.off + f_base + f_ib);
-        const float4* up = reinterpret_cast<const float4*>(a.u + f_base + f_ib);
+        const VecI* cp = reinterpret_cast<const VecI*>(a.cell + f_base + f_ib);
+        const VecF* op = reinterpret_cast<const VecF*>(a.off + f_base + f_ib);
+        const VecF* up = reinterpret_cast<const VecF*>(a.u + f_base + f_ib);
 #pragma unroll
-        for (int h = 0; h < PPT / 4; ++h) {
-            fc[h] = make_int4(DEAD_CELL, DEAD_CELL, DEAD_CELL, DEAD_CELL);
-            fo[h] = make_float4(0.5f, 0.5f, 0.5f, 0.5f);
-            fu[h] = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int h = 0; h < PPT / VN; ++h) {
+            if constexpr (PPT == 2) {
+                fc[h] = make_int2(DEAD_CELL, DEAD_CELL);
+                fo[h] = make_float2(0.5f, 0.5f);
+                fu[h] = make_float2(0.f, 0.f);
+            } else {
+                fc[h] = make_int4(DEAD_CELL, DEAD_CELL, DEAD_CELL, DEAD_CELL);
+                fo[h] = make_float4(0.5f, 0.5f, 0.5f, 0.5f);
+                fu[h] = make_float4(0.f, 0.f, 0.f, 0.f);
+            }
             if (f_nv > 0) { fc[h] = cp[h]; fo[h] = op[h]; fu[h] = up[h]; }
         }
     };
@@ -718,14 +731,20 @@ __attribute__((amdgpu_waves_per_eu(push_waves(BACKEND)))) void k_push(PushArgs a
         int cst[PPT];
         auto stage = [&](auto full) {
 #pragma unroll
-            for (int h = 0; h < PPT / 4; ++h) {
-                const int4 ci = fc[h];
-                const float4 oi = fo[h], ui = fu[h];
-                const int cv[4] = {ci.x, ci.y, ci.z, ci.w};
-                const float ov[4] = {oi.x, oi.y, oi.z, oi.w}, uv[4] = {ui.x, ui.y, ui.z, ui.w};
+            for (int h = 0; h < PPT / VN; ++h) {
+                int cv[VN];
+                float ov[VN], uv[VN];
+                cv[0] = fc[h].x; cv[1] = fc[h].y;
+                ov[0] = fo[h].x; ov[1] = fo[h].y;
+                uv[0] = fu[h].x; uv[1] = fu[h].y;
+                if constexpr (PPT != 2) {
+                    cv[2] = fc[h].z; cv[3] = fc[h].w;
+                    ov[2] = fo[h].z; ov[3] = fo[h].w;
+                    uv[2] = fu[h].z; uv[3] = fu[h].w;
+                }
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int q = 4 * h + i;
+                for (int i = 0; i < VN; ++i) {
+                    const int q = VN * h + i;
                     const bool valid = decltype(full)::value || q < nv;
                     const int c = valid ? cv[i] : DEAD_CELL;
                     cst[q] = c;
@@ -752,7 +771,7 @@ __attribute__((amdgpu_waves_per_eu(push_waves(BACKEND)))) void k_push(PushArgs a
         // (cell - first) * 2^VB + slot; the slot order is packed in VB-bit fields.
         // Slots already in that order (as unsigned, DEAD_CELL is the largest) keep
         // it; the network runs when any lane of the wavefront needs it.
-        constexpr int VB = PPT == 4 ? 2 : PPT == 8 ? 3 : 4;
+        constexpr int VB = PPT == 2 ? 1 : PPT == 4 ? 2 : PPT == 8 ? 3 : 4;
         using Visit = std::conditional_t<PPT == 16, uint64_t, uint32_t>;
         constexpr Visit IN_ORDER = [] {
             Visit v = 0;
@@ -874,7 +893,11 @@ __attribute__((amdgpu_waves_per_eu(push_waves(BACKEND)))) void k_push(PushArgs a
         if (nonfinite) set_error(&a.sc->err, -5);
         // write back (vector stores for full groups; never touch slots >= ncur, where
         // appended particles may be landing)
-        if (nv == PPT) {
+        if (PPT == 2 && nv == PPT) {
+            *reinterpret_cast<int2*>(a.cell + base + ib) = make_int2(sPc[wid][0][lane], sPc[wid][1][lane]);
+            *reinterpret_cast<float2*>(a.off + base + ib) = make_float2(sPo[wid][0][lane], sPo[wid][1][lane]);
+            *reinterpret_cast<float2*>(a.u + base + ib) = make_float2(sPu[wid][0][lane], sPu[wid][1][lane]);
+        } else if (nv == PPT) {
             int4* cp = reinterpret_cast<int4*>(a.cell + base + ib);
             float4* op = reinterpret_cast<float4*>(a.off + base + ib);
             float4* up = reinterpret_cast<float4*>(a.u + base + ib);
@@ -913,23 +936,30 @@ __attribute__((amdgpu_waves_per_eu(push_waves(BACKEND)))) void k_push(PushArgs a
 
 // the shapes the autotuner chooses from: 4, 8 or 16 particles per lane, and two
 // deposit windows per backend
-template __global__ void k_push<RICS_OFF, 4, 32, 0>(PushArgs);
-template __global__ void k_push<RICS_OFF, 8, 32, 0>(PushArgs);
-template __global__ void k_push<RICS_OFF, 16, 32, 0>(PushArgs);
-template __global__ void k_push<RICS_OFF, 8, 64, 0>(PushArgs);
-template __global__ void k_push<RICS_EXACT, 4, 32, 0>(PushArgs);
-template __global__ void k_push<RICS_EXACT, 8, 32, 0>(PushArgs);
-template __global__ void k_push<RICS_EXACT, 16, 32, 0>(PushArgs);
-template __global__ void k_push<RICS_EXACT, 8, 64, 0>(PushArgs);
-template __global__ void k_push<RICS_TABLE, 4, 128, 0>(PushArgs);
-template __global__ void k_push<RICS_TABLE, 8, 128, 0>(PushArgs);
-template __global__ void k_push<RICS_TABLE, 16, 128, 0>(PushArgs);
-template __global__ void k_push<RICS_TABLE, 8, 64, 0>(PushArgs);
-template __global__ void k_push<RICS_MLP, 4, 32, 0>(PushArgs);
+template __global__ void k_push<RICS_OFF, 4, 32, 0, 1>(PushArgs);
+template __global__ void k_push<RICS_OFF, 8, 32, 0, 1>(PushArgs);
+template __global__ void k_push<RICS_OFF, 16, 32, 0, 1>(PushArgs);
+template __global__ void k_push<RICS_OFF, 8, 64, 0, 1>(PushArgs);
+template __global__ void k_push<RICS_EXACT, 4, 32, 0, 1>(PushArgs);
+template __global__ void k_push<RICS_EXACT, 8, 32, 0, 1>(PushArgs);
+template __global__ void k_push<RICS_EXACT, 16, 32, 0, 1>(PushArgs);
+template __global__ void k_push<RICS_EXACT, 8, 64, 0, 1>(PushArgs);
+template __global__ void k_push<RICS_TABLE, 4, 128, 0, 1>(PushArgs);
+template __global__ void k_push<RICS_TABLE, 8, 128, 0, 1>(PushArgs);
+template __global__ void k_push<RICS_TABLE, 16, 128, 0, 1>(PushArgs);
+template __global__ void k_push<RICS_TABLE, 8, 64, 0, 1>(PushArgs);
+template __global__ void k_push<RICS_MLP, 4, 32, 0, 2>(PushArgs);
+// parts of the default tile, for states whose tiles are too few to fill the chip
+template __global__ void k_push<RICS_OFF, 4, 32, 0, 2>(PushArgs);
+template __global__ void k_push<RICS_OFF, 2, 32, 0, 4>(PushArgs);
+template __global__ void k_push<RICS_EXACT, 4, 32, 0, 2>(PushArgs);
+template __global__ void k_push<RICS_EXACT, 2, 32, 0, 4>(PushArgs);
+template __global__ void k_push<RICS_TABLE, 4, 128, 0, 2>(PushArgs);
+template __global__ void k_push<RICS_TABLE, 2, 128, 0, 4>(PushArgs);
 // the surrogate's states with lines on both sources: the table lines alone, the
 // network lines alone
-template __global__ void k_push<RICS_TABLE, 8, 128, 1>(PushArgs);
-template __global__ void k_push<RICS_MLP, 4, 32, 2>(PushArgs);
+template __global__ void k_push<RICS_TABLE, 8, 128, 1, 1>(PushArgs);
+template __global__ void k_push<RICS_MLP, 4, 32, 2, 2>(PushArgs);
 
 // ---------------------------------------------------------------------------
 // Photon conversion (Sec. 3): every recorded photon with E >= 2 m_e c^2 turns into
@@ -1264,7 +1294,10 @@ __device__ void bookkeeping(const BookArgs& b) {
         // (one segment per thread up to 256 segments: its count is still in a register)
         run += ((per == 1 ? n_last : b.n_cur[s]) + b.tile - 1) / b.tile;
     }
-    if (threadIdx.x == 255) b.tile_prefix[nseg] = total;
+    if (threadIdx.x == 255) {
+        b.tile_prefix[nseg] = total;
+        b.sc->tiles = total;
+    }
 }
 
 // Bookkeeping kernel of every step (and after init, sort, set_particles): one block.

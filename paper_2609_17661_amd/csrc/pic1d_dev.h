@@ -71,7 +71,7 @@ struct LineDev {
 struct DevScalars {
     uint64_t step;        // steps taken; keys Philox
     int32_t err;          // first error code (pic1d_status), 0 if none
-    int32_t pad;
+    int32_t tiles;        // tiles of the planned push (read back with the error word)
     uint64_t step_field;  // the running step, as k_field reads it (k_field advances `step`)
 };
 
