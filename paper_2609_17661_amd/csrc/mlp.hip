@@ -31,6 +31,7 @@ constexpr int MLP_MAX_ATTEMPTS = 64;
 constexpr int MLP_CHUNK = 256;          // samples per weight-gradient block
 constexpr int WGRAD_ROLES = 8;          // blocks per chunk: two per 128 x 128 layer, the input and the output layer
 constexpr int MLP_TPB = 256;
+constexpr int FWD_LDS_TPB = 768;
 constexpr int ADAM_BLOCKS = (MLP_NPARAM + MLP_TPB - 1) / MLP_TPB;   // one parameter per thread
 
 // float64 constants of the RICS prefactors (CODATA 2018; R* = 1e6 cm)
@@ -222,10 +223,11 @@ __device__ __forceinline__ void mlp_normalise(const float4& x, float (&xn)[4]) {
     for (int k = 0; k < 4; ++k) xn[k] = (v[k] - mlp_in_lo(k)) * (2.0f / (mlp_in_hi(k) - mlp_in_lo(k))) - 1.0f;
 }
 
-// Inference: raw inputs X (n x 4) -> network outputs out (n x 3, normalised targets).
-__global__ __launch_bounds__(MLP_TPB) void k_mlp_forward(const bf16x8* __restrict__ ft, const float* __restrict__ bias,
-                                                         const float4* __restrict__ X, int64_t n,
-                                                         float* __restrict__ out) {
+// Inference: raw inputs X (n x 4) -> network outputs out (n x 3, normalised targets), a
+// 16-sample group per wavefront at a time.
+template <class WPtr>
+__device__ __forceinline__ void forward_groups(WPtr ft, const float* bias, const float4* __restrict__ X, int64_t n,
+                                               float* __restrict__ out) {
     const int lane = threadIdx.x & 63, g = lane >> 4, r = lane & 15;
     const int64_t wave = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
     const int64_t nwave = ((int64_t)gridDim.x * blockDim.x) >> 6;
@@ -241,6 +243,29 @@ __global__ __launch_bounds__(MLP_TPB) void k_mlp_forward(const bf16x8* __restric
             out[row * 3 + 2] = o[2];
         }
     }
+}
+
+__global__ __launch_bounds__(MLP_TPB) void k_mlp_forward(const bf16x8* __restrict__ ft, const float* __restrict__ bias,
+                                                         const float4* __restrict__ X, int64_t n,
+                                                         float* __restrict__ out) {
+    forward_groups(ft, bias, X, n, out);
+}
+
+// ... with the weights in LDS, one block per CU and three wavefronts per SIMD: each
+// group otherwise reads 108 KB of them through the L2, about half of what that can
+// deliver.  Bound by vector issue (1,500 instructions and 308 MFMAs a group): 317 us a
+// call at 1e6 samples, 345 without; from 262,144 samples on the groups make up for the
+// staging (110 us either way there).  32-sample groups on 32x32x16 MFMAs give the same
+// bits and half the weight reads, but two wavefronts per SIMD at best: 352 us.
+__global__ __launch_bounds__(FWD_LDS_TPB) __attribute__((amdgpu_waves_per_eu(FWD_LDS_TPB / 256))) void k_mlp_forward_lds(
+    const bf16x8* __restrict__ ft, const float* __restrict__ bias, const float4* __restrict__ X, int64_t n,
+    float* __restrict__ out) {
+    __shared__ bf16x8 sW[FT_TOTAL * 64];
+    __shared__ __align__(16) float sB[MLP_BIAS];
+    for (int e = threadIdx.x; e < FT_TOTAL * 64; e += FWD_LDS_TPB) sW[e] = ft[e];
+    for (int e = threadIdx.x; e < MLP_BIAS; e += FWD_LDS_TPB) sB[e] = bias[e];
+    __syncthreads();
+    forward_groups((const bf16x8*)sW, (const float*)sB, X, n, out);
 }
 
 // Inference on a small batch, a block of four wavefronts per group (GroupOperands), from
@@ -752,6 +777,7 @@ struct MlpWork {
 
 constexpr int FWD_BLOCKS = 1024;
 constexpr int64_t FWD_SMALL = 4096;
+constexpr int64_t FWD_LARGE = 262144;
 
 // blocks of k_mlp_train: a 16-sample group each, at most two rounds of the chip
 int train_blocks(int64_t rows) { return (int)std::min<int64_t>(FWD_BLOCKS, rows / 16); }
@@ -935,9 +961,16 @@ int pic1d_mlp_forward(const float* params, int64_t n, const float* x, float* out
                            reinterpret_cast<const float4*>(x), n, out);
     } else if (n > 0) {
         hipLaunchKernelGGL(k_mlp_pack, dim3(64), dim3(MLP_TPB), 0, s, params, w.ft, w.bt, w.bias);
-        const int blocks = (int)std::min<int64_t>(FWD_BLOCKS, (n + 63) / 64);
-        hipLaunchKernelGGL(k_mlp_forward, dim3(blocks), dim3(MLP_TPB), 0, s, w.ft, w.bias,
-                           reinterpret_cast<const float4*>(x), n, out);
+        const float4* X = reinterpret_cast<const float4*>(x);
+        if (n >= FWD_LARGE) {
+            int dev = 0, n_cu = 0;
+            MLP_TRY(hipGetDevice(&dev));
+            MLP_TRY(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
+            hipLaunchKernelGGL(k_mlp_forward_lds, dim3(n_cu), dim3(FWD_LDS_TPB), 0, s, w.ft, w.bias, X, n, out);
+        } else {
+            const int blocks = (int)std::min<int64_t>(FWD_BLOCKS, (n + 63) / 64);
+            hipLaunchKernelGGL(k_mlp_forward, dim3(blocks), dim3(MLP_TPB), 0, s, w.ft, w.bias, X, n, out);
+        }
     }
     MLP_TRY(hipGetLastError());
     MLP_TRY(hipStreamSynchronize(s));

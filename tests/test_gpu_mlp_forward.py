@@ -1,5 +1,5 @@
-"""The surrogate's forward pass on both sides of its small-batch kernel: group edges, and parameters
-that are not 16-byte aligned (the packing path), against the oracle."""
+"""The surrogate's forward pass on both sides of its small-batch and its large-batch kernel: group
+edges, and parameters that are not 16-byte aligned (the packing path), against the oracle."""
 import numpy as np
 import pytest
 
@@ -11,7 +11,8 @@ from .test_gpu_mlp import OUT_TOL, _box_inputs, _params, _torch
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n,shift", [(1, 0), (17, 0), (4095, 0), (4096, 0), (4097, 0), (33, 1), (4096, 3)])
+@pytest.mark.parametrize("n,shift", [(1, 0), (17, 0), (4095, 0), (4096, 0), (4097, 0), (33, 1), (4096, 3), (262143, 0),
+                                     (262149, 1)])
 def test_forward_at_small_batch_edges(n, shift):
     torch = _torch()
     print("forward", n, shift, flush=True)
