@@ -723,6 +723,7 @@ int enqueue_step(pic1d_state* st) {
             ca.pair_step = st->pair_step; ca.counters = st->counters; ca.sc = st->sc;
             ca.photons = st->photons; ca.n_photons = st->n_photons; ca.photon_region = st->lay.photon_region;
             ca.conversion = st->cfg.conversion;
+            ca.n_lines = st->lay.n_lines;
             ca.key0 = (uint32_t)(st->cfg.seed & 0xFFFFFFFFu); ca.key1 = (uint32_t)(st->cfg.seed >> 32);
             // one block per CU: every block first scans the record regions' fills, which
             // is most of the launch where few photons were recorded (four per CU cost

@@ -100,6 +100,7 @@ struct ConvertArgs {
     const int32_t* n_photons;
     int32_t photon_region;
     int32_t conversion;
+    int32_t n_lines;
     uint32_t key0, key1;
 };
 

@@ -969,13 +969,18 @@ template __global__ void k_push<RICS_MLP, 4, 32, 2, 2>(PushArgs);
 // is below n_max.  Float64 throughout: the member momenta are ill-conditioned in
 // eps when eps/2 is close to 1.
 // ---------------------------------------------------------------------------
-// The records of all regions form one index space (regions in order); a block
-// takes CONV_CHUNK consecutive records at a time, CONV_K per thread.  The slots of
-// a chunk's pairs are reserved with one atomic per (block, line) on each
-// allocation counter: those counters are single addresses that every block
-// hits, and device-wide atomics on one address serialise.
+// The records of all regions form one index space (regions in order); a block takes
+// a chunk of consecutive records at a time, up to CONV_K per thread: as few as give
+// every block one, for a chunk is a chain of dependent loads, scans and atomics and
+// the blocks' chunks run side by side.  The slots of a chunk's pairs are reserved with
+// one atomic per (block, line) on each allocation counter: those counters are single
+// addresses that every block hits, and device-wide atomics on one address serialise.
+// On a single line no record's line is looked for, and a chunk whose pairs all fit their
+// segments needs no third scan.  Bound by the latency of that chain: k_append 9.3 us a
+// step at a few thousand records on 512 cells, 13 us on a line with some 2e4 and 20 us on
+// lines with some 1e5 (20, 26 and 34 us with CONV_K records a thread always, three scans
+// a line and the two reservations one after the other).
 constexpr int CONV_K = 4;
-constexpr int CONV_CHUNK = 256 * CONV_K;
 static_assert(PHOTON_REPL % 64 == 0 && PHOTON_REPL <= 256, "region fills: PHOTON_REPL / 64 per lane of one wave");
 
 struct ConvRec {
@@ -1092,12 +1097,15 @@ __device__ __forceinline__ void convert_photons(const ConvertArgs& a, int blk, i
     }
     __syncthreads();
     const int total = s_pref[PHOTON_REPL];
-    for (int c0 = blk * CONV_CHUNK; c0 < total; c0 += nblk * CONV_CHUNK) {
+    const int per = max(1, min(CONV_K, (total - 1) / (nblk * 256) + 1));     // records per thread
+    const int chunk = 256 * per;
+    const bool one_line = a.n_lines == 1;
+    for (int c0 = blk * chunk; c0 < total; c0 += nblk * chunk) {
         ConvRec rec[CONV_K];
 #pragma unroll
         for (int k = 0; k < CONV_K; ++k) {
             const int g = c0 + k * 256 + (int)threadIdx.x;
-            const bool valid = g < total;
+            const bool valid = k < per && g < total;
             PhotonRec p{};
             if (valid) {
                 int lo = 0, hi = PHOTON_REPL;          // s_pref[lo] <= g < s_pref[hi]
@@ -1111,15 +1119,18 @@ __device__ __forceinline__ void convert_photons(const ConvertArgs& a, int blk, i
         }
         // one reservation per line present in the chunk, lowest line first
         while (true) {
-            int m = INT32_MAX;
+            int gl = 0;
+            if (!one_line) {
+                int m = INT32_MAX;
 #pragma unroll
-            for (int k = 0; k < CONV_K; ++k) m = min(m, rec[k].line);
-            m = wave_min_i(m);
-            if (lane == 0) s_part[threadIdx.x >> 6] = m;
-            __syncthreads();
-            const int gl = min(min(s_part[0], s_part[1]), min(s_part[2], s_part[3]));
-            __syncthreads();
-            if (gl == INT32_MAX) break;
+                for (int k = 0; k < CONV_K; ++k) m = min(m, rec[k].line);
+                m = wave_min_i(m);
+                if (lane == 0) s_part[threadIdx.x >> 6] = m;
+                __syncthreads();
+                gl = min(min(s_part[0], s_part[1]), min(s_part[2], s_part[3]));
+                __syncthreads();
+                if (gl == INT32_MAX) break;
+            }
             int mine = 0, seen = 0;
 #pragma unroll
             for (int k = 0; k < CONV_K; ++k) {
@@ -1128,14 +1139,15 @@ __device__ __forceinline__ void convert_photons(const ConvertArgs& a, int blk, i
             }
             int nconv = 0;
             const int before = block_scan(mine, nconv, s_part);
-            int nseen = 0;
-            block_scan(seen, nseen, s_part);
-            if (threadIdx.x == 0) {
-                s_base[0] = nconv > 0 ? atomicAdd(&a.alloc[4 * gl + 0], nconv) : 0;
-                s_base[1] = nconv > 0 ? atomicAdd(&a.alloc[4 * gl + 1], nconv) : 0;
-            }
+            int nseen = min(chunk, total - c0);
+            if (!one_line) block_scan(seen, nseen, s_part);
+            // (the two round trips side by side, from two wavefronts)
+            if (threadIdx.x == 0) s_base[0] = nconv > 0 ? atomicAdd(&a.alloc[4 * gl + 0], nconv) : 0;
+            if (threadIdx.x == 64) s_base[1] = nconv > 0 ? atomicAdd(&a.alloc[4 * gl + 1], nconv) : 0;
             __syncthreads();
             const int base_e = s_base[0] + before, base_p = s_base[1] + before;
+            const bool fits = (int64_t)s_base[0] + nconv <= a.seg_cap[4 * gl + 0] &&
+                              (int64_t)s_base[1] + nconv <= a.seg_cap[4 * gl + 1];
             __syncthreads();
             int made = 0, j = 0;
 #pragma unroll
@@ -1170,13 +1182,14 @@ __device__ __forceinline__ void convert_photons(const ConvertArgs& a, int blk, i
                 }
                 rec[k].line = INT32_MAX;      // done with this record
             }
-            int n_made = 0;
-            block_scan(made, n_made, s_part);
+            int n_made = nconv;
+            if (!fits) block_scan(made, n_made, s_part);
             if (threadIdx.x == 0) {
                 const size_t rep = ((size_t)gl * CNT_REPL + (blk & (CNT_REPL - 1))) * NCOUNT;
                 if (n_made) atomicAdd(&a.counters[rep + 1], (unsigned long long)n_made);
                 if (nseen - n_made) atomicAdd(&a.counters[rep + 2], (unsigned long long)(nseen - n_made));
             }
+            if (one_line) break;
         }
     }
 }
@@ -2337,10 +2350,11 @@ __global__ __launch_bounds__(256) void k_hist(HistArgs h) {
 // ---------------------------------------------------------------------------
 // Moments: cloud-in-cell charge on nodes (fixed point), kinetic energy.
 // A block takes 256 MOM_U consecutive particles of one of the line's segments at a
-// time; neighbours in memory share cells, so a thread adds its runs of particles of
+// time, the chunks of the four segments dealt in turn, so that small segments share the
+// blocks; neighbours in memory share cells, so a thread adds its runs of particles of
 // one cell, and the block collects its charge in an LDS window of nodes before the
 // global one.  Bound by the float64 arithmetic of the kinetic energy: 153 us for 3.9e7
-// particles on 65,536 cells, 20 us for 1.5e5 on 512 (400 and 55 us with a segmented sum
+// particles on 65,536 cells, 14 us for 1.5e5 on 512 (400 and 55 us with a segmented sum
 // over every wavefront in place of the window, and atomics on three addresses for the
 // kinetic energy).
 // ---------------------------------------------------------------------------
@@ -2355,13 +2369,17 @@ __global__ __launch_bounds__(256) void k_moments_particles(MomArgs m) {
     // the order in which particles are visited (bits below 2^-48 of a term dropped)
     unsigned long long k0 = 0, k1 = 0, k2 = 0;
     constexpr int CHUNK = 256 * MOM_U;
+    // the chunks of the line's four segments are dealt to the blocks in turn
+    int64_t next = blockIdx.x;
     for (int sp = 0; sp < NSPEC; ++sp) {
         const int seg = 4 * m.line + sp;
         const int ncur = m.n_cur[seg];
         const int64_t base = m.seg_base[seg];
         const long long sg = m.sign[sp] < 0.0 ? -1 : 1;
         const double mass = (sp == 3) ? m.mass_ratio : 1.0;
-        for (int64_t i0 = (int64_t)blockIdx.x * CHUNK; i0 < ncur; i0 += (int64_t)gridDim.x * CHUNK) {
+        const int64_t nchunk = (ncur + (int64_t)CHUNK - 1) / CHUNK;
+        for (; next < nchunk; next += gridDim.x) {
+            const int64_t i0 = next * CHUNK;
             int cv[MOM_U];
             float ov[MOM_U], uv[MOM_U];
             int lo = INT32_MAX, hi = -1;
@@ -2447,6 +2465,7 @@ __global__ __launch_bounds__(256) void k_moments_particles(MomArgs m) {
             }
             __syncthreads();
         }
+        next -= nchunk;
     }
     for (int o = 32; o > 0; o >>= 1) {
         k0 += __shfl_xor(k0, o, 64);
