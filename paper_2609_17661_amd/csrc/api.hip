@@ -83,7 +83,8 @@ struct pic1d_state {
     long long *pair_sum = nullptr, *n_sum = nullptr, *avg_count = nullptr;
     float4* nodes = nullptr;
     double* rc_nodes = nullptr;
-    float4* table = nullptr;
+    float4* cell_rec = nullptr;
+    float2* table = nullptr;
     int32_t *ann_k = nullptr, *ann_off = nullptr, *ann_fill = nullptr, *ann_ctl = nullptr;
     uint32_t* ann_thr = nullptr;
     int32_t *layer_cell = nullptr, *layer_line = nullptr, *layer_target = nullptr;
@@ -223,7 +224,7 @@ void carve(Carver& cv, const Layout& L, pic1d_state* st) {
     s->sort_prefix = cv.take<int32_t>(L.nseg + 1);
     s->dlines = cv.take<LineDev>(L.n_lines);
     s->E = cv.take<double>(L.n_cells);
-    s->E32 = cv.take<float>(L.n_cells);
+    s->E32 = cv.take<float>(L.n_cells + 2 * (size_t)L.n_lines);
     s->J = cv.take<unsigned long long>(L.n_cells);
     s->j_last = cv.take<double>(L.n_cells);
     s->E_sum = cv.take<double>(L.n_cells);
@@ -242,7 +243,8 @@ void carve(Carver& cv, const Layout& L, pic1d_state* st) {
     s->avg_count = cv.take<long long>(1);
     s->nodes = cv.take<float4>(L.n_nodes);
     s->rc_nodes = cv.take<double>(L.n_nodes);
-    s->table = cv.take<float4>(std::max<int64_t>(L.table_floats / 4, 1));
+    s->cell_rec = cv.take<float4>(L.table_floats > 0 ? 2 * (size_t)L.n_cells : 1);
+    s->table = cv.take<float2>(std::max<int64_t>(L.table_floats / 2, 1));
     s->ann_k = cv.take<int32_t>(L.n_cells);
     s->ann_off = cv.take<int32_t>(L.n_cells);
     s->ann_thr = cv.take<uint32_t>(L.n_cells);
@@ -310,6 +312,7 @@ PushArgs push_args(pic1d_state* st) {
     a.pairs = st->cfg.pairs; a.conversion = st->cfg.conversion; a.emission = st->cfg.emission;
     a.gravity = st->cfg.atmosphere && st->cfg.gravity;
     a.lines = st->dlines; a.E32 = st->E32; a.J = st->J; a.nodes = st->nodes; a.rc_nodes = st->rc_nodes;
+    a.cell_rec = st->cell_rec;
     a.table = st->table; a.hist[0] = st->hist[0]; a.hist[1] = st->hist[1];
     a.pair_step = st->pair_step; a.counters = st->counters; a.sc = st->sc;
     a.key0 = (uint32_t)(st->cfg.seed & 0xFFFFFFFFu); a.key1 = (uint32_t)(st->cfg.seed >> 32);
@@ -609,7 +612,7 @@ int pic1d_init(const pic1d_config* cfg, pic1d_state** out) {
         da.theta = cfg->kT_keV / 510.99895000;
         for (int l = 0; l < st->lay.n_lines; ++l) {
             const LineHost& lh = st->lines[l];
-            da.table = st->table + lh.dev.table_off;
+            da.table = st->table + 2 * (int64_t)lh.dev.table_off;
             da.R = cfg->lines[l].r_eq;
             da.L = lh.L_rstar;
             da.AF = lh.AF;
@@ -626,6 +629,11 @@ int pic1d_init(const pic1d_config* cfg, pic1d_state** out) {
     INIT_TRY(hipMemcpyAsync(st->chunk_line, chunk_line.data(), chunk_line.size() * sizeof(int32_t), hipMemcpyHostToDevice, s));
     INIT_TRY(hipMemcpyAsync(st->line_chunk0, line_chunk0.data(), line_chunk0.size() * sizeof(int32_t),
                             hipMemcpyHostToDevice, s));
+    if (st->lay.table_floats > 0) {
+        hipLaunchKernelGGL(k_cell_records, dim3(std::max(1, st->n_cu)), dim3(256), 0, s, st->cell_rec, st->nodes,
+                           st->cell_line, st->dlines, st->lay.n_cells, cfg->table_ns, cfg->table_nlg);
+        INIT_TRY(hipGetLastError());
+    }
     if (st->lay.mlp) {
         for (int k = 0; k < 6; ++k) st->mlp_norm[k] = cfg->mlp_norm[k];
         for (int l = 0; l < st->lay.n_lines && !mlp_fallback; ++l) {
@@ -1261,7 +1269,9 @@ int pic1d_set_field(pic1d_state* st, int32_t line, const double* E) {
     HIP_TRY(st, hipStreamSynchronize(st->stream));
     HIP_TRY(st, copy_sync(st->stream, st->E + d.cell_base, E, 8 * (size_t)d.n_cells, hipMemcpyHostToDevice));
     std::vector<float> e32(E, E + d.n_cells);
-    HIP_TRY(st, copy_sync(st->stream, st->E32 + d.cell_base, e32.data(), 4 * (size_t)d.n_cells, hipMemcpyHostToDevice));
+    e32.insert(e32.begin(), e32.front());
+    e32.push_back(e32.back());
+    HIP_TRY(st, copy_sync(st->stream, st->E32 + d.field_base - 1, e32.data(), 4 * e32.size(), hipMemcpyHostToDevice));
     return PIC1D_OK;
 }
 

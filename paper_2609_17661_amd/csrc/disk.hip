@@ -13,9 +13,9 @@
 // over the product rule of n_c Gauss-Legendre nodes in cos t on [cos theta_d, 1]
 // and n_phi in phi on [0, pi] (weights doubled: the integrand is even in phi).
 // Taking the cone to pi/x^2 directions at mu' = mu gives back the radial beam.
-// The table has the layout of the radial one: [ns][nlg] records
-// {F(i), F(i+1), Ndot(i), Ndot(i+1)} at log10 gamma_i = 8 i/(nlg - 1) and row
-// centres s_j = (j + 1/2) L / ns, u >= 0 (u < 0 by the mirror of the lookup).
+// The table has the layout of the radial one: [ns][nlg] pairs
+// {F(j, i), F(j + 1, i)} at log10 gamma_i = 8 i/(nlg - 1) and row centres
+// s_j = (j + 1/2) L / ns, then as many of Ndot, u >= 0 (u < 0 by the mirror of the lookup).
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -84,18 +84,19 @@ __global__ __launch_bounds__(256) void k_disk_table(DiskTableArgs a) {
         }
         F *= a.AF / 3.14159265358979323846;
         N *= a.AN / (3.14159265358979323846 * gam);
-        // record i holds columns i and i + 1: this column is the first of record i and
-        // the second of record i - 1 (the last record repeats it, as the clamp needs)
-        float* r = tab + 4 * ((size_t)j * a.nlg + i);
-        r[0] = (float)F;
-        r[2] = (float)N;
-        if (i > 0) {
-            r[-3] = (float)F;
-            r[-1] = (float)N;
+        // a pair holds rows j and j + 1: this node is the first of its own pair and the
+        // second of the row before's (the last row repeats it)
+        float* f = tab + 2 * ((size_t)j * a.nlg + i);
+        float* nd = f + 2 * (size_t)a.nlg * a.ns;
+        f[0] = (float)F;
+        nd[0] = (float)N;
+        if (j > 0) {
+            f[1 - 2 * a.nlg] = (float)F;
+            nd[1 - 2 * a.nlg] = (float)N;
         }
-        if (i == a.nlg - 1) {
-            r[1] = (float)F;
-            r[3] = (float)N;
+        if (j == a.ns - 1) {
+            f[1] = (float)F;
+            nd[1] = (float)N;
         }
     }
 }

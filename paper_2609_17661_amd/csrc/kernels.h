@@ -58,11 +58,12 @@ struct PushArgs {
     int32_t pairs, conversion, gravity;
     int32_t emission;          // PIC1D_EMIT_*
     const LineDev* lines;
-    const float* E32;          // float32 copy of E (the gather needs no more)
+    const float* E32;          // float32 copy of E (the gather needs no more), the end cells doubled
     unsigned long long* J;
     const float4* nodes;
     const double* rc_nodes;
-    const float4* table;       // RICS tables, [line][ns][nlg] {F(i), F(i+1), Ndot(i), Ndot(i+1)}
+    const float4* cell_rec;    // table backend, two per cell: geometry and table rows (k_cell_records)
+    const float2* table;       // RICS tables: per line [ns][nlg] {F(j, i), F(j + 1, i)}, then of Ndot
     int32_t* hist[2];          // per-cell counts, ping-pong by step parity
     int32_t* pair_step;
     unsigned long long* counters;   // [line][CNT_REPL][NCOUNT]
@@ -294,7 +295,7 @@ struct MomArgs {
 // n_c x n_phi nodes over the stellar disk, float64, written as float32 records.
 constexpr int DISK_MAX_NODES = 32;
 struct DiskTableArgs {
-    float4* table;              // the line's [ns][nlg] records
+    float2* table;              // the line's pairs of F, then of Ndot
     double R, b_pole, L;        // R_max / R*, B* / B_QED, line length (R*)
     double theta, AF, AN;       // kT / m_e c^2 and the prefactors of the radial beam
     int32_t nlg, ns, n_c, n_phi;
@@ -316,6 +317,8 @@ __global__ void k_mlp_pack(const float* p, bf16x8* ft, bf16x8* bt, float* bias);
 __global__ void k_mlp_line_error(PushArgs a, const double* row_geo, double kT_keV, unsigned int* err);
 __global__ void k_rics_eval_mlp(PushArgs a, int line, int64_t n, const float* s_cells, const float* u, float* F,
                                 float* N, float* eps);
+__global__ void k_cell_records(float4* rec, const float4* nodes, const int32_t* cell_line, const LineDev* lines, int n_total,
+                               int ns, int nlg);
 __global__ void k_append(ConvertArgs ca, AtmArgs aa, int conv_blocks);
 __global__ void k_plan(BookArgs b, int advance_step);
 __global__ void k_field(FieldArgs f, BookArgs b);

@@ -97,15 +97,30 @@ struct TileWalk {
     }
 };
 
-// Geometry of a particle at cell c0, offset f: linear between the two nodes.
-__device__ __forceinline__ Geo geo_lerp(const LineDev& L, const float4& a, const float4& b, float f) {
+// {b, mu, x} of a cell's lower node and their change over the cell.
+struct GeoCell {
+    float b, mu, x, db, dmu, dx;
+    __device__ __forceinline__ void load(const float4& lo, const float4& hi) {
+        b = lo.x; mu = lo.y; x = lo.z;
+        db = hi.x - lo.x; dmu = hi.y - lo.y; dx = hi.z - lo.z;
+    }
+};
+
+// Geometry of a particle at offset f in its cell: linear between the two nodes.
+__device__ __forceinline__ Geo geo_lerp(const LineDev& L, const GeoCell& c, float f) {
     Geo g;
-    g.b = fmaf(f, b.x - a.x, a.x);
-    g.mu = fmaf(f, b.y - a.y, a.y);
-    const float xr = fmaf(f, b.z - a.z, a.z);
+    g.b = fmaf(f, c.db, c.b);
+    g.mu = fmaf(f, c.dmu, c.mu);
+    const float xr = fmaf(f, c.dx, c.x);
     g.ix2 = frcp(xr * xr);
     g.by = g.b * L.inv_theta;
     return g;
+}
+
+__device__ __forceinline__ Geo geo_lerp(const LineDev& L, const float4& lo, const float4& hi, float f) {
+    GeoCell c;
+    c.load(lo, hi);
+    return geo_lerp(L, c, f);
 }
 
 __device__ __forceinline__ Geo geo_at(const LineDev& L, const float4* __restrict__ nodes, int node, float f) {
@@ -128,17 +143,18 @@ struct PartGeo {
     TabMemo memo;
 };
 
-// The line's table and its second row (row j0 + 1 at the same byte offset).
+// The line's table, and how far its Ndot lies behind its F.
 __device__ __forceinline__ const char* tab_base(const PushArgs& a, const LineDev& L) {
-    return reinterpret_cast<const char*>(a.table + L.table_off);
+    return reinterpret_cast<const char*>(a.table + 2 * (int64_t)L.table_off);
 }
+__device__ __forceinline__ uint32_t tab_n_off(const PushArgs& a) { return 8u * (uint32_t)(a.ns * a.nlg); }
 
 // F_hat at u with what dF/du needs (evaluated only where the midpoint asks for it).
 template <int BACKEND>
 __device__ __forceinline__ auto rics_eval(const PushArgs& a, const LineDev& L, float u, PartGeo& pg) {
     if constexpr (BACKEND == RICS_TABLE) {
         const char* tb = tab_base(a, L);
-        return table_eval(L, tb, tb + 16 * a.nlg, a.nlg, pg.rows, u, pg.memo);
+        return table_eval(L, tb, tab_n_off(a), a.nlg, pg.rows, u, pg.memo);
     } else {
         return exact_eval(L, u, pg.g);
     }
@@ -150,7 +166,7 @@ template <int BACKEND>
 __device__ __forceinline__ float rics_N(const PushArgs& a, const LineDev& L, float u, PartGeo& pg) {
     if constexpr (BACKEND == RICS_TABLE) {
         const char* tb = tab_base(a, L);
-        return table_N(L, tb, tb + 16 * a.nlg, a.nlg, pg.rows, u, pg.memo);
+        return table_N(L, tb, tab_n_off(a), a.nlg, pg.rows, u, pg.memo);
     } else {
         return exact_N(L, u, pg.g);
     }
@@ -163,7 +179,7 @@ __device__ __forceinline__ PartGeo part_geo(const PushArgs& a, const LineDev& L,
                                             int c0, float o0) {
     PartGeo pg;
     pg.g = geo_lerp(L, n0, n1, o0);
-    if constexpr (BACKEND == RICS_TABLE) pg.rows = table_rows(L, a.ns, 16 * a.nlg, (double)c0 + (double)o0);
+    if constexpr (BACKEND == RICS_TABLE) pg.rows = table_rows(L, a.ns, 8 * a.nlg, (double)c0 + (double)o0);
     return pg;
 }
 
@@ -251,8 +267,11 @@ __device__ __forceinline__ float stochastic_step(const PushArgs& a, const LineDe
     if (!(lam > 0.0f)) return u;
     ++cnt.draws;
     const uint64_t pid = a.id[k];
-    const uint4 w = philox4x32_10(make_uint4((uint32_t)T.step, (uint32_t)pid, (uint32_t)(pid >> 32), STREAM_RICS),
-                                  a.key0, a.key1);
+    // (the round keys formed here: kept for the launch, they spill)
+    uint32_t k0 = a.key0, k1 = a.key1;
+    asm volatile("" : "+s"(k0), "+s"(k1));
+    const uint4 w = philox4x32_10_wide(make_uint4((uint32_t)T.step, (uint32_t)pid, (uint32_t)(pid >> 32), STREAM_RICS),
+                                       k0, k1);
     if (!(uniform24(w.x) < fminf(lam, 1.0f))) return u;
     ++cnt.events;
     const float gam = fsqrt(fmaf(u, u, 1.0f));
@@ -383,47 +402,72 @@ __device__ __forceinline__ float mlp_drag_half(const PushArgs& a, const bf16x8* 
 // The kick q E / (m C) is kept as its value at the cell centre and its change per
 // cell towards the neighbouring centres, whose E is clamped at the walls (the
 // gather is constant beyond the outermost cell centres).  The table backend
-// keeps the per-cell part of the particle's table rows: for offset o the row
-// position is rows0.pos.wj + o s_scale (u >= 0) and rows0.neg.wj - o s_scale
-// (mirrored), valid for the whole cell where rows_simple (the cell lies between
-// two rows, clear of the clamped ends).
+// keeps the per-cell part of the particle's table rows (k_cell_records): for offset o the
+// row position is rows0.pos.wj + o s_scale (u >= 0) and rows0.neg.wj - o s_scale
+// (mirrored), valid for the whole cell where the cell lies between two rows, clear
+// of the clamped ends.
 struct CellCache {
     int cell;
     float K0, KsL, KsU;
-    float4 n0, n1;          // geometry nodes c, c+1
-    TabRows rows0;
-    bool rows_simple;
+    GeoCell geo;
+    TabRows rows0;          // (rows0.pos.off < 0: the general form)
     TabMemo memo;           // the lane's last table record (reset per tile)
 };
 
 template <int BACKEND>
 __device__ __forceinline__ void cache_load(CellCache& cc, const PushArgs& a, const LineDev& L, float qmC, int c0) {
     cc.cell = c0;
-    const float* E = a.E32 + L.cell_base;
-    const float Em = E[max(c0 - 1, 0)];
-    const float E0 = E[c0];
-    const float Ep = E[min(c0 + 1, L.n_cells - 1)];
-    cc.K0 = qmC * E0;
-    cc.KsL = qmC * (E0 - Em);
-    cc.KsU = qmC * (Ep - E0);
-    if constexpr (BACKEND != RICS_OFF) {
-        cc.n0 = a.nodes[L.node_base + c0];
-        cc.n1 = a.nodes[L.node_base + c0 + 1];
-    }
+    // (32-bit byte offsets from the line's arrays: one address register per load)
+    struct __attribute__((packed, aligned(4))) Three { float m, c, p; };
+    const uint32_t e = 4u * (uint32_t)c0;
+    const Three E = *reinterpret_cast<const Three*>(reinterpret_cast<const char*>(a.E32 + L.field_base - 1) + e);
+    cc.K0 = qmC * E.c;
+    cc.KsL = qmC * (E.c - E.m);
+    cc.KsU = qmC * (E.p - E.c);
     if constexpr (BACKEND == RICS_TABLE) {
+        const char* rec = reinterpret_cast<const char*>(a.cell_rec + 2 * (size_t)L.cell_base);
+        const float4 g = *reinterpret_cast<const float4*>(rec + 8u * e);
+        const float4 r = *reinterpret_cast<const float4*>(rec + (8u * e + 16u));
+        cc.geo.b = g.x;
+        cc.geo.mu = g.y;
+        cc.geo.db = g.z;
+        cc.geo.dmu = g.w;
+        cc.geo.x = cc.geo.dx = 0.0f;       // (in the table's values already)
+        cc.rows0.pos.off = __float_as_int(r.x);
+        cc.rows0.pos.wj = r.y;
+        cc.rows0.neg.off = __float_as_int(r.z);
+        cc.rows0.neg.wj = r.w;
+    } else if constexpr (BACKEND != RICS_OFF) {
+        const char* nd = reinterpret_cast<const char*>(a.nodes + L.node_base);
+        const float4 lo = *reinterpret_cast<const float4*>(nd + 4u * e);
+        const float4 hi = *reinterpret_cast<const float4*>(nd + (4u * e + 16u));
+        cc.geo.load(lo, hi);
+    }
+}
+
+// What the table backend's particle kernel reads of a cell, in one place, once per
+// state: {b, mu} at its lower face and their change over it; the table rows {row offset,
+// weight} at the lower face for u >= 0 and mirrored, an offset of -1 where a particle
+// has to form its rows itself.
+__global__ __launch_bounds__(256) void k_cell_records(float4* rec, const float4* nodes, const int32_t* cell_line,
+                                                      const LineDev* lines, int n_total, int ns, int nlg) {
+    for (int g = blockIdx.x * 256 + threadIdx.x; g < n_total; g += gridDim.x * 256) {
+        const LineDev& L = lines[cell_line[g]];
+        const int c = g - L.cell_base;
+        GeoCell geo;
+        geo.load(nodes[L.node_base + c], nodes[L.node_base + c + 1]);
+        rec[2 * (size_t)g] = make_float4(geo.b, geo.mu, geo.db, geo.dmu);
         const double sc = L.s_scale;
-        const double fp = fma((double)c0, sc, -0.5);
-        const double fn = fma((double)(L.n_cells - c0), sc, -0.5);
+        const double fp = fma((double)c, sc, -0.5);
+        const double fn = fma((double)(L.n_cells - c), sc, -0.5);
         const double jp = floor(fp), jn = floor(fn);
-        const double top = (double)(a.ns - 2);
+        const double top = (double)(ns - 2);
         constexpr double M = 0x1.0p-20;      // margin for the float32 row weight
-        cc.rows_simple = jp >= 0.0 && jp <= top && fp + sc <= jp + 1.0 - M &&
-                         jn >= 0.0 && jn <= top && fn - sc >= jn + M;
-        const int nlg16 = 16 * a.nlg;
-        cc.rows0.pos.off = cc.rows_simple ? (int)jp * nlg16 : 0;
-        cc.rows0.pos.wj = (float)(fp - jp);
-        cc.rows0.neg.off = cc.rows_simple ? (int)jn * nlg16 : 0;
-        cc.rows0.neg.wj = (float)(fn - jn);
+        const bool simple = jp >= 0.0 && jp <= top && fp + sc <= jp + 1.0 - M &&
+                            jn >= 0.0 && jn <= top && fn - sc >= jn + M;
+        const int nlg8 = 8 * nlg;
+        rec[2 * (size_t)g + 1] = make_float4(__int_as_float(simple ? (int)jp * nlg8 : -1), (float)(fp - jp),
+                                             __int_as_float(simple ? (int)jn * nlg8 : -1), (float)(fn - jn));
     }
 }
 
@@ -456,7 +500,7 @@ __device__ __forceinline__ void advance_particle(const PushArgs& a, const LineDe
 
     if constexpr (BACKEND == RICS_MLP) {
         if (sp != 3) {            // wave-uniform: a tile holds one species
-            const Geo g = geo_lerp(L, cc.n0, cc.n1, o0);
+            const Geo g = geo_lerp(L, cc.geo, o0);
             const float sl = (float)(((double)c0 + (double)o0) / (double)n);
             const bool cont = g.b < L.b_thr;
             const float pt = g.mu * frsq(fmaxf(fmaf(-g.mu, g.mu, 1.0f), 1e-30f));
@@ -478,16 +522,16 @@ __device__ __forceinline__ void advance_particle(const PushArgs& a, const LineDe
         }
     } else if (RICS && sp != 3) {
         PartGeo pg;
-        pg.g = geo_lerp(L, cc.n0, cc.n1, o0);
+        pg.g = geo_lerp(L, cc.geo, o0);
         if constexpr (BACKEND == RICS_TABLE) {
             pg.memo = cc.memo;
-            if (cc.rows_simple) {
+            if (cc.rows0.pos.off >= 0) {
                 pg.rows.pos.off = cc.rows0.pos.off;
                 pg.rows.pos.wj = fmaf(o0, L.s_scale_f, cc.rows0.pos.wj);
                 pg.rows.neg.off = cc.rows0.neg.off;
                 pg.rows.neg.wj = fmaf(-o0, L.s_scale_f, cc.rows0.neg.wj);
             } else {
-                pg.rows = table_rows(L, a.ns, 16 * a.nlg, (double)c0 + (double)o0);
+                pg.rows = table_rows(L, a.ns, 8 * a.nlg, (double)c0 + (double)o0);
             }
         }
         if (pg.g.b < L.b_thr) {
@@ -606,6 +650,14 @@ __device__ __forceinline__ void wave_sync() {
 // merges its lanes in a private LDS window and flushes the window to the global
 // fixed-point current with one atomic per touched cell.  No block-level
 // synchronisation.
+// Bound, with the table, by vector issue (70-80% of the cycles) and by the latency of
+// the loads at a change of cell and of the table gathers, five wavefronts per SIMD
+// covering the rest.  So a change of cell is three wide loads of ready values
+// (k_cell_records, the field's neighbours in one), a table lookup one gather, the
+// Philox keys are formed where they are used, and a run's sums go to the window as they
+// are.  2.7e7 heated particles on 65,536 cells: 244 -> 225 us; 4e7 at the density limit
+// 433 -> 394; the cascade lines 644 -> 581; 40 uneven lines 736 -> 706 (against eight
+// loads and the rows in float64 at every change of cell, and two gathers).
 template <int BACKEND, int PPT, int WW, int KIND, int SUB>
 __global__ __launch_bounds__(BACKEND == RICS_MLP ? PUSH_TPB_MLP : PUSH_TPB)
 __attribute__((amdgpu_waves_per_eu(push_waves(BACKEND)))) void k_push(PushArgs a) {
@@ -804,8 +856,8 @@ __attribute__((amdgpu_waves_per_eu(push_waves(BACKEND)))) void k_push(PushArgs a
             hi = wave_max_i(lane_hi);
         }
         const bool any = lo <= hi;
-        lo = any ? max(lo, 0) : 0;
-        hi = any ? min(hi, L.n_cells - 1) : -1;
+        lo = any ? lo : 0;
+        hi = any ? hi : -1;
         const bool use_lds = any && (hi - lo + 1) <= WW;
         const int span = use_lds ? (hi - lo + 1) : 0;
         for (int cc = lane; cc < span; cc += 64) {
@@ -831,26 +883,37 @@ __attribute__((amdgpu_waves_per_eu(push_waves(BACKEND)))) void k_push(PushArgs a
         int key = cc.cell;
         int jv0 = 0, jv1 = 0, jv2 = 0, hc = 0;
         // flush the lowest `ncells` cells of the run's three (all of them, or only
-        // key-1 when the next run starts in key+1 and the other two carry over)
+        // key-1 when the next run starts in key+1 and the other two carry over).  The
+        // window holds the sums unsigned and unshifted and has room for the cells beyond
+        // the walls, so that nothing is tested or converted here
         auto flush_run = [&](int ncells) {
             const int jv[3] = {jv0, jv1, jv2};
+            if (use_lds) {
+                if (lane_any) {
+                    unsigned long long* wj = &sJ[wid][key - 1 - lo];
+                    int* wh = &sH[wid][key - 1 - lo];
+#pragma unroll
+                    for (int r = 0; r < 3; ++r) {
+                        if (r >= ncells) continue;
+                        atomicAdd(wj + r, (unsigned long long)(long long)jv[r]);
+                        atomicAdd(wh + r, (hc >> (10 * r)) & 1023);
+                    }
+                }
+                return;
+            }
 #pragma unroll
             for (int r = 0; r < 3; ++r) {
                 const int cell = key - 1 + r;
                 const int hv = (hc >> (10 * r)) & 1023;
                 if (r < ncells && cell >= 0 && cell < L.n_cells) {
                     const long long j = (long long)(T.negative ? -jv[r] : jv[r]) << POS_TO_FIX;
-                    if (use_lds) {
-                        if (j != 0) atomicAdd(&sJ[wid][cell - lo], (unsigned long long)j);
-                        if (hv != 0) atomicAdd(&sH[wid][cell - lo], hv);
-                    } else {
-                        if (j != 0) atomicAdd(&Jg[cell], (unsigned long long)j);
-                        if (hv != 0) atomicAdd(&Hg[4 * (size_t)cell], hv);
-                    }
+                    if (j != 0) atomicAdd(&Jg[cell], (unsigned long long)j);
+                    if (hv != 0) atomicAdd(&Hg[4 * (size_t)cell], hv);
                 }
             }
         };
-        bool nonfinite = false;
+        float nonfinite = 0.0f;       // NaN once a momentum is not finite
+        int n_alive = 0;
 #pragma unroll 1
         for (int q = 0; q < PPT; ++q) {
             const int slot = (int)(visit >> (VB * q)) & ((1 << VB) - 1);
@@ -878,9 +941,8 @@ __attribute__((amdgpu_waves_per_eu(push_waves(BACKEND)))) void k_push(PushArgs a
             bool gone;
             advance_particle<BACKEND>(a, L, T, cc, alive, line, sp, base + ib + slot, cc.cell, oq, uq, cnt, c1, o1,
                                       jm, j0, jp, d, gone, sW, a.mlp_bias);
-            nonfinite = nonfinite || !isfinite(uq);
-            cnt.pushed += alive ? 1 : 0;
-            cnt.pushed_ion += (alive && sp == 3) ? 1 : 0;
+            nonfinite = fmaf(uq, 0.0f, nonfinite);
+            n_alive += __popcll(__ballot(alive));
             jv0 += jm;
             jv1 += j0;
             jv2 += jp;
@@ -890,7 +952,9 @@ __attribute__((amdgpu_waves_per_eu(push_waves(BACKEND)))) void k_push(PushArgs a
             sPu[wid][slot][lane] = gone ? 0.0f : uq;
         }
         flush_run(3);
-        if (nonfinite) set_error(&a.sc->err, -5);
+        cnt.pushed += lane == 0 ? n_alive : 0;
+        cnt.pushed_ion += lane == 0 && sp == 3 ? n_alive : 0;
+        if (nonfinite != nonfinite) set_error(&a.sc->err, -5);
         // write back (vector stores for full groups; never touch slots >= ncur, where
         // appended particles may be landing)
         if (PPT == 2 && nv == PPT) {
@@ -924,10 +988,13 @@ __attribute__((amdgpu_waves_per_eu(push_waves(BACKEND)))) void k_push(PushArgs a
         // flush the window
         wave_sync();
         for (int cc2 = lane; cc2 < span; cc2 += 64) {
-            const unsigned long long sj = sJ[wid][cc2];
-            if (sj != 0ull) atomicAdd(&Jg[lo + cc2], sj);
+            const int cell = lo + cc2;
+            const long long sj = (long long)sJ[wid][cc2] << POS_TO_FIX;
             const int sh = sH[wid][cc2];
-            if (sh != 0) atomicAdd(&Hg[4 * (size_t)(lo + cc2)], sh);
+            if ((unsigned)cell < (unsigned)L.n_cells) {
+                if (sj != 0) atomicAdd(&Jg[cell], (unsigned long long)(T.negative ? -sj : sj));
+                if (sh != 0) atomicAdd(&Hg[4 * (size_t)cell], sh);
+            }
         }
         wave_sync();
     }
@@ -1774,7 +1841,11 @@ __global__ __launch_bounds__(256) void k_field(FieldArgs f, BookArgs b) {
         if (!f.frozen) {
             const double En = f.E[g] - 4.0 * 3.14159265358979323846 * (j - L.j_tw);
             f.E[g] = En;
-            f.E32[g] = (float)En;
+            const int c = g - L.cell_base;
+            float* e32 = f.E32 + L.field_base + c;
+            e32[0] = (float)En;
+            if (c == 0) e32[-1] = (float)En;
+            if (c == L.n_cells - 1) e32[1] = (float)En;
         }
         const int ps = f.pair_step[g];
         f.pair_step[g] = 0;

@@ -42,7 +42,7 @@ struct LineDev {
     int32_t cell_base;    // first global cell
     int32_t n_cells;
     int32_t node_base;    // first global node = cell_base + line index
-    int32_t table_off;    // float4 offset of this line's RICS table
+    int32_t table_off;    // offset of this line's RICS table in units of two pairs
     float C, invC;        // cells per step at c, and its inverse
     float h;              // one step in R*/c
     float tau_hat;        // tau_min in R*/c
@@ -55,9 +55,10 @@ struct LineDev {
     float half_n;         // n_cells / 2
     int32_t use_table;    // 1: the line's RICS comes from its table (TABLE backend, or the
                           //    MLP backend where the network's error estimate exceeds the tolerance)
-    int32_t pad_ut;
+    int32_t field_base;   // E32 index of cell 0: each line has a cell more at either end, the end cells' copies
     float lgk;            // table: (nlg - 1)/16 log10(2): fractional column per unit log2 gamma^2
-    float pad_lgk[2];
+    float col_max;        // table: nlg - 1, the last column
+    float lg_scale_f;     // table: lg_scale in float32
     float s_scale_f;      // table: s_scale in float32 (rows per cell)
     double s_scale;       // table: ns / n_cells
     double lg_scale;      // table: (nlg - 1) / 8

@@ -75,7 +75,7 @@ __device__ __forceinline__ float exact_N(const LineDev& L, float u, const Geo& g
 // weight wj of row j0 + 1, for the u >= 0 half at x (cells) and for the mirrored
 // u < 0 half at L - x.  Row j sits at x = (j + 1/2) / s_scale.
 struct TabRow {
-    int off;        // j0 * nlg * 16
+    int off;        // j0 * nlg * 8
     float wj;
 };
 
@@ -85,20 +85,20 @@ struct TabRows {
 
 // General form, in float64 from the position x (the pusher takes it only where
 // a cell straddles a row or the clamped ends; elsewhere the rows are per cell).
-__device__ __forceinline__ TabRow table_row(const LineDev& L, int ns, int nlg16, double xm) {
+__device__ __forceinline__ TabRow table_row(const LineDev& L, int ns, int nlg8, double xm) {
     double fj = fma(xm, L.s_scale, -0.5);
     fj = fmin(fmax(fj, 0.0), (double)(ns - 1));
     const int j0 = min((int)fj, ns - 2);
     TabRow r;
-    r.off = j0 * nlg16;
+    r.off = j0 * nlg8;
     r.wj = (float)(fj - (double)j0);
     return r;
 }
 
-__device__ __forceinline__ TabRows table_rows(const LineDev& L, int ns, int nlg16, double x) {
+__device__ __forceinline__ TabRows table_rows(const LineDev& L, int ns, int nlg8, double x) {
     TabRows r;
-    r.pos = table_row(L, ns, nlg16, x);
-    r.neg = table_row(L, ns, nlg16, (double)L.n_cells - x);
+    r.pos = table_row(L, ns, nlg8, x);
+    r.neg = table_row(L, ns, nlg8, (double)L.n_cells - x);
     return r;
 }
 
@@ -115,46 +115,47 @@ struct TabCol {
 __device__ __forceinline__ TabCol table_col(const LineDev& L, int nlg, float ua) {
     TabCol c;
     c.g2 = fmaf(ua, ua, 1.0f);
-    const float r = fmaxf(__builtin_amdgcn_logf(c.g2) * L.lgk, 0.0f);
-    const float fr = floorf(r);
-    const int i = (int)fr;
-    const int i0 = min(i, nlg - 2);
-    // above the table the weight clamps to 1
-    const float wi = fminf((r - fr) + (float)(i - i0), 1.0f);
-    c.inside = (i == i0) && !(i == 0 && wi == 0.0f);
-    c.i0 = i0;
-    c.wi = wi;
+    // (clamped to the last column: there the weight of column nlg - 1 is 1)
+    const float r = fminf(fmaxf(__builtin_amdgcn_logf(c.g2) * L.lgk, 0.0f), L.col_max);
+    c.i0 = min((int)r, nlg - 2);
+    c.wi = r - (float)c.i0;
+    c.inside = r > 0.0f && r < L.col_max;
     return c;
 }
 
-// The last table record a lane read: its byte offset (row j0, column i0, half)
-// and the two row pairs.  Consecutive evaluations of a lane often read the same
+// The four values around a point: rows j0 and j0 + 1 at column i0, then at i0 + 1.
+struct __attribute__((packed, aligned(8))) TabQuad {
+    float a0, b0, a1, b1;
+};
+
+// The last table record a lane read: its byte offset (row j0, column i0, quantity)
+// and its values.  Consecutive evaluations of a lane often read the same
 // record (particles of one cell at similar gamma); they reuse it without a load.
 struct TabMemo {
     uint32_t o = 0xffffffffu;
-    float2 a, b;
+    TabQuad q;
 };
 
-// The table is stored as [ns][nlg] float4 {F(i), F(i+1), Ndot(i), Ndot(i+1)} so that
-// one gather per row brings both columns of a quantity.  tb is the line's table,
-// tb1 = tb + nlg * 16 bytes (row j0 + 1 at the same offset).
+// The table is stored as [ns][nlg] pairs {F(j, i), F(j + 1, i)}, then as many of Ndot,
+// n_off bytes on, so that one 16-byte gather (8-byte aligned) brings both rows and both
+// columns of a quantity, and a cache line holds 16 columns (eight, with two gathers, in
+// records of both columns of F and Ndot: 3.5e8 L1 accesses a launch of the cascade lines'
+// particle kernel, this and its cell records together, for 5.0e8).
+// tb is the line's table.
 template <int HALF>      // 0: F, 1: Ndot
-__device__ __forceinline__ float2 table_pair(const char* __restrict__ tb, const char* __restrict__ tb1,
+__device__ __forceinline__ float2 table_pair(const char* __restrict__ tb, uint32_t n_off,
                                              const TabRow& rw, const TabCol& cl, float& slope, TabMemo& m) {
-    const uint32_t o = (uint32_t)rw.off + ((uint32_t)cl.i0 << 4) + 8u * HALF;
-    float2 a, b;
+    const uint32_t o = (uint32_t)rw.off + ((uint32_t)cl.i0 << 3) + (HALF ? n_off : 0u);
+    TabQuad q;
     if (o == m.o) {
-        a = m.a;
-        b = m.b;
+        q = m.q;
     } else {
-        a = *reinterpret_cast<const float2*>(tb + o);      // row j0
-        b = *reinterpret_cast<const float2*>(tb1 + o);     // row j0 + 1
+        q = *reinterpret_cast<const TabQuad*>(tb + o);
         m.o = o;
-        m.a = a;
-        m.b = b;
+        m.q = q;
     }
-    const float fa = fmaf(rw.wj, b.x - a.x, a.x);                    // at column i0
-    const float fc = fmaf(rw.wj, b.y - a.y, a.y);                    // at column i0 + 1
+    const float fa = fmaf(rw.wj, q.b0 - q.a0, q.a0);                 // at column i0
+    const float fc = fmaf(rw.wj, q.b1 - q.a1, q.a1);                 // at column i0 + 1
     slope = fc - fa;
     return make_float2(fa, fc);
 }
@@ -166,16 +167,16 @@ struct TableEval {
     // d(fractional column)/d|u| = (nlg-1)/8 |u| / (gamma^2 ln 10); for u < 0,
     // d(-F(|u|))/du = +dF/d|u|
     __device__ __forceinline__ float dF(const LineDev& L) const {
-        return inside ? slope * (float)L.lg_scale * ua * frcp(g2 * 2.302585093f) : 0.0f;
+        return inside ? slope * L.lg_scale_f * ua * frcp(g2 * 2.302585093f) : 0.0f;
     }
 };
 
-__device__ __forceinline__ TableEval table_eval(const LineDev& L, const char* tb, const char* tb1, int nlg,
+__device__ __forceinline__ TableEval table_eval(const LineDev& L, const char* tb, uint32_t n_off, int nlg,
                                                 const TabRows& rows, float u, TabMemo& m) {
     TableEval e;
     e.ua = fabsf(u);
     const TabCol cl = table_col(L, nlg, e.ua);
-    const float2 f = table_pair<0>(tb, tb1, u < 0.0f ? rows.neg : rows.pos, cl, e.slope, m);
+    const float2 f = table_pair<0>(tb, n_off, u < 0.0f ? rows.neg : rows.pos, cl, e.slope, m);
     const float F = fmaf(cl.wi, e.slope, f.x);
     e.F = u < 0.0f ? -F : F;
     e.g2 = cl.g2;
@@ -183,11 +184,11 @@ __device__ __forceinline__ TableEval table_eval(const LineDev& L, const char* tb
     return e;
 }
 
-__device__ __forceinline__ float table_N(const LineDev& L, const char* tb, const char* tb1, int nlg,
+__device__ __forceinline__ float table_N(const LineDev& L, const char* tb, uint32_t n_off, int nlg,
                                          const TabRows& rows, float u, TabMemo& m) {
     const TabCol cl = table_col(L, nlg, fabsf(u));
     float slope;
-    const float2 n = table_pair<1>(tb, tb1, u < 0.0f ? rows.neg : rows.pos, cl, slope, m);
+    const float2 n = table_pair<1>(tb, n_off, u < 0.0f ? rows.neg : rows.pos, cl, slope, m);
     return fmaf(cl.wi, slope, n.x);
 }
 

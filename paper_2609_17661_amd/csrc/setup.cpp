@@ -140,6 +140,7 @@ void build_line(const pic1d_config* c, int line, int32_t cell_base, int32_t tabl
     d.cell_base = cell_base;
     d.n_cells = n;
     d.node_base = cell_base + line;
+    d.field_base = cell_base + 2 * line + 1;
     d.table_off = table_off;
     d.C = (float)C;
     d.invC = (float)(1.0 / C);
@@ -156,6 +157,8 @@ void build_line(const pic1d_config* c, int line, int32_t cell_base, int32_t tabl
     d.use_table = c->rics_backend == 2 ? 1 : 0;     // the MLP backend's lines decide at init
     d.s_scale_f = (float)d.s_scale;
     d.lgk = (float)(0.5 * d.lg_scale * log10(2.0));
+    d.col_max = (float)(table ? c->table_nlg - 1 : 0);
+    d.lg_scale_f = (float)d.lg_scale;
     const double nmax = (c->nmax_over_n0 > 0.0 ? c->nmax_over_n0 : c->d0_cells * c->d0_cells) * c->ppc0;
     d.nmax = (float)nmax;
     d.half_n = 0.5f * (float)n;
@@ -203,7 +206,7 @@ void build_line(const pic1d_config* c, int line, int32_t cell_base, int32_t tabl
     }
 
     // RICS table for u >= 0 at log10 gamma_i = 8 i/(nlg-1), s_j = (j + 1/2) L/ns, stored as
-    // [ns][nlg] records {F(i), F(i+1), Ndot(i), Ndot(i+1)} (column i+1 clamped at the end)
+    // [ns][nlg] pairs {F(j, i), F(j + 1, i)}, then as many of Ndot (row j + 1 clamped at the end)
     o.table.clear();
     o.row_geo.clear();
     if (table && c->photon_field == 1) {
@@ -226,12 +229,18 @@ void build_line(const pic1d_config* c, int line, int32_t cell_base, int32_t tabl
                 rics_closed(u, g.b, g.mu, g.x, theta, AF, AN, Fr[i], Nr[i]);
             }
             for (int i = 0; i < nlg; ++i) {
-                const int i1 = std::min(i + 1, nlg - 1);
-                float* rec = &o.table[4 * ((size_t)j * nlg + i)];
-                rec[0] = (float)Fr[i];
-                rec[1] = (float)Fr[i1];
-                rec[2] = (float)Nr[i];
-                rec[3] = (float)Nr[i1];
+                float* f = &o.table[2 * ((size_t)j * nlg + i)];
+                float* nd = f + 2 * (size_t)nlg * ns;
+                f[0] = (float)Fr[i];
+                nd[0] = (float)Nr[i];
+                if (j > 0) {
+                    f[1 - 2 * nlg] = f[0];
+                    nd[1 - 2 * nlg] = nd[0];
+                }
+                if (j == ns - 1) {
+                    f[1] = f[0];
+                    nd[1] = nd[0];
+                }
             }
         }
     }
