@@ -769,7 +769,7 @@ int enqueue_step(pic1d_state* st) {
             an.seg_base = st->seg_base; an.seg_cap = st->seg_cap; an.alloc = st->alloc;
             an.hist[0] = st->hist[0]; an.hist[1] = st->hist[1];
             an.cell_line = st->cell_line; an.lines = st->dlines;
-            an.n_total = nt; an.n_lines = st->lay.n_lines;
+            an.n_total = nt; an.n_lines = st->lay.n_lines; an.tile = 64 * st->ppt;
             an.ann_k = st->ann_k; an.ann_off = st->ann_off; an.ann_thr = st->ann_thr; an.ann_fill = st->ann_fill; an.ann_ctl = st->ann_ctl;
             // candidate records in the other particle buffer set (written only by the sort)
             an.cand_key = st->id[1 - b];

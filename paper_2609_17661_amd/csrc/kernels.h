@@ -25,8 +25,7 @@ constexpr int SORT_TILE = SORT_TPB * SORT_U;    // consecutive slots of a segmen
 constexpr int SORT_W = 2048;                    // bins of a tile ranked at a time in LDS
 constexpr int SORT_PASSES = 8;                  // windows of SORT_W bins at most; wider tiles go to the global bins
 
-constexpr int GATHER_U = 4;                     // particles per thread and pass of the annihilation gather
-constexpr int GATHER_BLOCKS_PER_CU = 16;        // its blocks per CU
+constexpr int GATHER_BLOCKS_PER_CU = 16;        // blocks of the annihilation gather per CU
 
 constexpr int PHOTON_REPL = 256;                // append regions of the photon buffer (one per wavefront
                                                 // slot of a block and block mod 64: spreads the reservations)
@@ -156,6 +155,7 @@ struct AnnihArgs {
     const LineDev* lines;
     int32_t n_total;            // cells over all lines
     int32_t n_lines;
+    int32_t tile;               // particles per planned tile
     int32_t* ann_k;             // per global cell: pairs to annihilate this step, 0 if none
     int32_t* ann_off;           // per global cell: first candidate record (e- then e+)
     uint32_t* ann_thr;          // per global cell: largest high key word recorded, 0 if none

@@ -1894,22 +1894,13 @@ __device__ __forceinline__ int& int4_at(int4& v, int k) {
 }
 
 // The candidates: every live e- and e+ (appends included) of a cell over the limit
-// whose key is at most the cell's threshold records its key and slot.  Exits at once
-// when no cell is over the limit.  Bound by HBM: 4 bytes of cell, and in a cell over
-// the limit 8 of id, per particle (with every candidate recorded it was bound by the
-// records' scattered writes and the lanes' matching: 118 -> 88 us on a 65,536-cell line
-// of 600 per cell, 185 -> 138 us on eight lines of 32,768, 20 -> 14 us on one of 9,973).
-__global__ __launch_bounds__(256) void k_annih_gather(AnnihArgs a) {
-    if (a.sc->err != 0) return;
-    // a copy of the over-limit flag for k_field, which clears [1] for the next step
-    // while its other blocks still need to know
-    if (blockIdx.x == 0 && threadIdx.x == 0) a.ann_ctl[2] = a.ann_ctl[1];
-    if (a.ann_ctl[1] == 0) return;
+// whose key is at most the cell's threshold records its key and slot.  A thread takes
+// U particles per pass, four consecutive ones by one load, and issues its loads
+// together.
+template <int U>
+__device__ __forceinline__ void annih_gather(const AnnihArgs& a) {
     const uint64_t step = a.sc->step;
     const int32_t* hist_out = a.hist[(step & 1) ^ 1];
-    // a thread takes GATHER_U particles per pass and issues their loads together, so
-    // that several loads are in flight per lane
-    constexpr int U = GATHER_U;
     constexpr int CHUNK = 256 * U;
     // the chunks of all segments are dealt to the blocks in turn
     int64_t first = blockIdx.x;                                  // this block's next chunk, from the segment's start
@@ -1921,16 +1912,36 @@ __global__ __launch_bounds__(256) void k_annih_gather(AnnihArgs a) {
             const int64_t base = a.seg_base[seg];
             const int64_t nchunk = (n + (int64_t)CHUNK - 1) / CHUNK;     // (a segment may hold nearly 2^31 slots)
             for (; first < nchunk; first += gridDim.x) {
-                const int64_t i0 = first * CHUNK + (int)threadIdx.x;
+                // four consecutive particles at a time; a group that starts below n lies within
+                // the segment (capacities are multiples of 256)
+                const int64_t i0 = first * CHUNK + 4 * (int)threadIdx.x;
+                auto at = [&](int u) { return i0 + (u >> 2) * 1024 + (u & 3); };
                 int cu[U];
                 uint32_t tu[U];
                 uint64_t du[U];
 #pragma unroll
-                for (int u = 0; u < U; ++u) cu[u] = i0 + u * 256 < n ? a.cell[base + i0 + u * 256] : DEAD_CELL;
+                for (int u = 0; u < U; u += 4) {
+                    const int4 c = at(u) < n ? *reinterpret_cast<const int4*>(a.cell + base + at(u))
+                                             : make_int4(DEAD_CELL, DEAD_CELL, DEAD_CELL, DEAD_CELL);
+                    cu[u] = c.x;
+                    cu[u + 1] = at(u + 1) < n ? c.y : DEAD_CELL;
+                    cu[u + 2] = at(u + 2) < n ? c.z : DEAD_CELL;
+                    cu[u + 3] = at(u + 3) < n ? c.w : DEAD_CELL;
+                }
 #pragma unroll
                 for (int u = 0; u < U; ++u) tu[u] = cu[u] != DEAD_CELL ? a.ann_thr[cb + cu[u]] : 0u;
 #pragma unroll
-                for (int u = 0; u < U; ++u) du[u] = tu[u] != 0u ? a.id[base + i0 + u * 256] : 0ull;
+                for (int u = 0; u < U; u += 4) {
+                    ulonglong2 d0 = make_ulonglong2(0ull, 0ull), d1 = d0;
+                    if ((tu[u] | tu[u + 1] | tu[u + 2] | tu[u + 3]) != 0u) {
+                        d0 = *reinterpret_cast<const ulonglong2*>(a.id + base + at(u));
+                        d1 = *reinterpret_cast<const ulonglong2*>(a.id + base + at(u) + 2);
+                    }
+                    du[u] = d0.x;
+                    du[u + 1] = d0.y;
+                    du[u + 2] = d1.x;
+                    du[u + 3] = d1.y;
+                }
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
                     if (tu[u] == 0u) continue;
@@ -1945,12 +1956,29 @@ __global__ __launch_bounds__(256) void k_annih_gather(AnnihArgs a) {
                     }
                     const int64_t rec = (int64_t)a.ann_off[g] + (s ? h[0] : 0) + r;
                     a.cand_key[rec] = key;
-                    a.cand_slot[rec] = (int)(i0 + u * 256);
+                    a.cand_slot[rec] = (int)at(u);
                 }
             }
             first -= nchunk;
         }
     }
+}
+
+// Exits at once when no cell is over the limit.  Bound by HBM: 4 bytes of cell, and in a
+// cell over the limit 8 of id, per particle, and by the latency of the chain cell ->
+// threshold -> id -> key -> record, so a thread takes eight particles at a time where
+// the grid's blocks all find a chunk that long, and four below.  70 us on a 65,536-cell
+// line of 600 per cell, 109 us on eight lines of 32,768, 12 us on one of 9,973 (81, 134
+// and 12 us by fours, 72, 112 and 15 us by eights; 88, 137 and 13.5 us by fours with one
+// load a particle).  Eight wavefronts per SIMD: with one less 77 and 119 us.
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k_annih_gather(AnnihArgs a) {
+    if (a.sc->err != 0) return;
+    // a copy of the over-limit flag for k_field, which clears [1] for the next step
+    // while its other blocks still need to know
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.ann_ctl[2] = a.ann_ctl[1];
+    if (a.ann_ctl[1] == 0) return;
+    if ((int64_t)a.sc->tiles * a.tile >= (int64_t)gridDim.x * 256 * 8) annih_gather<8>(a);
+    else annih_gather<4>(a);
 }
 
 // Segment of a tile by the whole wavefront: 64-way search over the tile prefix (the

@@ -83,3 +83,28 @@ def test_equal_high_key_words():
     _place(sim, 0, np.full(50, 4), np.concatenate([rest[:20], ids[pair], rest[20:]]))
     _place(sim, 1, np.full(50, 4), np.arange(700000, 700050, dtype=np.uint64))
     _check(cfg, sim, 1)
+
+
+@pytest.mark.parametrize("per_cell", [37, 1390, 1401])
+def test_gather_at_either_pass_length(per_cell):
+    # the gather takes four particles a thread, or eight from 8,388,608 particles on (256 CUs); ragged
+    # segments, every cell over the limit: the k pairs of the smallest keys go
+    _print("gather", per_cell)
+    cells, k = 3000, 3
+    n = cells * per_cell
+    cfg = workloads.small(n_cells=cells, ppc=1, init="empty", rics="off", j_twist=0.0, pairs=False,
+                          nmax_over_n0=2 * per_cell - 2 * k, capacity=[n + 64, n + 64, 256, 256])
+    sim = Pic1D(cfg)
+    ids = [np.arange(n, dtype=np.uint64) * np.uint64(5) + np.uint64(s + 1) for s in (0, 1)]
+    cell = np.repeat(np.arange(cells, dtype=np.int32), per_cell)
+    for s in (0, 1):
+        _place(sim, s, cell, ids[s])
+    sim.step(1)
+    for s in (0, 1):
+        keys = _keys(cfg, ids[s]).reshape(cells, per_cell)
+        gone = np.argsort(keys, axis=1)[:, :k] + per_cell * np.arange(cells)[:, None]
+        want = np.delete(ids[s], gone.ravel())
+        got = sim.get_particles(0, s)["id"]
+        np.testing.assert_array_equal(np.sort(got), want)
+    assert sim.moments(0)["counters"]["annihilated"] == k * cells
+    sim.close()
