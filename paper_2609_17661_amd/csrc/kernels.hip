@@ -656,7 +656,7 @@ __device__ __forceinline__ void wave_sync() {
 // (k_cell_records, the field's neighbours in one), a table lookup one gather, the
 // Philox keys are formed where they are used, and a run's sums go to the window as they
 // are.  2.7e7 heated particles on 65,536 cells: 244 -> 225 us; 4e7 at the density limit
-// 433 -> 394; the cascade lines 644 -> 581; 40 uneven lines 736 -> 706 (against eight
+// 433 -> 389; the cascade lines 644 -> 581; 40 uneven lines 736 -> 696 (against eight
 // loads and the rows in float64 at every change of cell, and two gathers).
 template <int BACKEND, int PPT, int WW, int KIND, int SUB>
 __global__ __launch_bounds__(BACKEND == RICS_MLP ? PUSH_TPB_MLP : PUSH_TPB)
@@ -885,7 +885,9 @@ __attribute__((amdgpu_waves_per_eu(push_waves(BACKEND)))) void k_push(PushArgs a
         // flush the lowest `ncells` cells of the run's three (all of them, or only
         // key-1 when the next run starts in key+1 and the other two carry over).  The
         // window holds the sums unsigned and unshifted and has room for the cells beyond
-        // the walls, so that nothing is tested or converted here
+        // the walls, so that no bounds are tested and nothing is converted here; an outer
+        // cell of a whole run that got nothing is skipped (not so 709 us on 40 uneven lines
+        // and 394 on the line at the density limit instead of 696 and 389)
         auto flush_run = [&](int ncells) {
             const int jv[3] = {jv0, jv1, jv2};
             if (use_lds) {
@@ -895,8 +897,10 @@ __attribute__((amdgpu_waves_per_eu(push_waves(BACKEND)))) void k_push(PushArgs a
 #pragma unroll
                     for (int r = 0; r < 3; ++r) {
                         if (r >= ncells) continue;
+                        const int hv = (hc >> (10 * r)) & 1023;
+                        if (ncells == 3 && r != 1 && (jv[r] | hv) == 0) continue;
                         atomicAdd(wj + r, (unsigned long long)(long long)jv[r]);
-                        atomicAdd(wh + r, (hc >> (10 * r)) & 1023);
+                        atomicAdd(wh + r, hv);
                     }
                 }
                 return;
