@@ -370,16 +370,16 @@ void prof_collect(pic1d_state* st) {
 
 // Parts of the default tile that the wavefronts take separately (0: whole tiles).  Few
 // tiles leave the chip idle while each wavefront works through its eight particles per
-// lane, so the parts follow the last read-back number of tiles against the wavefronts
-// the chip holds (20 per CU): four up to half of them, two up to twice as many.
-// TABLE, us a launch with whole, half and quarter tiles: 35 / 23 / 18 at 124 tiles,
-// 42 / 31 / 30 at 1,863, 50 / 42 / 43 at 3,829, 70 / 64 / 70 at 7,846, 114 / 114 / 128 at
-// 16,023.  A shape set through pic1d_set_push_shape stays as it was set.
+// lane, so the parts follow the last read-back number of tiles per CU: four up to 3, two
+// up to 64.  TABLE, us a launch with whole, half and quarter tiles: 31 / 20 / 18 at 124
+// tiles, 24 / 17 / 16 at 593, 32 / 24 / 25 at 902, 36 / 28 / 29 at 1,863, 43 / 38 / 40 at
+// 3,829, 63 / 56 / 63 at 7,846, 103 / 99 / 116 at 16,023; EXACT 30 / 23 / 23 at 901,
+// 58 / 52 / 59 at 7,849, 96 / 92 / 103 at 16,018.  A shape set through
+// pic1d_set_push_shape stays as it was set.
 int push_parts(const pic1d_state* st) {
     if (st->shape_set || st->backend == RICS_MLP || st->ppt != PUSH_PPT_DEFAULT || st->ww != default_window(st->backend))
         return 0;
-    const int waves = 20 * st->n_cu;
-    return 2 * st->tiles <= waves ? 4 : st->tiles <= 2 * waves ? 2 : 0;
+    return st->tiles <= 3 * st->n_cu ? 4 : st->tiles <= 64 * st->n_cu ? 2 : 0;
 }
 
 int launch_push(pic1d_state* st) {

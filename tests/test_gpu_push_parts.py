@@ -18,11 +18,12 @@ def _moments(sim):
 @pytest.mark.parametrize("rics,cells,ppc,graph", [
     ("table", 3, 1, 0),            # one item, nearly empty
     ("exact", 64, 40, 0),          # a few tiles: quarters
-    ("off", 700, 200, 3),          # quarters from graphs
+    ("off", 700, 200, 3),          # 547: quarters from graphs
     ("table", 3000, 300, 0),       # 3,516 tiles: halves
     ("exact", 3000, 300, 3),
     ("off", 3000, 300, 0),
-    ("table", 9000, 300, 0),       # 10,547: whole tiles of themselves
+    ("table", 9000, 300, 0),       # 10,547
+    ("off", 15000, 300, 0),        # 17,579: whole tiles of themselves
 ])
 def test_parts_of_tiles_give_the_same_results(rics, cells, ppc, graph):
     print("parts", rics, cells, ppc, graph, flush=True)
