@@ -412,6 +412,7 @@ int launch_plan(pic1d_state* st, int advance, const int32_t* new_count = nullptr
     const int pk = prof_begin(st, 3);
     BookArgs b = book_args(st);
     b.new_count = new_count;
+    b.live = st->cur;
     hipLaunchKernelGGL(k_plan, dim3(1), dim3(256), 0, st->stream, b, advance);
     prof_end(st, pk);
     return PIC1D_OK;
@@ -468,6 +469,10 @@ int check_error(pic1d_state* st) {
     if (int rc = read_scalars(st, h)) return rc;
     if (h.err != 0) {
         st->frozen = h.err;
+        // the kernels queued behind the error left at once, sorts among them: the particles
+        // are where the last sort before it put them, at the step that was not completed
+        st->cur = h.live;
+        st->host_step = h.step;
         return fail(st, h.err, h.err == PIC1D_ECAPACITY   ? "particle capacity exceeded (state frozen)"
                                : h.err == PIC1D_ENONFINITE ? "non-finite momentum (state frozen)"
                                                            : "cell counts and particles disagree (state frozen)");

@@ -131,7 +131,8 @@ struct BookArgs {
     int32_t* alloc;
     const int32_t* seg_cap;
     int32_t* tile_prefix;
-    const int32_t* new_count;  // after a sort: its live counts (null otherwise)
+    const int32_t* new_count;  // after a sort: its live counts (null otherwise) ...
+    int32_t live;              // ... and the buffer set it wrote
     int32_t nseg;
     int32_t tile;              // particles per tile (64 ppt)
     DevScalars* sc;

@@ -1381,6 +1381,7 @@ __device__ void bookkeeping(const BookArgs& b) {
     if (threadIdx.x == 255) {
         b.tile_prefix[nseg] = total;
         b.sc->tiles = total;
+        if (b.new_count) b.sc->live = b.live;
     }
 }
 

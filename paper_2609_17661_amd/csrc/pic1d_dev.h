@@ -74,6 +74,8 @@ struct DevScalars {
     int32_t err;          // first error code (pic1d_status), 0 if none
     int32_t tiles;        // tiles of the planned push (read back with the error word)
     uint64_t step_field;  // the running step, as k_field reads it (k_field advances `step`)
+    int32_t live;         // the buffer set that holds the particles (a sort that took place moves them)
+    int32_t pad;
 };
 
 // ---------------------------------------------------------------------------
