@@ -28,7 +28,8 @@ constexpr int SORT_PASSES = 8;                  // windows of SORT_W bins at mos
 constexpr int GATHER_BLOCKS_PER_CU = 16;        // blocks of the annihilation gather per CU
 
 constexpr int PHOTON_REPL = 256;                // append regions of the photon buffer (one per wavefront
-                                                // slot of a block and block mod 64: spreads the reservations)
+                                                // slot of a block and block mod 64, or work item of the
+                                                // network's pusher: spreads the reservations)
 
 // A photon above the pair threshold, recorded by the pusher for the conversion kernel.
 struct PhotonRec {

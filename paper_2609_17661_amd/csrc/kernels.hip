@@ -231,6 +231,7 @@ struct TileCtx {
     float inv_mass;             // m_e / m
     bool negative;              // negative charge
     bool gravity;               // the tile touches an atmosphere layer
+    int item;                   // work item (the queue of the network's pusher)
 };
 
 // Append one particle to a segment; returns false (and flags ECAPACITY) if full.
@@ -259,6 +260,11 @@ struct Counts {
 // emits eps = gamma (1 - (1+2b)^-1/2) and leaves gamma / (1+2b)^1/2 (Appendix A), or,
 // with an angular emission pattern, the photon leaves the excited lepton's rest frame
 // at the cosine drawn from the block's other words.
+// Append regions fill by the wavefront's slot where each wavefront walks fixed tiles; from
+// the queue, which hands items out by timing, by the item, so that whether a region overflows
+// follows from the state alone: consecutive items go to regions of their own, and (the
+// second term) so do the same items of lines a multiple of 256 items long.
+template <bool QUEUE>
 __device__ __forceinline__ float stochastic_step(const PushArgs& a, const LineDev& L, const TileCtx& T, int line,
                                               int64_t k, int c0, float o0, float u, const Geo& g, float ndot,
                                               Counts& cnt) {
@@ -291,7 +297,8 @@ __device__ __forceinline__ float stochastic_step(const PushArgs& a, const LineDe
         const unsigned long long m = __ballot(1);
         const int lane = threadIdx.x & 63;
         const int leader = __ffsll((long long)m) - 1;
-        const int r = (int)((blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) & (PHOTON_REPL - 1));
+        const int r = QUEUE ? (T.item ^ (T.item >> 8)) & (PHOTON_REPL - 1)
+                            : (int)((blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) & (PHOTON_REPL - 1));
         int slot0 = 0;
         if (lane == leader) slot0 = atomicAdd(&a.n_photons[r], __popcll(m));
         const int slot = __shfl(slot0, leader, 64) + __popcll(m & ((1ull << lane) - 1ull));
@@ -516,7 +523,7 @@ __device__ __forceinline__ void advance_particle(const PushArgs& a, const LineDe
             u += kick;
             const MlpRics rb = mlp_rics(a, W, Wb, u, g, sl, cnt.mlp);
             if (any_cont) u = mlp_drag_half(a, W, Wb, L, u, rb.F, g, sl, pt, cont, alive, cnt);
-            if (!cont && alive) u = stochastic_step(a, L, T, line, k, c0, o0, u, g, rb.N, cnt);
+            if (!cont && alive) u = stochastic_step<true>(a, L, T, line, k, c0, o0, u, g, rb.N, cnt);
         } else {
             u += kick;
         }
@@ -543,7 +550,7 @@ __device__ __forceinline__ void advance_particle(const PushArgs& a, const LineDe
             u = drag_half<BACKEND>(a, L, u, pg, pt, alive, cnt.limited, cnt.newton);
         } else {
             u += kick;
-            if (alive) u = stochastic_step(a, L, T, line, k, c0, o0, u, pg.g, rics_N<BACKEND>(a, L, u, pg), cnt);
+            if (alive) u = stochastic_step<false>(a, L, T, line, k, c0, o0, u, pg.g, rics_N<BACKEND>(a, L, u, pg), cnt);
         }
         if constexpr (BACKEND == RICS_TABLE) cc.memo = pg.memo;
     } else {
@@ -868,6 +875,7 @@ __attribute__((amdgpu_waves_per_eu(push_waves(BACKEND)))) void k_push(PushArgs a
 
         TileCtx T;
         T.step = step;
+        T.item = ww.t;
         T.hist_in = hist_in;
         T.hist_out = hist_out;
         T.negative = (sp == 0 || sp == 2);
