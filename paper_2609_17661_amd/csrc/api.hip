@@ -1138,7 +1138,7 @@ int pic1d_moments(pic1d_state* st, int32_t line, int32_t flags, pic1d_moments_ou
     for (int k = 0; k < 4; ++k) m.sign[k] = sign[k];
     m.mass_ratio = st->cfg.mass_ratio;
     int64_t chunks = 0;
-    for (int k = 0; k < 4; ++k) chunks += (st->seg_cap_h[4 * line + k] + 256 * MOM_U - 1) / (256 * MOM_U);
+    for (int k = 0; k < 4; ++k) chunks += tiles_of(st->seg_cap_h[4 * line + k], 256 * MOM_U);
     const int part_blocks = (int)std::max<int64_t>(1, std::min<int64_t>(MOM_PART_BLOCKS, chunks));
     const int grid_blocks = std::max(1, std::min(MOM_GRID_BLOCKS, (n + 256) / 256));
     hipLaunchKernelGGL(k_moments_particles, dim3(part_blocks), dim3(256), 0, s, m);

@@ -1225,8 +1225,8 @@ __device__ __forceinline__ void convert_photons(const ConvertArgs& a, int blk, i
             if (threadIdx.x == 64) s_base[1] = nconv > 0 ? atomicAdd(&a.alloc[4 * gl + 1], nconv) : 0;
             __syncthreads();
             const int base_e = s_base[0] + before, base_p = s_base[1] + before;
-            const bool fits = (int64_t)s_base[0] + nconv <= a.seg_cap[4 * gl + 0] &&
-                              (int64_t)s_base[1] + nconv <= a.seg_cap[4 * gl + 1];
+            const bool fits = slots_in(s_base[0], nconv, a.seg_cap[4 * gl + 0]) &&
+                              slots_in(s_base[1], nconv, a.seg_cap[4 * gl + 1]);
             __syncthreads();
             int made = 0, j = 0;
 #pragma unroll
@@ -1235,7 +1235,7 @@ __device__ __forceinline__ void convert_photons(const ConvertArgs& a, int blk, i
                 if (rec[k].convert) {
                     const int se = base_e + j, spp = base_p + j;
                     ++j;
-                    const bool e_ok = se < a.seg_cap[4 * gl + 0], p_ok = spp < a.seg_cap[4 * gl + 1];
+                    const bool e_ok = slot_in(se, a.seg_cap[4 * gl + 0]), p_ok = slot_in(spp, a.seg_cap[4 * gl + 1]);
                     if (!e_ok || !p_ok) set_error(&a.sc->err, -3);
                     const uint4 wc = philox4x32_10(make_uint4((uint32_t)step, (uint32_t)rec[k].pid,
                                                               (uint32_t)(rec[k].pid >> 32), STREAM_CHILD),
@@ -1300,7 +1300,7 @@ __device__ __forceinline__ void refill_atmosphere(const AtmArgs& a, int blk, int
         }
         baseE = __shfl(baseE, 0, 64);
         baseI = __shfl(baseI, 0, 64);
-        if (baseE + D > a.seg_cap[segE] || baseI + D > a.seg_cap[segI]) {
+        if (!slots_in(baseE, D, a.seg_cap[segE]) || !slots_in(baseI, D, a.seg_cap[segI])) {
             if (lane == 0) set_error(&a.sc->err, -3);
             continue;
         }
@@ -1377,14 +1377,14 @@ __device__ void bookkeeping(const BookArgs& b) {
         b.n_cur[s] = n;
         b.alloc[s] = n;
         n_last = n;
-        sum += (n + b.tile - 1) / b.tile;
+        sum += tiles_of(n, b.tile);
     }
     int total;
     int run = block_excl_scan(sum, total);
     for (int s = s0; s < s1; ++s) {
         b.tile_prefix[s] = run;
         // (one segment per thread up to 256 segments: its count is still in a register)
-        run += ((per == 1 ? n_last : b.n_cur[s]) + b.tile - 1) / b.tile;
+        run += tiles_of(per == 1 ? n_last : b.n_cur[s], b.tile);
     }
     if (threadIdx.x == 255) {
         b.tile_prefix[nseg] = total;
@@ -2018,12 +2018,12 @@ __global__ __launch_bounds__(256) void k_sort_zero(SortArgs s) {
         const int per = (s.nseg + 255) / 256;
         const int s0 = threadIdx.x * per, s1 = min(s0 + per, s.nseg);
         int sum = 0;
-        for (int k = s0; k < s1; ++k) sum += (s.n_cur[k] + SORT_TILE - 1) / SORT_TILE;
+        for (int k = s0; k < s1; ++k) sum += tiles_of(s.n_cur[k], SORT_TILE);
         int total;
         int run = block_excl_scan(sum, total);
         for (int k = s0; k < s1; ++k) {
             s.sort_prefix[k] = run;
-            run += (s.n_cur[k] + SORT_TILE - 1) / SORT_TILE;
+            run += tiles_of(s.n_cur[k], SORT_TILE);
         }
         if (threadIdx.x == 255) s.sort_prefix[s.nseg] = total;
         return;

@@ -17,6 +17,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "slots.h"
+
 namespace pic1d {
 
 constexpr int32_t DEAD_CELL = INT32_MIN;
