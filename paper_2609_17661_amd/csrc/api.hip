@@ -433,7 +433,7 @@ int launch_sort(pic1d_state* st) {
     const int b = st->cur, o = 1 - st->cur;
     s.cell = st->cell[b]; s.off = st->off[b]; s.u = st->u[b]; s.id = st->id[b];
     s.cell2 = st->cell[o]; s.off2 = st->off[o]; s.u2 = st->u[o]; s.id2 = st->id[o];
-    s.seg_base = st->seg_base; s.n_cur = st->n_cur; s.sort_prefix = st->sort_prefix;
+    s.seg_base = st->seg_base; s.seg_cap = st->seg_cap; s.n_cur = st->n_cur; s.sort_prefix = st->sort_prefix;
     s.nseg = st->lay.nseg; s.lines = st->dlines;
     s.bins = st->bins; s.chunk_sum = st->chunk_sum; s.chunk_line = st->chunk_line; s.line_chunk0 = st->line_chunk0;
     s.n_chunks = st->lay.n_chunks; s.n_bins = st->sort_sub * st->lay.n_cells; s.sub = st->sort_sub;

@@ -207,6 +207,7 @@ struct SortArgs {
     float* u2;
     uint64_t* id2;
     const int64_t* seg_base;
+    const int32_t* seg_cap;
     const int32_t* n_cur;
     int32_t* sort_prefix;      // [nseg + 1]: first tile of SORT_TILE slots of each segment
     int32_t nseg;

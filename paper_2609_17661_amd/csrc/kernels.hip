@@ -50,6 +50,16 @@ __device__ __forceinline__ auto kconst(const T* p) {
 #endif
 }
 
+// Whether an earlier error stops the kernel, the same answer for the whole block: a kernel
+// that may set the error word itself, and whose wavefronts wait for each other, must not
+// lose some of them to it.
+__device__ __forceinline__ bool block_stopped(const DevScalars* sc) {
+    __shared__ int s_err;
+    if (threadIdx.x == 0) s_err = sc->err;
+    __syncthreads();
+    return s_err != 0;
+}
+
 // Segment of a global tile index by binary search over the tile prefix.
 template <typename P>
 __device__ __forceinline__ int find_segment(P prefix, int nseg, int t) {
@@ -2040,13 +2050,14 @@ __global__ __launch_bounds__(256) void k_sort_zero(SortArgs s) {
 // pushes of a quiet line 4% slower: 757 against 726 us on 40 lines).  The count, which
 // leaves no order, takes four per lane: its LDS atomics then meet in fewer bins.
 struct SortTile {
-    int sp, ncur, i0;
+    int sp, ncur, i0, cap;
     int64_t base;
     const LineDev* L;
     __device__ SortTile(const SortArgs& s, int t) {
         const int seg = find_segment_wave(s.sort_prefix, s.nseg, t);
         sp = seg & 3;
         ncur = s.n_cur[seg];
+        cap = s.seg_cap[seg];
         base = s.seg_base[seg];
         i0 = (t - s.sort_prefix[seg]) * SORT_TILE;
         L = &s.lines[seg >> 2];
@@ -2281,7 +2292,7 @@ __device__ __forceinline__ int tile_scan(int v, int& total, int* s_part) {
 // 4,096 is the largest of which two fit a CU's LDS: the longer a bin's run, the fewer
 // lines a store touches.
 __global__ __launch_bounds__(SORT_TPB) __attribute__((amdgpu_waves_per_eu(4))) void k_sort_scatter(SortArgs s) {
-    if (s.sc->err != 0) return;
+    if (block_stopped(s.sc)) return;
     // the windows of the ranking, and after it the tile's particles in bin order
     __shared__ union {
         struct { int cnt[SORT_W], excl[SORT_W], base[SORT_W]; } w;
@@ -2294,6 +2305,14 @@ __global__ __launch_bounds__(SORT_TPB) __attribute__((amdgpu_waves_per_eu(4))) v
     const int total = s.sort_prefix[s.nseg];
     constexpr int BPT = SORT_W / SORT_TPB;        // bins per thread of the window's scan
     static_assert(BPT == 4, "the scan reads one int4 of counts per thread");
+    // Counts and particles that disagree would run into the next segment: such a run goes to
+    // the segment's start and the state freezes, with its particles in the set they come from.
+    bool overrun = false;
+    auto checked = [&](int at, int n, int cap) {
+        const bool in = slots_in(at, n, cap);
+        overrun = overrun || !in;
+        return in ? at : 0;
+    };
     for (TileWalk tw(total); tw.t < tw.end; tw.t += tw.stride) {
         const SortTile T(s, tw.t);
         const int cb = T.L->cell_base;
@@ -2323,7 +2342,7 @@ __global__ __launch_bounds__(SORT_TPB) __attribute__((amdgpu_waves_per_eu(4))) v
 #pragma unroll
             for (int q = 0; q < SORT_U; ++q) {
                 if (bin[q] < 0) continue;
-                const int64_t k = T.base + atomicAdd(&bins[4 * (size_t)bin[q] + T.sp], 1);
+                const int64_t k = T.base + checked(atomicAdd(&bins[4 * (size_t)bin[q] + T.sp], 1), 1, T.cap);
                 s.cell2[k] = cv[q];
                 s.off2[k] = ov[q];
                 s.u2[k] = uv[q];
@@ -2351,7 +2370,7 @@ __global__ __launch_bounds__(SORT_TPB) __attribute__((amdgpu_waves_per_eu(4))) v
             const int nbin = min(SORT_W, hi - w0 + 1);
             for (int b = threadIdx.x; b < nbin; b += SORT_TPB) {
                 const int c = sh.w.cnt[b];
-                if (c != 0) sh.w.base[b] = atomicAdd(&bins[4 * (size_t)(w0 + b) + T.sp], c);
+                if (c != 0) sh.w.base[b] = checked(atomicAdd(&bins[4 * (size_t)(w0 + b) + T.sp], c), c, T.cap);
             }
             __syncthreads();
 #pragma unroll
@@ -2388,6 +2407,7 @@ __global__ __launch_bounds__(SORT_TPB) __attribute__((amdgpu_waves_per_eu(4))) v
         for (int i = threadIdx.x; i < live; i += SORT_TPB) s.id2[T.base + sDst[i]] = sh.id[i];
         __syncthreads();
     }
+    if (overrun) set_error(&s.sc->err, -3);
 }
 
 // ---------------------------------------------------------------------------
