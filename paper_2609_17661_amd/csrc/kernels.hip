@@ -1341,7 +1341,7 @@ __device__ __forceinline__ void refill_atmosphere(const AtmArgs& a, int blk, int
 // and 3).  The two touch different segments and different species counts, so they
 // run side by side.
 __global__ __launch_bounds__(256) void k_append(ConvertArgs ca, AtmArgs aa, int conv_blocks) {
-    if (ca.sc->err != 0) return;
+    if (block_stopped(ca.sc)) return;
     if ((int)blockIdx.x < conv_blocks) convert_photons(ca, blockIdx.x, conv_blocks);
     else refill_atmosphere(aa, blockIdx.x - conv_blocks, gridDim.x - conv_blocks);
 }
@@ -1373,9 +1373,10 @@ __device__ __forceinline__ int block_excl_scan(int v, int& total) {
 // ---------------------------------------------------------------------------
 // Per-step bookkeeping shared by k_field and k_plan: live counts <- allocation
 // counters (after a sort, its counts; clamped to capacity), tile plan of the next push.
+// Nothing (false) after an error.
 // ---------------------------------------------------------------------------
-__device__ void bookkeeping(const BookArgs& b) {
-    if (b.sc->err != 0) return;
+__device__ bool bookkeeping(const BookArgs& b) {
+    if (block_stopped(b.sc)) return false;
     if (b.n_photons && threadIdx.x < PHOTON_REPL) b.n_photons[threadIdx.x] = 0;
     if (threadIdx.x == 0) b.queue[0] = 0;
     const int nseg = b.nseg;
@@ -1401,6 +1402,7 @@ __device__ void bookkeeping(const BookArgs& b) {
         b.sc->tiles = total;
         if (b.new_count) b.sc->live = b.live;
     }
+    return true;
 }
 
 // Bookkeeping kernel of every step (and after init, sort, set_particles): one block.
@@ -1440,7 +1442,7 @@ __device__ __forceinline__ uint32_t annih_threshold(int k, int m) {
 // run of candidate records (room for all their e- then their e+), one allocation
 // per block.
 __global__ __launch_bounds__(256) void k_annih_plan(AnnihArgs a) {
-    if (a.sc->err != 0) return;
+    if (block_stopped(a.sc)) return;
     const uint64_t step = a.sc->step;
     const int32_t* hist_out = a.hist[(step & 1) ^ 1];
     __shared__ int s_base;
@@ -1785,7 +1787,9 @@ __device__ long long annihilate_cell(const AnnihArgs& a, const AnnihCell& c, uin
 // the step's bookkeeping (live counts, the next push's tile plan) and advances the
 // step counter; the cells read the running step from the copy the push left.
 __global__ __launch_bounds__(256) void k_field(FieldArgs f, BookArgs b) {
-    if (f.sc->err != 0) return;
+    const int nb = gridDim.x - 1;
+    // (the last block asks for itself, all its wavefronts together)
+    if ((int)blockIdx.x != nb && f.sc->err != 0) return;
     const uint64_t step = f.sc->step_field;
     const int n = f.n_total;
     const int hin = (int)(step & 1);
@@ -1794,9 +1798,8 @@ __global__ __launch_bounds__(256) void k_field(FieldArgs f, BookArgs b) {
     const bool averaging = f.avg_start >= 0 && step >= (uint64_t)f.avg_start;
     // the last block plans the next push and advances the step counter, beside the
     // cells' blocks rather than before one of them (none of them reads what it writes)
-    const int nb = gridDim.x - 1;
     if ((int)blockIdx.x == nb) {
-        bookkeeping(b);
+        if (!bookkeeping(b)) return;
         if (threadIdx.x == 0) {
             if (b.sc->err == 0) b.sc->step += 1;
             if (f.annihilation) {

@@ -15,7 +15,8 @@ def _sim(rics="exact"):
     # a hot line whose cascade outgrows its segments; one crowded cell annihilates in every step, so
     # that the other buffer set holds candidate records
     cfg = workloads.small(n_cells=CELLS, ppc=PPC, rics=rics, gamma_max=1e4, pairs=True, conversion="immediate",
-                          nmax_over_n0=8.0, sort_interval=1, capacity=[3 * CELLS * PPC, 3 * CELLS * PPC, 0, 0])
+                          nmax_over_n0=8.0, sort_interval=1, avg_start_step=0,
+                          capacity=[3 * CELLS * PPC, 3 * CELLS * PPC, 0, 0])
     sim = Pic1D(cfg)
     for s in (0, 1):
         p = sim.get_particles(0, s)
@@ -77,6 +78,7 @@ def test_particles_after_an_error_in_a_long_call(rics, ahead, graph):
     a, b = _particles(one), _particles(many)
     m = many.moments(0)
     assert m["step"] == k and one.moments(0)["step"] == k
+    assert m["avg_steps"] == k and one.moments(0, average=True)["avg_steps"] == k
     for s in (0, 1):
         print("species", s, "step", k, "live", a[s]["id"].size, b[s]["id"].size, m["count"][s], flush=True)
         for p in (a[s], b[s]):
