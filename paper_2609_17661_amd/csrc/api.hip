@@ -86,6 +86,7 @@ struct pic1d_state {
     float4* cell_rec = nullptr;
     float2* table = nullptr;
     int32_t *ann_k = nullptr, *ann_off = nullptr, *ann_fill = nullptr, *ann_ctl = nullptr;
+    uint32_t* ann_tags = nullptr;
     uint32_t* ann_thr = nullptr;
     int32_t *layer_cell = nullptr, *layer_line = nullptr, *layer_target = nullptr;
     unsigned long long* counters = nullptr;
@@ -250,6 +251,7 @@ void carve(Carver& cv, const Layout& L, pic1d_state* st) {
     s->ann_thr = cv.take<uint32_t>(L.n_cells);
     s->ann_fill = cv.take<int32_t>(2 * (size_t)L.n_cells);
     s->ann_ctl = cv.take<int32_t>(4);
+    s->ann_tags = cv.take<uint32_t>(32 * ANN_TAGS);
     s->layer_cell = cv.take<int32_t>(std::max(L.n_layer, 1));
     s->layer_line = cv.take<int32_t>(std::max(L.n_layer, 1));
     s->layer_target = cv.take<int32_t>(std::max(L.n_layer, 1));
@@ -776,6 +778,7 @@ int enqueue_step(pic1d_state* st) {
             an.cell_line = st->cell_line; an.lines = st->dlines;
             an.n_total = nt; an.n_lines = st->lay.n_lines; an.tile = 64 * st->ppt;
             an.ann_k = st->ann_k; an.ann_off = st->ann_off; an.ann_thr = st->ann_thr; an.ann_fill = st->ann_fill; an.ann_ctl = st->ann_ctl;
+            an.ann_tags = st->ann_tags;
             // candidate records in the other particle buffer set (written only by the sort)
             an.cand_key = st->id[1 - b];
             an.cand_slot = st->cell[1 - b];
@@ -790,15 +793,17 @@ int enqueue_step(pic1d_state* st) {
             hipLaunchKernelGGL(k_annih_gather, dim3(GATHER_BLOCKS_PER_CU * st->n_cu), dim3(256), 0, st->stream, an);
             prof_end(st, pk);
         }
-        // Ampere; its last block plans the next push and advances the step counter
+        // Ampere; its first block plans the next push and advances the step counter
         const int pk = prof_begin(st, 2);
         // 64 cells per wavefront; with annihilation 4, or 1 up to 64 cells per CU in all:
         // there four selections one after another leave the chip idle (9,973 cells: k_field
         // 48 us at 4, 24 us at 1), beyond it the extra blocks of the quiet steps cost more
         const int field_cells = !f.annihilation ? 256 : nt <= 64 * st->n_cu ? 4 : 16;
         // (and one more block for the bookkeeping)
+        BookArgs bk = book_args(st);
+        if (f.annihilation) bk.ann_tags = st->ann_tags;
         hipLaunchKernelGGL(k_field, dim3(std::min(16 * st->aux_blocks, (nt + field_cells - 1) / field_cells) + 1),
-                           dim3(256), 0, st->stream, f, book_args(st));
+                           dim3(256), 0, st->stream, f, bk);
         prof_end(st, pk);
         st->host_step += 1;
         if (st->cfg.sort_interval > 0 && st->host_step % st->cfg.sort_interval == 0) {

@@ -25,6 +25,7 @@ constexpr int SORT_TILE = SORT_TPB * SORT_U;    // consecutive slots of a segmen
 constexpr int SORT_W = 2048;                    // bins of a tile ranked at a time in LDS
 constexpr int SORT_PASSES = 8;                  // windows of SORT_W bins at most; wider tiles go to the global bins
 
+constexpr int ANN_TAGS = 64;                    // replicas of the annihilation's tag sum
 constexpr int GATHER_BLOCKS_PER_CU = 16;        // blocks of the annihilation gather per CU
 
 constexpr int PHOTON_REPL = 256;                // append regions of the photon buffer (one per wavefront
@@ -134,6 +135,7 @@ struct BookArgs {
     int32_t* tile_prefix;
     const int32_t* new_count;  // after a sort: its live counts (null otherwise) ...
     int32_t live;              // ... and the buffer set it wrote
+    const uint32_t* ann_tags;  // after an annihilation: its tag sums (null otherwise)
     int32_t nseg;
     int32_t tile;              // particles per tile (64 ppt)
     DevScalars* sc;
@@ -162,6 +164,8 @@ struct AnnihArgs {
     int32_t* ann_off;           // per global cell: first candidate record (e- then e+)
     uint32_t* ann_thr;          // per global cell: largest high key word recorded, 0 if none
     int32_t* ann_fill;          // per global cell and species 0/1: candidates recorded
+    uint32_t* ann_tags;         // ANN_TAGS replicas, 128 bytes apart: the tags of the particles in the cells over
+                                //   the limit less those of their counts; they sum to zero
     int32_t* ann_ctl;           // [0] records allocated, [1] cells over the limit (this step),
                                 //   [2] its copy for the field kernel
     uint64_t* cand_key;         // candidate records: ranking key ...

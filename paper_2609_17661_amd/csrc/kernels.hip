@@ -38,6 +38,19 @@ __device__ __forceinline__ int wave_sum_i(int v) {
     return v;
 }
 
+// The sum over a wavefront, in its last lane, by register moves between lanes (a tenth of
+// the latency of the shuffles).
+__device__ __forceinline__ uint32_t wave_sum_last(uint32_t v) {
+    int x = (int)v;
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, true);     // row_shr 1, 2, 4, 8:
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, true);     //   sums over rows of 16
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, true);     //   in their last lanes
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, true);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);    // row_bcast 15 into rows 1 and 3
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);    // row_bcast 31 into rows 2 and 3
+    return (uint32_t)x;
+}
+
 // Data that the running kernel never writes (segment tables, line constants),
 // read at a wave-uniform index: through the constant address space the compiler
 // issues scalar loads into SGPRs instead of holding the values in VGPRs.
@@ -1376,7 +1389,19 @@ __device__ __forceinline__ int block_excl_scan(int v, int& total) {
 // Nothing (false) after an error.
 // ---------------------------------------------------------------------------
 __device__ bool bookkeeping(const BookArgs& b) {
+    // did the annihilation find the particles in the cells over the limit that are counted
+    // there?  (asked by the second wavefront while the first reads the error word)
+    __shared__ uint32_t s_differ;
+    if (threadIdx.x >= 64 && threadIdx.x < 128) {
+        const int lane = threadIdx.x & 63;
+        const uint32_t sum = wave_sum_last(b.ann_tags && lane < ANN_TAGS ? b.ann_tags[32 * lane] : 0u);
+        if (lane == 63) s_differ = sum;
+    }
     if (block_stopped(b.sc)) return false;
+    if (s_differ != 0u) {
+        if (threadIdx.x == 0) set_error(&b.sc->err, -4);
+        return false;
+    }
     if (b.n_photons && threadIdx.x < PHOTON_REPL) b.n_photons[threadIdx.x] = 0;
     if (threadIdx.x == 0) b.queue[0] = 0;
     const int nseg = b.nseg;
@@ -1438,6 +1463,14 @@ __device__ __forceinline__ uint32_t annih_threshold(int k, int m) {
     return lam < (float)m ? (uint32_t)(lam / (float)m * 4294967040.0f) : 0xffffffffu;
 }
 
+// Adds a wavefront's tags (see cell_tag) to their sum.
+__device__ __forceinline__ void add_tags(uint32_t* tags, uint32_t v) {
+    if (__ballot(v != 0u) == 0ull) return;
+    const uint32_t sum = wave_sum_last(v);
+    if ((threadIdx.x & 63) == 63 && sum != 0u)
+        atomicAdd(&tags[32 * ((blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) % ANN_TAGS)], sum);
+}
+
 // Every cell's k from its end-of-step counts, and for the cells over the limit a
 // run of candidate records (room for all their e- then their e+), one allocation
 // per block.
@@ -1480,6 +1513,8 @@ __global__ __launch_bounds__(256) void k_annih_plan(AnnihArgs a) {
             a.ann_k[g] = k;
             a.ann_thr[g] = k > 0 ? annih_threshold(k, min(h0, h1)) : 0u;
         }
+        if (total > 0)
+            add_tags(a.ann_tags, k > 0 ? 0u - (uint32_t)h0 * cell_tag(g, 0) - (uint32_t)h1 * cell_tag(g, 1) : 0u);
         __syncthreads();
     }
 }
@@ -1787,18 +1822,20 @@ __device__ long long annihilate_cell(const AnnihArgs& a, const AnnihCell& c, uin
 // the step's bookkeeping (live counts, the next push's tile plan) and advances the
 // step counter; the cells read the running step from the copy the push left.
 __global__ __launch_bounds__(256) void k_field(FieldArgs f, BookArgs b) {
-    const int nb = gridDim.x - 1;
-    // (the last block asks for itself, all its wavefronts together)
-    if ((int)blockIdx.x != nb && f.sc->err != 0) return;
+    const int nb = gridDim.x - 1, block = (int)blockIdx.x - 1;
+    // (the first block asks for itself, all its wavefronts together)
+    if (block >= 0 && f.sc->err != 0) return;
     const uint64_t step = f.sc->step_field;
     const int n = f.n_total;
     const int hin = (int)(step & 1);
     int* hist_in = f.hist[hin];
     int* hist_out = f.hist[hin ^ 1];
     const bool averaging = f.avg_start >= 0 && step >= (uint64_t)f.avg_start;
-    // the last block plans the next push and advances the step counter, beside the
-    // cells' blocks rather than before one of them (none of them reads what it writes)
-    if ((int)blockIdx.x == nb) {
+    // the first block plans the next push and advances the step counter, beside the
+    // cells' blocks rather than before one of them (none of them reads what it writes,
+    // but for the allocation counters, which annih_record_all clamps to the same value
+    // that they are given here)
+    if (block < 0) {
         if (!bookkeeping(b)) return;
         if (threadIdx.x == 0) {
             if (b.sc->err == 0) b.sc->step += 1;
@@ -1820,7 +1857,7 @@ __global__ __launch_bounds__(256) void k_field(FieldArgs f, BookArgs b) {
     const int wpb = blockDim.x >> 6;
     const int nw = nb * wpb;
     const int cpw = (f.annihilation && f.an.ann_ctl[2] != 0) ? max(1, min(4, (n + nw - 1) / nw)) : 64;
-    for (int gw = (blockIdx.x * wpb + wid) * cpw; gw < n; gw += nw * cpw) {
+    for (int gw = (block * wpb + wid) * cpw; gw < n; gw += nw * cpw) {
         const int g = gw + lane;
         const bool own = lane < cpw && g < n;
         long long dJ = 0;        // this lane's cell: annihilation current and pairs removed
@@ -1930,6 +1967,7 @@ __device__ __forceinline__ void annih_gather(const AnnihArgs& a) {
     constexpr int CHUNK = 256 * U;
     // the chunks of all segments are dealt to the blocks in turn
     int64_t first = blockIdx.x;                                  // this block's next chunk, from the segment's start
+    uint32_t tags = 0u;
     for (int l = 0; l < a.n_lines; ++l) {
         const int cb = a.lines[l].cell_base;
         for (int s = 0; s < 2; ++s) {
@@ -1971,6 +2009,7 @@ __device__ __forceinline__ void annih_gather(const AnnihArgs& a) {
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
                     if (tu[u] == 0u) continue;
+                    tags += cell_tag(cb + cu[u], s);
                     const uint64_t key = annih_key(step, du[u], a.key0, a.key1);
                     if ((uint32_t)(key >> 32) > tu[u]) continue;
                     const int g = cb + cu[u];
@@ -1988,6 +2027,7 @@ __device__ __forceinline__ void annih_gather(const AnnihArgs& a) {
             first -= nchunk;
         }
     }
+    add_tags(a.ann_tags, tags);
 }
 
 // Exits at once when no cell is over the limit.  Bound by HBM: 4 bytes of cell, and in a

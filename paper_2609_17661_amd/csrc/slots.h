@@ -15,4 +15,14 @@ constexpr bool slot_in(int32_t slot, int32_t cap) { return (uint32_t)slot < (uin
 // ... and whether all n slots from it do.
 constexpr bool slots_in(int32_t slot, int32_t n, int32_t cap) { return (uint32_t)slot + (uint32_t)n <= (uint32_t)cap; }
 
+// Tag of a species' cell.  The tags of the particles sum to the counts times the tags (mod
+// 2^32) if every cell holds as many particles as its count says; tags of neighbours are not
+// related, so particles counted in another cell do not cancel.
+constexpr uint32_t cell_tag(uint32_t cell, uint32_t species) {
+    uint32_t x = (4u * cell + species + 1u) * 0x9E3779B1u;
+    x ^= x >> 15;
+    x *= 0x2C1B3C6Du;
+    return x ^ (x >> 13);
+}
+
 }  // namespace pic1d
