@@ -299,7 +299,7 @@ int pic1d_profile_read(pic1d_state* st, pic1d_profile_out* out);
 /* Capture the step sequence in HIP graphs of steps_per_graph steps (rounded up
  * to a multiple of sort_interval) and replay them in pic1d_step; 0 returns to
  * eager launches.  Graphs are captured on first use (one per live particle
- * buffer set) on a private stream and replayed on the config's stream; steps
+ * buffer set and particle kernel, see pic1d_set_push_shape) on a private stream and replayed on the config's stream; steps
  * before the next multiple of the graph length, remainders and profiled steps
  * run eagerly.  The results are the same as eager stepping.
  * Errors: EINVAL. */

@@ -119,19 +119,19 @@ struct pic1d_state {
     int n_table_lines = 0;                         // MLP with table fallback: lines on their table
     int push_blocks_table = 0;                     // ... and the table kernel's blocks for them
     int graph_steps = 0;                           // requested steps per graph; 0 = eager
-    int graph_parts = 0;                           // push_parts of the captured graphs
     int graph_len = 0;                             // steps per graph (a multiple of sort_interval)
-    hipGraphExec_t gexec[2] = {nullptr, nullptr};  // by the live buffer set at the graph's start
+    hipGraphExec_t gexec[5][2] = {};               // by push_parts and the live buffer set at the graph's start
     hipStream_t cap_stream = nullptr;
     std::vector<hipEvent_t> ev_pool;
     std::vector<int> ev_kernel;     // kernel id of each recorded pair (pool index 2k, 2k+1)
     double prof_ms[8] = {0};
     int64_t prof_n[8] = {0};
     void drop_graphs() {
-        for (auto& g : gexec) {
-            if (g) (void)hipGraphExecDestroy(g);
-            g = nullptr;
-        }
+        for (auto& by_set : gexec)
+            for (auto& g : by_set) {
+                if (g) (void)hipGraphExecDestroy(g);
+                g = nullptr;
+            }
     }
     ~pic1d_state() {
         drop_graphs();
@@ -841,10 +841,11 @@ int capture_graph(pic1d_state* st) {
         return rc;
     }
     if (e != hipSuccess) return fail(st, PIC1D_EDEVICE, std::string("graph capture: ") + hipGetErrorString(e));
-    e = hipGraphInstantiate(&st->gexec[cur0], g, nullptr, nullptr, 0);
+    hipGraphExec_t& exec = st->gexec[push_parts(st)][cur0];
+    e = hipGraphInstantiate(&exec, g, nullptr, nullptr, 0);
     (void)hipGraphDestroy(g);
     if (e != hipSuccess) {
-        st->gexec[cur0] = nullptr;
+        exec = nullptr;
         return fail(st, PIC1D_EDEVICE, std::string("graph instantiate: ") + hipGetErrorString(e));
     }
     return PIC1D_OK;
@@ -868,9 +869,6 @@ int pic1d_step(pic1d_state* st, int32_t n_steps) {
     int32_t i = 0;
     const int G = st->graph_len;
     if (G > 0 && !st->prof_on) {
-        // captured graphs hold the particle kernel of their time
-        if (st->graph_parts != push_parts(st)) st->drop_graphs();
-        st->graph_parts = push_parts(st);
         // eager up to the next multiple of G, then whole graphs
         while (i < n_steps && st->host_step % (uint64_t)G != 0) {
             if (int rc = enqueue_step(st)) return rc;
@@ -879,9 +877,12 @@ int pic1d_step(pic1d_state* st, int32_t n_steps) {
         const int S = st->cfg.sort_interval;
         const int flips = S > 0 ? (G / S) & 1 : 0;
         while (n_steps - i >= G) {
-            if (!st->gexec[st->cur])
+            // a captured graph holds the particle kernel of its time: one for each number of
+            // parts, kept, so that a state that goes to and fro across a switch captures no more
+            const hipGraphExec_t& exec = st->gexec[push_parts(st)][st->cur];
+            if (!exec)
                 if (int rc = capture_graph(st)) return rc;
-            HIP_TRY(st, hipGraphLaunch(st->gexec[st->cur], st->stream));
+            HIP_TRY(st, hipGraphLaunch(exec, st->stream));
             st->host_step += (uint64_t)G;
             st->cur ^= flips;
             i += G;
