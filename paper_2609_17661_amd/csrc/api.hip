@@ -793,7 +793,7 @@ int enqueue_step(pic1d_state* st) {
             hipLaunchKernelGGL(k_annih_gather, dim3(GATHER_BLOCKS_PER_CU * st->n_cu), dim3(256), 0, st->stream, an);
             prof_end(st, pk);
         }
-        // Ampere; its first block plans the next push and advances the step counter
+        // Ampere; its last block plans the next push and advances the step counter
         const int pk = prof_begin(st, 2);
         // 64 cells per wavefront; with annihilation 4, or 1 up to 64 cells per CU in all:
         // there four selections one after another leave the chip idle (9,973 cells: k_field

@@ -1822,20 +1822,20 @@ __device__ long long annihilate_cell(const AnnihArgs& a, const AnnihCell& c, uin
 // the step's bookkeeping (live counts, the next push's tile plan) and advances the
 // step counter; the cells read the running step from the copy the push left.
 __global__ __launch_bounds__(256) void k_field(FieldArgs f, BookArgs b) {
-    const int nb = gridDim.x - 1, block = (int)blockIdx.x - 1;
-    // (the first block asks for itself, all its wavefronts together)
-    if (block >= 0 && f.sc->err != 0) return;
+    const int nb = gridDim.x - 1;
+    // (the last block asks for itself, all its wavefronts together)
+    if ((int)blockIdx.x != nb && f.sc->err != 0) return;
     const uint64_t step = f.sc->step_field;
     const int n = f.n_total;
     const int hin = (int)(step & 1);
     int* hist_in = f.hist[hin];
     int* hist_out = f.hist[hin ^ 1];
     const bool averaging = f.avg_start >= 0 && step >= (uint64_t)f.avg_start;
-    // the first block plans the next push and advances the step counter, beside the
+    // the last block plans the next push and advances the step counter, beside the
     // cells' blocks rather than before one of them (none of them reads what it writes,
     // but for the allocation counters, which annih_record_all clamps to the same value
     // that they are given here)
-    if (block < 0) {
+    if ((int)blockIdx.x == nb) {
         if (!bookkeeping(b)) return;
         if (threadIdx.x == 0) {
             if (b.sc->err == 0) b.sc->step += 1;
@@ -1857,7 +1857,7 @@ __global__ __launch_bounds__(256) void k_field(FieldArgs f, BookArgs b) {
     const int wpb = blockDim.x >> 6;
     const int nw = nb * wpb;
     const int cpw = (f.annihilation && f.an.ann_ctl[2] != 0) ? max(1, min(4, (n + nw - 1) / nw)) : 64;
-    for (int gw = (block * wpb + wid) * cpw; gw < n; gw += nw * cpw) {
+    for (int gw = (blockIdx.x * wpb + wid) * cpw; gw < n; gw += nw * cpw) {
         const int g = gw + lane;
         const bool own = lane < cpw && g < n;
         long long dJ = 0;        // this lane's cell: annihilation current and pairs removed
