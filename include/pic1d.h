@@ -215,7 +215,8 @@ int pic1d_init(const pic1d_config* cfg, pic1d_state** out);
 
 /* Advance all lines by n_steps >= 0 steps; enqueues the work and returns after
  * checking the device error word of the completed steps (this synchronises
- * the stream once per call).
+ * the stream once per call, and every 1,024 steps of a longer one: an error ends
+ * the call there).
  *
  * One step (Sec. 3): gather, RICS drag / events, kick, move, charge-conserving
  * deposit; photon conversion into pairs; atmosphere refill; with

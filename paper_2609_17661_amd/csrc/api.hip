@@ -466,6 +466,10 @@ int read_scalars(pic1d_state* st, DevScalars& h) {
     return PIC1D_OK;
 }
 
+// Steps of a long call between two looks at the device scalars.  A look empties the queue:
+// some 50 us, a step and a half of the shortest.
+constexpr int READBACK_STEPS = 1024;
+
 int check_error(pic1d_state* st) {
     DevScalars h{};
     if (int rc = read_scalars(st, h)) return rc;
@@ -866,13 +870,23 @@ extern "C" {
 int pic1d_step(pic1d_state* st, int32_t n_steps) {
     if (!st || n_steps < 0) return fail(st, PIC1D_EINVAL, "bad arguments");
     if (st->frozen) return fail(st, PIC1D_ESTATE, "state frozen by an earlier error");
-    int32_t i = 0;
+    int32_t i = 0, seen = 0;
+    // after `k` more steps: in a long call the tiles are read back now and then, so that the
+    // particle kernel follows their number (and an error ends the call early)
+    auto done = [&](int32_t k) -> int {
+        i += k;
+        if (i - seen < READBACK_STEPS || i >= n_steps) return PIC1D_OK;
+        seen = i;
+        const int rc = check_error(st);
+        if (rc) prof_collect(st);
+        return rc;
+    };
     const int G = st->graph_len;
     if (G > 0 && !st->prof_on) {
         // eager up to the next multiple of G, then whole graphs
         while (i < n_steps && st->host_step % (uint64_t)G != 0) {
             if (int rc = enqueue_step(st)) return rc;
-            ++i;
+            if (int rc = done(1)) return rc;
         }
         const int S = st->cfg.sort_interval;
         const int flips = S > 0 ? (G / S) & 1 : 0;
@@ -885,11 +899,13 @@ int pic1d_step(pic1d_state* st, int32_t n_steps) {
             HIP_TRY(st, hipGraphLaunch(exec, st->stream));
             st->host_step += (uint64_t)G;
             st->cur ^= flips;
-            i += G;
+            if (int rc = done(G)) return rc;
         }
     }
-    for (; i < n_steps; ++i)
+    while (i < n_steps) {
         if (int rc = enqueue_step(st)) return rc;
+        if (int rc = done(1)) return rc;
+    }
     HIP_TRY(st, hipGetLastError());
     const int rc = check_error(st);
     prof_collect(st);

@@ -47,7 +47,7 @@ def _particles(sim):
 
 
 @pytest.mark.parametrize("rics", ["off", "exact", "table"])
-@pytest.mark.parametrize("ahead,graph", [(40, 0), (41, 0), (40, 4), (40, 5)])
+@pytest.mark.parametrize("ahead,graph", [(40, 0), (41, 0), (40, 4), (40, 5), (1100, 0), (1101, 4)])
 def test_particles_after_an_error_in_a_long_call(rics, ahead, graph):
     # (no pairs are made without scattering: a momentum that leaves the float range instead)
     want = "ENONFINITE" if rics == "off" else "ECAPACITY"

@@ -36,3 +36,27 @@ def test_graphs_are_kept_across_the_switch_of_parts(tmp_path):
     # one per live buffer set (a sort within each graph) and number of parts, in the first calls on either side
     assert r["captured"] == [2, 2] + [0] * 10
     assert r["kernels"][0] == [[2, 4, 128, 2]] and r["kernels"][1] == [[2, 2, 128, 4]]
+
+
+@pytest.mark.parametrize("graph", [0, 10])
+def test_a_long_call_follows_the_number_of_tiles(tmp_path, graph):
+    # an empty line that the atmosphere fills in the first step: 0 tiles when the call begins, more
+    # than 3 a CU for the rest of it
+    r = launches.run(tmp_path, f"""
+    graph = {graph}
+    """ + """
+    cells, ppc = 700, 800
+    cfg = workloads.small(r_eq=8.0, n_cells=cells, ppc=ppc, init="empty", rics="table", atmosphere=True, pairs=False,
+                          sort_interval=10, capacity=[256, 256, 4_000_000, 4_000_000])
+    sim = Pic1D(cfg)
+    if graph:
+        sim.set_graph(graph)
+    pushes()
+    sim.step(1500)
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    count = sim.moments(0)["count"]
+    result = dict(kernels=pushes(), tiles=sum((c + 511) // 512 for c in count) / n_cu)
+    sim.close()
+    """)
+    assert 3 < r["tiles"] <= 64
+    assert r["kernels"] == [[2, 2, 128, 4], [2, 4, 128, 2]]
