@@ -313,7 +313,8 @@ typedef struct {
     int32_t n_trials;            /* launch shapes timed                            */
     double ms_per_step_before;   /* with the shape the state had                   */
     double ms_per_step_after;    /* with the chosen shape                          */
-    int32_t push_ppt;            /* particles per lane of a particle-kernel tile   */
+    int32_t push_ppt;            /* particles per lane of a particle-kernel tile (see
+                                    pic1d_set_push_shape)                          */
     int32_t deposit_window;      /* cells of a wavefront's LDS deposit window      */
     int32_t sort_granularity;    /* sort bins per cell                             */
 } pic1d_tune_out;
@@ -336,8 +337,11 @@ int pic1d_autotune(pic1d_state* st, int32_t trial_steps, pic1d_tune_out* out);
 /* Set the particle kernel's launch shape directly: blocks per CU (1..32),
  * particles per lane of a tile (4, 8, 16) and the deposit window in cells (the
  * combinations pic1d_autotune lists, and a 64-cell window for the TABLE
- * backend; the MLP backend has 8 and 32 only).  The results do not depend on
- * it.  Errors: EINVAL (a shape that is not built), ESTATE. */
+ * backend; the MLP backend has 8 and 32 only).  A tile is a wavefront's work
+ * item, but for the shape a state starts with (8 particles per lane and the
+ * backend's default window; OFF, EXACT and TABLE): there the wavefronts take
+ * quarters or halves of tiles while these are few (up to 3 and 64 a CU), also
+ * when the shape is set here.  The results do not depend on it.  Errors: EINVAL (a shape that is not built), ESTATE. */
 int pic1d_set_push_shape(pic1d_state* st, int32_t blocks_per_cu, int32_t ppt, int32_t window);
 
 /* Granularity of the cell sort: after a sort every species' particles are in

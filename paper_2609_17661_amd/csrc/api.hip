@@ -113,7 +113,6 @@ struct pic1d_state {
     int push_bpc = 0;                              // push blocks per CU
     int ppt = PUSH_PPT_DEFAULT;                    // particles per lane per tile of the push
     int ww = 0;                                    // deposit window of the push (cells)
-    bool shape_set = false;                        // through pic1d_set_push_shape
     int tiles = 0;                                 // tiles of the planned push when last read back
     int sort_sub = SORT_SUB_DEFAULT;               // sort bins per cell
     int n_table_lines = 0;                         // MLP with table fallback: lines on their table
@@ -376,10 +375,11 @@ void prof_collect(pic1d_state* st) {
 // up to 64.  TABLE, us a launch with whole, half and quarter tiles: 31 / 20 / 18 at 124
 // tiles, 24 / 17 / 16 at 593, 32 / 24 / 25 at 902, 36 / 28 / 29 at 1,863, 43 / 38 / 40 at
 // 3,829, 63 / 56 / 63 at 7,846, 103 / 99 / 116 at 16,023; EXACT 30 / 23 / 23 at 901,
-// 58 / 52 / 59 at 7,849, 96 / 92 / 103 at 16,018.  A shape set through
-// pic1d_set_push_shape stays as it was set.
+// 58 / 52 / 59 at 7,849, 96 / 92 / 103 at 16,018.  The rule goes with the default tile and
+// window, however they came to be set, so that a shape that the tuner reports runs what the
+// tuner timed; any other shape takes whole tiles.
 int push_parts(const pic1d_state* st) {
-    if (st->shape_set || st->backend == RICS_MLP || st->ppt != PUSH_PPT_DEFAULT || st->ww != default_window(st->backend))
+    if (st->backend == RICS_MLP || st->ppt != PUSH_PPT_DEFAULT || st->ww != default_window(st->backend))
         return 0;
     return st->tiles <= 3 * st->n_cu ? 4 : st->tiles <= 64 * st->n_cu ? 2 : 0;
 }
@@ -932,6 +932,8 @@ int set_push_shape(pic1d_state* st, int blocks_per_cu, int ppt, int ww) {
     if (retile) {
         if (int rc = launch_plan(st, 0)) return rc;
         HIP_TRY(st, hipGetLastError());
+        DevScalars h{};
+        return read_scalars(st, h);            // (tiles of the new size)
     }
     return PIC1D_OK;
 }
@@ -940,7 +942,6 @@ int pic1d_set_push_shape(pic1d_state* st, int32_t blocks_per_cu, int32_t ppt, in
     if (!st || blocks_per_cu < 1 || blocks_per_cu > 32) return fail(st, PIC1D_EINVAL, "bad arguments");
     if (st->frozen) return fail(st, PIC1D_ESTATE, "state frozen by an earlier error");
     if (!push_kernel(st->backend, ppt, window)) return fail(st, PIC1D_EINVAL, "push shape not built");
-    st->shape_set = true;
     return set_push_shape(st, blocks_per_cu, ppt, window);
 }
 
