@@ -250,7 +250,6 @@ void carve(Carver& cv, const Layout& L, pic1d_state* st) {
     s->ann_thr = cv.take<uint32_t>(L.n_cells);
     s->ann_fill = cv.take<int32_t>(2 * (size_t)L.n_cells);
     s->ann_ctl = cv.take<int32_t>(4);
-    s->ann_tags = cv.take<uint32_t>(32 * ANN_TAGS);
     s->layer_cell = cv.take<int32_t>(std::max(L.n_layer, 1));
     s->layer_line = cv.take<int32_t>(std::max(L.n_layer, 1));
     s->layer_target = cv.take<int32_t>(std::max(L.n_layer, 1));
@@ -266,6 +265,7 @@ void carve(Carver& cv, const Layout& L, pic1d_state* st) {
     s->mlp_bias = cv.take<float>(L.mlp ? MLP_BIAS : 1);
     s->row_geo = cv.take<double>(L.mlp_fallback ? 3 * (size_t)L.n_lines * L.table_ns : 1);
     s->mlp_err_bits = cv.take<unsigned int>(L.mlp_fallback ? L.n_lines : 1);
+    s->ann_tags = cv.take<uint32_t>(32 * ANN_TAGS);
 }
 
 // The particle kernel of a backend at a tile shape (particles per lane, deposit

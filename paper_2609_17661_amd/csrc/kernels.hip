@@ -1491,6 +1491,7 @@ __global__ __launch_bounds__(256) void k_annih_plan(AnnihArgs a) {
             if ((double)N > nmax) k = (int)fmin(fmin((double)h0, (double)h1), ceil(((double)N - nmax) * 0.5));
             need = k > 0 ? h0 + h1 : 0;
         }
+        add_tags(a.ann_tags, k > 0 ? 0u - (uint32_t)h0 * cell_tag(g, 0) - (uint32_t)h1 * cell_tag(g, 1) : 0u);
         int total = 0;
         const int excl = block_excl_scan(need, total);
         if (total > 0 && threadIdx.x == 0) {
@@ -1513,8 +1514,6 @@ __global__ __launch_bounds__(256) void k_annih_plan(AnnihArgs a) {
             a.ann_k[g] = k;
             a.ann_thr[g] = k > 0 ? annih_threshold(k, min(h0, h1)) : 0u;
         }
-        if (total > 0)
-            add_tags(a.ann_tags, k > 0 ? 0u - (uint32_t)h0 * cell_tag(g, 0) - (uint32_t)h1 * cell_tag(g, 1) : 0u);
         __syncthreads();
     }
 }
