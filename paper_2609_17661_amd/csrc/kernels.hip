@@ -146,18 +146,6 @@ __device__ __forceinline__ Geo geo_lerp(const LineDev& L, const float4& lo, cons
     return geo_lerp(L, c, f);
 }
 
-__device__ __forceinline__ Geo geo_at(const LineDev& L, const float4* __restrict__ nodes, int node, float f) {
-    const float4 a = nodes[node];
-    const float4 b = nodes[node + 1];
-    Geo g;
-    g.b = fmaf(f, b.x - a.x, a.x);
-    g.mu = fmaf(f, b.y - a.y, a.y);
-    const float xr = fmaf(f, b.z - a.z, a.z);
-    g.ix2 = frcp(xr * xr);
-    g.by = g.b * L.inv_theta;
-    return g;
-}
-
 // What the RICS evaluations of one particle share: its geometry and (table
 // backend) its table rows.
 struct PartGeo {
@@ -248,30 +236,12 @@ __device__ __forceinline__ float drag_half(const PushArgs& a, const LineDev& L, 
 // Per-tile constants of the pusher (species of the tile, step, count buffers).
 struct TileCtx {
     uint64_t step;
-    const int32_t* hist_in;     // counts at the start of the step
     int32_t* hist_out;          // counts of the new positions
-    float qm;                   // charge / mass of the species (units of e/m_e)
     float inv_mass;             // m_e / m
     bool negative;              // negative charge
     bool gravity;               // the tile touches an atmosphere layer
     int item;                   // work item (the queue of the network's pusher)
 };
-
-// Append one particle to a segment; returns false (and flags ECAPACITY) if full.
-__device__ __forceinline__ bool append_particle(const PushArgs& a, int seg, int cell, float off, float u,
-                                                uint64_t id) {
-    const int slot = atomicAdd(&a.alloc[seg], 1);
-    if (slot >= a.seg_cap[seg]) {
-        set_error(&a.sc->err, -3);
-        return false;
-    }
-    const int64_t k = a.seg_base[seg] + slot;
-    a.cell[k] = cell;
-    a.off[k] = off;
-    a.u[k] = u;
-    a.id[k] = id;
-    return true;
-}
 
 struct Counts {
     int events = 0, pairs = 0, escaped = 0, absorbed = 0, clipped = 0, limited = 0, newton = 0, pushed = 0,
@@ -721,7 +691,6 @@ __attribute__((amdgpu_waves_per_eu(push_waves(BACKEND)))) void k_push(PushArgs a
     if (a.sc->err != 0) return;
     const uint64_t step = a.sc->step;
     if (blockIdx.x == 0 && threadIdx.x == 0) a.sc->step_field = step;
-    const int32_t* hist_in = (step & 1) ? a.hist[1] : a.hist[0];
     int32_t* hist_out = (step & 1) ? a.hist[0] : a.hist[1];
     const int total = SUB * a.tile_prefix[a.nseg];
     const int lane = threadIdx.x & 63;
@@ -899,10 +868,8 @@ __attribute__((amdgpu_waves_per_eu(push_waves(BACKEND)))) void k_push(PushArgs a
         TileCtx T;
         T.step = step;
         T.item = ww.t;
-        T.hist_in = hist_in;
         T.hist_out = hist_out;
         T.negative = (sp == 0 || sp == 2);
-        T.qm = T.negative ? -1.0f : (sp == 1 ? 1.0f : a.qm_ion);
         T.inv_mass = (sp == 3) ? a.inv_mass_ion : 1.0f;
         T.gravity = a.gravity && any && ((double)lo <= L.atm_depth + 1.0 ||
                                          (double)(L.n_cells - 1 - hi) <= L.atm_depth + 1.0);
@@ -1690,7 +1657,6 @@ __device__ __forceinline__ bool annih_rank64(const AnnihArgs& a, uint64_t key, i
     const int lane = threadIdx.x & 63;
     const uint32_t lo = (uint32_t)key, hi = (uint32_t)(key >> 32);
     int rank = 0;
-#pragma unroll 4
     for (int i = 0; i < m; ++i) rank += lane_word(hi, i) < hi ? 1 : 0;
     bool take = lane < m && rank < k;
     if (__popcll(__ballot(take)) != k) {

@@ -141,17 +141,17 @@ struct PlainOperand {
 // write eight different accumulators (independent chains); each tile sums in the
 // order K0 hi, K0 mid, K0 lo, K1 hi, ...  An operand is formed right before its MFMAs, so
 // that only one is live (12 registers instead of 48), and the scheduler is kept from
-// hoisting the next one's: two wavefronts then fit a SIMD without spills.  They
+// hoisting the next one's: two wavefronts then fit a SIMD (the pusher spills four
+// registers, outside of its loop over the layers).  They
 // overlap one's vector with the other's matrix instructions (which leave the vector
 // unit half of their 16 cycles; mixing the two within a wavefront, one MFMA to four
-// vector instructions, was 6% slower).  bias == nullptr starts from zero.
-template <class WPtr, class Operand>
+// vector instructions, was 6% slower).
+template <class WPtr>
 __device__ __forceinline__ void hidden_layer(WPtr w, int base, const float* __restrict__ bias, const f32x4 (&in)[8],
-                                             f32x4 (&out)[8], Operand operand) {
+                                             f32x4 (&out)[8]) {
     const int lane = threadIdx.x & 63, g = lane >> 4;
 #pragma unroll
-    for (int T = 0; T < 8; ++T)
-        out[T] = bias ? *reinterpret_cast<const f32x4*>(bias + 16 * T + 4 * g) : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    for (int T = 0; T < 8; ++T) out[T] = *reinterpret_cast<const f32x4*>(bias + 16 * T + 4 * g);
 #pragma unroll
     for (int K = 0; K < 4; ++K) {
         bf16x8 wt[8];
@@ -159,7 +159,7 @@ __device__ __forceinline__ void hidden_layer(WPtr w, int base, const float* __re
         for (int T = 0; T < 8; ++T) wt[T] = w[(base + T * 4 + K) * 64 + lane];
         __builtin_amdgcn_sched_barrier(0);       // the weights' latency passes under the operand
         Split3 op;
-        operand(in[2 * K], in[2 * K + 1], op);
+        SiluOperand()(in[2 * K], in[2 * K + 1], op);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int T = 0; T < 8; ++T) out[T] = mfma(wt[T], op.hi, out[T]);
@@ -184,7 +184,7 @@ __device__ __forceinline__ f32x4 mlp_group_forward(WPtr wf, const float* __restr
 #pragma unroll 1
     for (int h = 0; h < 3; ++h) {
         f32x4 next[8];
-        hidden_layer(wf, FT_H0 + 32 * h, bias + MLP_W * (h + 1), acc, next, SiluOperand());
+        hidden_layer(wf, FT_H0 + 32 * h, bias + MLP_W * (h + 1), acc, next);
 #pragma unroll
         for (int T = 0; T < 8; ++T) acc[T] = next[T];
     }
