@@ -25,6 +25,7 @@ constexpr int SORT_TILE = SORT_TPB * SORT_U;    // consecutive slots of a segmen
 constexpr int SORT_W = 2048;                    // bins of a tile ranked at a time in LDS
 constexpr int SORT_PASSES = 8;                  // windows of SORT_W bins at most; wider tiles go to the global bins
 
+constexpr int ANN_SEARCHES = 1024;              // cells that the annihilation may search in full, ever
 constexpr int ANN_TAGS = 64;                    // replicas of the annihilation's tag sum
 constexpr int GATHER_BLOCKS_PER_CU = 16;        // blocks of the annihilation gather per CU
 
@@ -167,7 +168,7 @@ struct AnnihArgs {
     uint32_t* ann_tags;         // ANN_TAGS replicas, 128 bytes apart: the tags of the particles in the cells over
                                 //   the limit less those of their counts; they sum to zero
     int32_t* ann_ctl;           // [0] records allocated, [1] cells over the limit (this step),
-                                //   [2] its copy for the field kernel
+                                //   [2] its copy for the field kernel, [3] cells searched in full since init
     uint64_t* cand_key;         // candidate records: ranking key ...
     int32_t* cand_slot;         // ... and slot within its species segment
     int64_t cand_cap;           // records available

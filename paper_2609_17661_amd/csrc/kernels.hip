@@ -1424,7 +1424,11 @@ __device__ __forceinline__ uint64_t annih_key(uint64_t step, uint64_t id, uint32
 // The gather records only the candidates whose key's high word is at most the
 // cell's threshold, which admits lambda = k + 8 k^1/2 + 20 of the m keys of the
 // smaller species on average (the keys are uniform): fewer than k of them pass with
-// a probability below 1e-12 a cell, and k_field then records the whole cell.
+// a probability below 1e-12 a cell, and k_field then searches the segment for the whole
+// cell.  Keys are uniform because ids differ: a program that sets the same id many times
+// could have every cell searched, hours of work on a long line.  So after ANN_SEARCHES
+// searches a state records every candidate from its next step on, and a cell that would
+// have been the next one to search keeps its pairs for that step.
 __device__ __forceinline__ uint32_t annih_threshold(int k, int m) {
     const float lam = (float)k + 8.0f * sqrtf((float)k) + 20.0f;
     return lam < (float)m ? (uint32_t)(lam / (float)m * 4294967040.0f) : 0xffffffffu;
@@ -1445,6 +1449,7 @@ __global__ __launch_bounds__(256) void k_annih_plan(AnnihArgs a) {
     if (block_stopped(a.sc)) return;
     const uint64_t step = a.sc->step;
     const int32_t* hist_out = a.hist[(step & 1) ^ 1];
+    const bool all = a.sc->ann_all != 0;
     __shared__ int s_base;
     for (int g0 = blockIdx.x * 256; g0 < a.n_total; g0 += gridDim.x * 256) {
         const int g = g0 + (int)threadIdx.x;
@@ -1479,7 +1484,7 @@ __global__ __launch_bounds__(256) void k_annih_plan(AnnihArgs a) {
         }
         if (g < a.n_total) {
             a.ann_k[g] = k;
-            a.ann_thr[g] = k > 0 ? annih_threshold(k, min(h0, h1)) : 0u;
+            a.ann_thr[g] = k > 0 ? (all ? 0xffffffffu : annih_threshold(k, min(h0, h1))) : 0u;
         }
         __syncthreads();
     }
@@ -1687,20 +1692,29 @@ struct AnnihCell {
 // and ranked; up to 512 in registers (annih_select_regs); beyond, a
 // most-significant-bit-first radix select over the records in memory.  Returns (to
 // every lane) the annihilation current in the deposit's units (2^-28 cell); the
-// caller adds it to J[g] and takes k off the cell's e-/e+ counts.  Latency-bound: two
+// caller adds it to J[g] and takes the pairs removed (k, or none where the searches are
+// used up) off the cell's e-/e+ counts.  Latency-bound: two
 // dependent round trips per cell, and the removed particles' scattered lines.  With
 // every candidate recorded and k wave-wide minima per species k_field took 57 us on
 // a 512-cell line, 51 us on 9,973 cells and 92 us on 65,536 (600 per cell); 21, 24
 // and 71 us now.
-__device__ long long annihilate_cell(const AnnihArgs& a, const AnnihCell& c, uint64_t step, int* hist) {
+__device__ long long annihilate_cell(const AnnihArgs& a, const AnnihCell& c, uint64_t step, int* hist, int& removed) {
     const int lane = threadIdx.x & 63;
     const int k = c.k;
+    removed = k;
     int m[2] = {c.r0, c.r1};
     if (m[0] > c.h0 || m[1] > c.h1) {
         if (lane == 0) set_error(&a.sc->err, -4);
         return 0;
     }
     if (m[0] < k || m[1] < k) {
+        int n = 0;
+        if (lane == 0) n = atomicAdd(&a.ann_ctl[3], 1);
+        if (__builtin_amdgcn_readfirstlane(n) >= ANN_SEARCHES) {
+            if (lane == 0) a.sc->ann_all = 1;
+            removed = 0;
+            return 0;
+        }
         const int cl = c.g - a.lines[c.line].cell_base;
         for (int s = 0; s < 2; ++s) {
             if (m[s] >= k) continue;
@@ -1845,10 +1859,11 @@ __global__ __launch_bounds__(256) void k_field(FieldArgs f, BookArgs b) {
                     m &= m - 1ull;
                     auto of = [&](int v) { return __builtin_amdgcn_readlane(v, lead); };
                     const AnnihCell c{gw + lead, of(k), of(line), of(h0), of(h1), of(r0), of(r1), of(off)};
-                    const long long d = annihilate_cell(f.an, c, step, sHist[wid]);
+                    int removed;
+                    const long long d = annihilate_cell(f.an, c, step, sHist[wid], removed);
                     if (lane == lead) {
                         dJ = d;
-                        k_own = k;
+                        k_own = removed;
                     }
                 }
                 if (k_own > 0) {

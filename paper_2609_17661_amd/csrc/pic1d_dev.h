@@ -77,7 +77,7 @@ struct DevScalars {
     int32_t tiles;        // tiles of the planned push (read back with the error word)
     uint64_t step_field;  // the running step, as k_field reads it (k_field advances `step`)
     int32_t live;         // the buffer set that holds the particles (a sort that took place moves them)
-    int32_t pad;
+    int32_t ann_all;      // 1: the annihilation records every candidate (its keys are not spread)
 };
 
 // ---------------------------------------------------------------------------
