@@ -255,6 +255,7 @@ void carve(Carver& cv, const Layout& L, pic1d_state* st) {
     s->layer_target = cv.take<int32_t>(std::max(L.n_layer, 1));
     s->counters = cv.take<unsigned long long>((size_t)NCOUNT * CNT_REPL * L.n_lines);
     s->sc = cv.take<DevScalars>(1);
+    s->ann_tags = cv.take<uint32_t>(32 * ANN_TAGS);        // (read with the scalars, in every step)
     s->rho = cv.take<unsigned long long>(L.max_nodes);
     s->photons = cv.take<PhotonRec>(c_pairs(L) ? (size_t)PHOTON_REPL * L.photon_region : 1);
     s->n_photons = cv.take<int32_t>(PHOTON_REPL);
@@ -265,7 +266,6 @@ void carve(Carver& cv, const Layout& L, pic1d_state* st) {
     s->mlp_bias = cv.take<float>(L.mlp ? MLP_BIAS : 1);
     s->row_geo = cv.take<double>(L.mlp_fallback ? 3 * (size_t)L.n_lines * L.table_ns : 1);
     s->mlp_err_bits = cv.take<unsigned int>(L.mlp_fallback ? L.n_lines : 1);
-    s->ann_tags = cv.take<uint32_t>(32 * ANN_TAGS);
 }
 
 // The particle kernel of a backend at a tile shape (particles per lane, deposit
@@ -377,7 +377,8 @@ void prof_collect(pic1d_state* st) {
 // 3,829, 63 / 56 / 63 at 7,846, 103 / 99 / 116 at 16,023; EXACT 30 / 23 / 23 at 901,
 // 58 / 52 / 59 at 7,849, 96 / 92 / 103 at 16,018.  The rule goes with the default tile and
 // window, however they came to be set, so that a shape that the tuner reports runs what the
-// tuner timed; any other shape takes whole tiles.
+// tuner timed; any other shape takes whole tiles, and so do the table lines of a state of the
+// network (its own lines come from a queue of half tiles; not measured there).
 int push_parts(const pic1d_state* st) {
     if (st->backend == RICS_MLP || st->ppt != PUSH_PPT_DEFAULT || st->ww != default_window(st->backend))
         return 0;
@@ -797,7 +798,7 @@ int enqueue_step(pic1d_state* st) {
             hipLaunchKernelGGL(k_annih_gather, dim3(GATHER_BLOCKS_PER_CU * st->n_cu), dim3(256), 0, st->stream, an);
             prof_end(st, pk);
         }
-        // Ampere; its last block plans the next push and advances the step counter
+        // Ampere; a block of its own plans the next push and advances the step counter
         const int pk = prof_begin(st, 2);
         // 64 cells per wavefront; with annihilation 4, or 1 up to 64 cells per CU in all:
         // there four selections one after another leave the chip idle (9,973 cells: k_field

@@ -25,6 +25,7 @@ constexpr int SORT_TILE = SORT_TPB * SORT_U;    // consecutive slots of a segmen
 constexpr int SORT_W = 2048;                    // bins of a tile ranked at a time in LDS
 constexpr int SORT_PASSES = 8;                  // windows of SORT_W bins at most; wider tiles go to the global bins
 
+constexpr int FIELD_ROUND = 4096;               // blocks of k_field from which its bookkeeping comes first
 constexpr int ANN_SEARCHES = 1024;              // cells that the annihilation may search in full, ever
 constexpr int ANN_TAGS = 64;                    // replicas of the annihilation's tag sum
 constexpr int GATHER_BLOCKS_PER_CU = 16;        // blocks of the annihilation gather per CU

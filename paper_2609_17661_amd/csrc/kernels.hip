@@ -668,8 +668,10 @@ __attribute__((amdgpu_waves_per_eu(push_waves(BACKEND)))) void k_push(PushArgs a
     // depending on where it is: the wavefronts take their items from a queue, and half
     // a planned tile at a time, as a few of these fill a launch (4.9e6 particles on 16,384
     // cells: 2.40 ms where each XCD walked its own range of whole tiles, the wavefronts
-    // of the cheap ranges idle 45% of the launch; 1.65 ms so, with two wavefronts per
-    // SIMD; three spill, 1.87 ms).  Bound by vector issue: 1,500 instructions and 308
+    // of the cheap ranges idle 45% of the launch; 1.56 to 1.65 ms so, by card, with two
+    // wavefronts per SIMD; three spill, 1.87 ms beside 1.65).  States of fewer items than
+    // wavefronts leave some without one (10 steps of 4,000 cells of 60 pairs 9.3 ms, 13.1
+    // before the queue; of 1,000 cells 5.2 and 6.1; 500 cells of 30 pairs 3.3 and 4.7).  Bound by vector issue: 1,500 instructions and 308
     // MFMAs per 16 evaluations.
     constexpr bool QUEUE = BACKEND == RICS_MLP;
     using VecI = std::conditional_t<PPT == 2, int2, int4>;
@@ -1356,6 +1358,11 @@ __device__ __forceinline__ int block_excl_scan(int v, int& total) {
 // Nothing (false) after an error.
 // ---------------------------------------------------------------------------
 __device__ bool bookkeeping(const BookArgs& b) {
+    const int nseg = b.nseg;
+    const int per = (nseg + 255) / 256;
+    const int s0 = threadIdx.x * per, s1 = min(s0 + per, nseg);
+    auto count = [&](int s) { return min(b.new_count ? b.new_count[s] : b.alloc[s], b.seg_cap[s]); };
+    const int first = s0 < s1 ? count(s0) : 0;       // (on its way while the questions below are answered)
     // did the annihilation find the particles in the cells over the limit that are counted
     // there?  (asked by the second wavefront while the first reads the error word)
     __shared__ uint32_t s_differ;
@@ -1371,12 +1378,9 @@ __device__ bool bookkeeping(const BookArgs& b) {
     }
     if (b.n_photons && threadIdx.x < PHOTON_REPL) b.n_photons[threadIdx.x] = 0;
     if (threadIdx.x == 0) b.queue[0] = 0;
-    const int nseg = b.nseg;
-    const int per = (nseg + 255) / 256;
-    const int s0 = threadIdx.x * per, s1 = min(s0 + per, nseg);
     int sum = 0, n_last = 0;
     for (int s = s0; s < s1; ++s) {
-        const int n = min(b.new_count ? b.new_count[s] : b.alloc[s], b.seg_cap[s]);
+        const int n = s == s0 ? first : count(s);
         b.n_cur[s] = n;
         b.alloc[s] = n;
         n_last = n;
@@ -1801,20 +1805,23 @@ __device__ long long annihilate_cell(const AnnihArgs& a, const AnnihCell& c, uin
 // the step's bookkeeping (live counts, the next push's tile plan) and advances the
 // step counter; the cells read the running step from the copy the push left.
 __global__ __launch_bounds__(256) void k_field(FieldArgs f, BookArgs b) {
+    // One block plans the next push and advances the step counter, beside the cells' blocks
+    // rather than before one of them (none of them reads what it writes, but for the
+    // allocation counters, which annih_record_all clamps to the same value that they are
+    // given here): the last one, or, where the chip holds the grid only in rounds, the first,
+    // so that its chain of round trips does not come after theirs (380,000 cells in a quiet
+    // step 17.4 us, 19.7 as the last; 512 cells 0.25 us a step the other way).
     const int nb = gridDim.x - 1;
-    // (the last block asks for itself, all its wavefronts together)
-    if ((int)blockIdx.x != nb && f.sc->err != 0) return;
+    const int block = nb >= FIELD_ROUND ? (int)blockIdx.x - 1 : (int)blockIdx.x == nb ? -1 : (int)blockIdx.x;
+    // (it asks for itself, all its wavefronts together)
+    if (block >= 0 && f.sc->err != 0) return;
     const uint64_t step = f.sc->step_field;
     const int n = f.n_total;
     const int hin = (int)(step & 1);
     int* hist_in = f.hist[hin];
     int* hist_out = f.hist[hin ^ 1];
     const bool averaging = f.avg_start >= 0 && step >= (uint64_t)f.avg_start;
-    // the last block plans the next push and advances the step counter, beside the
-    // cells' blocks rather than before one of them (none of them reads what it writes,
-    // but for the allocation counters, which annih_record_all clamps to the same value
-    // that they are given here)
-    if ((int)blockIdx.x == nb) {
+    if (block < 0) {
         if (!bookkeeping(b)) return;
         if (threadIdx.x == 0) {
             if (b.sc->err == 0) b.sc->step += 1;
@@ -1836,7 +1843,7 @@ __global__ __launch_bounds__(256) void k_field(FieldArgs f, BookArgs b) {
     const int wpb = blockDim.x >> 6;
     const int nw = nb * wpb;
     const int cpw = (f.annihilation && f.an.ann_ctl[2] != 0) ? max(1, min(4, (n + nw - 1) / nw)) : 64;
-    for (int gw = (blockIdx.x * wpb + wid) * cpw; gw < n; gw += nw * cpw) {
+    for (int gw = (block * wpb + wid) * cpw; gw < n; gw += nw * cpw) {
         const int g = gw + lane;
         const bool own = lane < cpw && g < n;
         long long dJ = 0;        // this lane's cell: annihilation current and pairs removed
