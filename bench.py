@@ -72,7 +72,7 @@ PROFILE_HBM = os.path.join(ROOT, "profiles", "k_push_cfg2_table_hbm.md")
 CAL_BYTES = 256 << 20      # bytes read (and written) by one calibration copy
 
 
-KERNEL_SOURCES = ("kernels.hip", "kernels.h", "pic1d_dev.h", "rics_dev.h", "mlp_dev.h")
+KERNEL_SOURCES = ("kernels.hip", "kernels.h", "pic1d_dev.h", "slots.h", "rics_dev.h", "mlp_dev.h")
 
 
 def sources_digest():

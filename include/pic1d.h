@@ -29,9 +29,12 @@
  *   - All device work is enqueued on the hipStream_t given in the config;
  *     calls that return data to host buffers synchronise that stream.
  *   - One state handle must not be used from two threads at once.
- *   - After PIC1D_ECAPACITY or PIC1D_ENONFINITE the state is frozen: further
+ *   - After PIC1D_ECAPACITY or PIC1D_ENONFINITE (or PIC1D_EDEVICE from the check
+ *     that cell counts and particles agree) the state is frozen: further
  *     pic1d_step calls return PIC1D_ESTATE; moments and particles stay readable
  *     but reflect the partially completed step in which the error occurred.
+ *   - Device memory is the caller's.  A state besides holds up to 4 MiB of pinned
+ *     host memory, which results come back through.
  */
 #ifndef PIC1D_H
 #define PIC1D_H
@@ -210,7 +213,8 @@ int pic1d_workspace_size(const pic1d_config* cfg, size_t* bytes);
  * (Philox-uniform offsets, stratified ppc_init per cell).  cfg and the arrays
  * it points to are copied; the workspace stays owned by the caller and must
  * outlive the state.  *out receives the handle (NULL on error).
- * Errors: EINVAL (config), ENOMEM (workspace too small), EDEVICE. */
+ * Errors: EINVAL (config), ENOMEM (workspace too small), EDEVICE (also where the
+ * state's pinned host memory is refused). */
 int pic1d_init(const pic1d_config* cfg, pic1d_state** out);
 
 /* Advance all lines by n_steps >= 0 steps; enqueues the work and returns after
@@ -254,7 +258,8 @@ int pic1d_step(pic1d_state* st, int32_t n_steps);
  * Errors: EINVAL (line out of range), EDEVICE. */
 int pic1d_moments(pic1d_state* st, int32_t line, int32_t flags, pic1d_moments_out* out);
 
-/* Release the state (not the workspace).  NULL is a no-op. */
+/* Release the state and its pinned host memory (not the workspace); may wait for the
+ * device.  NULL is a no-op. */
 void pic1d_free(pic1d_state* st);
 
 /* Text of the last error on st (or of the last failed init when st is NULL);
@@ -269,7 +274,8 @@ int pic1d_get_particles(pic1d_state* st, int32_t line, int32_t species, int64_t 
                         int64_t* count, int32_t* cell, float* offset, float* u, uint64_t* id);
 
 /* Replace one species of one line by `count` particles from host arrays.
- * cell in [0, n_cells), offset in [0, 1).  Errors: EINVAL, ECAPACITY. */
+ * cell in [0, n_cells), offset in [0, 1).  id keys the particle's draws (events,
+ * annihilation): those of a species should differ.  Errors: EINVAL, ECAPACITY. */
 int pic1d_set_particles(pic1d_state* st, int32_t line, int32_t species, int64_t count,
                         const int32_t* cell, const float* offset, const float* u,
                         const uint64_t* id);

@@ -2023,7 +2023,8 @@ __device__ __forceinline__ void annih_gather(const AnnihArgs& a) {
 // the grid's blocks all find a chunk that long, and four below.  70 us on a 65,536-cell
 // line of 600 per cell, 109 us on eight lines of 32,768, 12 us on one of 9,973 (81, 134
 // and 12 us by fours, 72, 112 and 15 us by eights; 88, 137 and 13.5 us by fours with one
-// load a particle).  Eight wavefronts per SIMD: with one less 77 and 119 us.
+// load a particle); the tag sums add 1.4, 1.2 and 0.4 us.  Eight wavefronts per SIMD: with
+// one less 77 and 119 us.
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k_annih_gather(AnnihArgs a) {
     if (a.sc->err != 0) return;
     // a copy of the over-limit flag for k_field, which clears [1] for the next step
