@@ -1146,10 +1146,12 @@ __device__ __forceinline__ void convert_photons(const ConvertArgs& a, int blk, i
     const int lane = threadIdx.x & 63;
     constexpr int RPL = PHOTON_REPL / 64;      // regions per lane
     if (threadIdx.x < 64) {
+        // after an error there is nothing to convert, for the whole block (see block_stopped)
+        const bool stopped = a.sc->err != 0;
         int f[RPL], sum = 0;
 #pragma unroll
         for (int k = 0; k < RPL; ++k) {
-            f[k] = min(a.n_photons[lane * RPL + k], a.photon_region);
+            f[k] = stopped ? 0 : min(a.n_photons[lane * RPL + k], a.photon_region);
             sum += f[k];
         }
         int inc = sum;
@@ -1270,6 +1272,7 @@ __device__ __forceinline__ void convert_photons(const ConvertArgs& a, int blk, i
 // target with co-located (e-, ion) pairs; one wavefront per layer cell.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void refill_atmosphere(const AtmArgs& a, int blk, int nblk) {
+    if (a.sc->err != 0) return;
     const uint64_t step = a.sc->step;
     int32_t* hist_out = a.hist[(step & 1) ^ 1];
     const int lane = threadIdx.x & 63;
@@ -1323,7 +1326,6 @@ __device__ __forceinline__ void refill_atmosphere(const AtmArgs& a, int blk, int
 // and 3).  The two touch different segments and different species counts, so they
 // run side by side.
 __global__ __launch_bounds__(256) void k_append(ConvertArgs ca, AtmArgs aa, int conv_blocks) {
-    if (block_stopped(ca.sc)) return;
     if ((int)blockIdx.x < conv_blocks) convert_photons(ca, blockIdx.x, conv_blocks);
     else refill_atmosphere(aa, blockIdx.x - conv_blocks, gridDim.x - conv_blocks);
 }
@@ -1362,36 +1364,38 @@ __device__ bool bookkeeping(const BookArgs& b) {
     const int per = (nseg + 255) / 256;
     const int s0 = threadIdx.x * per, s1 = min(s0 + per, nseg);
     auto count = [&](int s) { return min(b.new_count ? b.new_count[s] : b.alloc[s], b.seg_cap[s]); };
-    const int first = s0 < s1 ? count(s0) : 0;       // (on its way while the questions below are answered)
     // did the annihilation find the particles in the cells over the limit that are counted
-    // there?  (asked by the second wavefront while the first reads the error word)
+    // there?  (asked by the second wavefront while the first reads the error word; the
+    // scan's barriers make both known to the block, see block_stopped)
+    __shared__ int s_err;
     __shared__ uint32_t s_differ;
+    if (threadIdx.x == 0) s_err = b.sc->err;
     if (threadIdx.x >= 64 && threadIdx.x < 128) {
         const int lane = threadIdx.x & 63;
-        const uint32_t sum = wave_sum_last(b.ann_tags && lane < ANN_TAGS ? b.ann_tags[32 * lane] : 0u);
-        if (lane == 63) s_differ = sum;
+        const uint32_t differ = wave_sum_last(b.ann_tags && lane < ANN_TAGS ? b.ann_tags[32 * lane] : 0u);
+        if (lane == 63) s_differ = differ;
     }
-    if (block_stopped(b.sc)) return false;
+    int sum = 0, n_last = 0;
+    for (int s = s0; s < s1; ++s) {
+        n_last = count(s);
+        sum += tiles_of(n_last, b.tile);
+    }
+    int total;
+    int run = block_excl_scan(sum, total);
+    if (s_err != 0) return false;
     if (s_differ != 0u) {
         if (threadIdx.x == 0) set_error(&b.sc->err, -4);
         return false;
     }
     if (b.n_photons && threadIdx.x < PHOTON_REPL) b.n_photons[threadIdx.x] = 0;
     if (threadIdx.x == 0) b.queue[0] = 0;
-    int sum = 0, n_last = 0;
     for (int s = s0; s < s1; ++s) {
-        const int n = s == s0 ? first : count(s);
+        // (one segment per thread up to 256 segments: its count is still in a register)
+        const int n = per == 1 ? n_last : count(s);
         b.n_cur[s] = n;
         b.alloc[s] = n;
-        n_last = n;
-        sum += tiles_of(n, b.tile);
-    }
-    int total;
-    int run = block_excl_scan(sum, total);
-    for (int s = s0; s < s1; ++s) {
         b.tile_prefix[s] = run;
-        // (one segment per thread up to 256 segments: its count is still in a register)
-        run += tiles_of(per == 1 ? n_last : b.n_cur[s], b.tile);
+        run += tiles_of(n, b.tile);
     }
     if (threadIdx.x == 255) {
         b.tile_prefix[nseg] = total;
@@ -1450,7 +1454,8 @@ __device__ __forceinline__ void add_tags(uint32_t* tags, uint32_t v) {
 // run of candidate records (room for all their e- then their e+), one allocation
 // per block.
 __global__ __launch_bounds__(256) void k_annih_plan(AnnihArgs a) {
-    if (block_stopped(a.sc)) return;
+    __shared__ int s_err;                 // (read once for the block, see block_stopped)
+    if (threadIdx.x == 0) s_err = a.sc->err;
     const uint64_t step = a.sc->step;
     const int32_t* hist_out = a.hist[(step & 1) ^ 1];
     const bool all = a.sc->ann_all != 0;
@@ -1470,6 +1475,7 @@ __global__ __launch_bounds__(256) void k_annih_plan(AnnihArgs a) {
         add_tags(a.ann_tags, k > 0 ? 0u - (uint32_t)h0 * cell_tag(g, 0) - (uint32_t)h1 * cell_tag(g, 1) : 0u);
         int total = 0;
         const int excl = block_excl_scan(need, total);
+        if (s_err != 0) return;
         if (total > 0 && threadIdx.x == 0) {
             s_base = atomicAdd(&a.ann_ctl[0], total);
             atomicOr(&a.ann_ctl[1], 1);
