@@ -38,8 +38,8 @@ __device__ __forceinline__ int wave_sum_i(int v) {
     return v;
 }
 
-// The sum over a wavefront, in its last lane, by register moves between lanes (a tenth of
-// the latency of the shuffles).
+// The sum over a wavefront, in its last lane, by register moves between lanes (the shuffles
+// above go through the LDS unit).
 __device__ __forceinline__ uint32_t wave_sum_last(uint32_t v) {
     int x = (int)v;
     x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, true);     // row_shr 1, 2, 4, 8:
@@ -671,8 +671,8 @@ __attribute__((amdgpu_waves_per_eu(push_waves(BACKEND)))) void k_push(PushArgs a
     // of the cheap ranges idle 45% of the launch; 1.56 to 1.65 ms so, by card, with two
     // wavefronts per SIMD; three spill, 1.87 ms beside 1.65).  States of fewer items than
     // wavefronts leave some without one (10 steps of 4,000 cells of 60 pairs 9.3 ms, 13.1
-    // before the queue; of 1,000 cells 5.2 and 6.1; 500 cells of 30 pairs 3.3 and 4.7).  Bound by vector issue: 1,500 instructions and 308
-    // MFMAs per 16 evaluations.
+    // before the queue; of 1,000 cells 5.2 and 6.1; 500 cells of 30 pairs 3.3 and 4.7).
+    // Bound by vector issue: 1,500 instructions and 308 MFMAs per 16 evaluations.
     constexpr bool QUEUE = BACKEND == RICS_MLP;
     using VecI = std::conditional_t<PPT == 2, int2, int4>;
     using VecF = std::conditional_t<PPT == 2, float2, float4>;
@@ -1807,7 +1807,7 @@ __device__ long long annihilate_cell(const AnnihArgs& a, const AnnihCell& c, uin
 }
 
 // Ampere's law with the static twist current (Sec. 3): E -= 4 pi (j - j_twist),
-// plus time averages and the reset of the step's accumulators.  Block 0 also does
+// plus time averages and the reset of the step's accumulators.  A block of its own does
 // the step's bookkeeping (live counts, the next push's tile plan) and advances the
 // step counter; the cells read the running step from the copy the push left.
 __global__ __launch_bounds__(256) void k_field(FieldArgs f, BookArgs b) {
